@@ -19,7 +19,7 @@ using namespace gp::rt;
 struct gp_data {
   gp_op* op = nullptr;
   int T = 0, P = 0, K = 0, N = 0;
-  double* X = nullptr;    // T x K
+  double* X = nullptr;    // T x data_design_stride(K)
   double* G = nullptr;    // [X'X | R | S]
   double* YX = nullptr;   // [K][N]
   double* Bt = nullptr;   // [P][K][N]
@@ -71,7 +71,8 @@ int gp_data_create(gp_op* op, int T, int P, const double* X_host, const double* 
   d->P = P;
   d->K = K;
   d->N = N;
-  d->nX = (size_t)T * K;
+  const int Ks = data_design_stride(K);
+  d->nX = (size_t)T * Ks;
   d->nG = (size_t)K * K + (size_t)K * K * P + (size_t)P * K * K * P;
   d->nYX = (size_t)K * N;
   d->nBt = std::max<size_t>(1, (size_t)P * K * N);
@@ -92,7 +93,9 @@ int gp_data_create(gp_op* op, int T, int P, const double* X_host, const double* 
     release(d);
     return st;
   }
-  hipError_t e = hipMemcpyAsync(d->X, X_host, d->nX * sizeof(double), hipMemcpyHostToDevice, c->stream);
+  std::vector<double> Xp(d->nX, 0.0);
+  for (int t = 0; t < T; ++t) std::copy_n(X_host + (size_t)t * K, K, Xp.data() + (size_t)t * Ks);
+  hipError_t e = hipMemcpyAsync(d->X, Xp.data(), d->nX * sizeof(double), hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess)
     e = launch_data_tensors(c->stream, T, K, P, N, d->X, Y, d->G, d->YX, d->Bt, d->Dt, d->YY, d->dY, d->dd);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);

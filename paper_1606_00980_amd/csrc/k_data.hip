@@ -30,67 +30,206 @@ namespace {
 
 constexpr int DT = 256;   // threads per workgroup
 
-// One thread per global tensor entry.
-__global__ __launch_bounds__(DT) void k_data_globals(int T, int K, int P, const double* __restrict__ X,
-                                                     double* __restrict__ G) {
-  const int e = blockIdx.x * DT + threadIdx.x;
-  const int nXX = K * K, nR = K * K * P, nS = P * K * K * P;
-  if (e >= nXX + nR + nS) return;
-  double s = 0.0;
-  if (e < nXX) {
-    const int k = e / K, l = e % K;
-    for (int t = P; t < T; ++t) s += X[t * K + k] * X[t * K + l];
-  } else if (e < nXX + nR) {
-    const int i = e - nXX, k = i / (K * P), l = (i / P) % K, p = i % P;
-    for (int t = P; t < T; ++t) s += X[t * K + k] * X[(t - 1 - p) * K + l];
-  } else {
-    const int i = e - nXX - nR;
-    const int p = i / (K * K * P), k = (i / (K * P)) % K, l = (i / P) % K, q = i % P;
-    for (int t = P; t < T; ++t) s += X[(t - 1 - p) * K + k] * X[(t - 1 - q) * K + l];
+// Compile-time lags: for_lags<P>(f) calls f(Lag<0>), .., f(Lag<P - 1>).
+template <int V> struct Lag { static constexpr int v = V; };
+template <int P, int I = 0, typename F>
+__device__ __forceinline__ void for_lags(const F& f) {
+  if constexpr (I < P) {
+    f(Lag<I>{});
+    for_lags<P, I + 1>(f);
   }
-  G[e] = s;
 }
 
-// blockIdx.y = tensor entry (YX, Bt, Dt, YY, dY, dd in that order); threads over voxels.
-// The design is staged in LDS (T*K doubles, dynamic).
-__global__ __launch_bounds__(DT) void k_data_tensors(int T, int K, int P, int N, const double* __restrict__ X,
-                                                     const double* __restrict__ Y, double* __restrict__ YX,
-                                                     double* __restrict__ Bt, double* __restrict__ Dt,
-                                                     double* __restrict__ YY, double* __restrict__ dY,
-                                                     double* __restrict__ dd) {
-  extern __shared__ double sX[];
-  for (int i = threadIdx.x; i < T * K; i += DT) sX[i] = X[i];
-  __syncthreads();
-  const int n = blockIdx.x * DT + threadIdx.x;
-  if (n >= N) return;
-  const int e = blockIdx.y;
-  const __attribute__((address_space(1))) double* y = (const __attribute__((address_space(1))) double*)Y;
-  double s = 0.0;
-  if (e < K) {
-    const int k = e;
-    for (int t = P; t < T; ++t) s += y[(size_t)t * N + n] * sX[t * K + k];
-    YX[(size_t)k * N + n] = s;
-  } else if (e < K + P * K) {
-    const int i = e - K, p = i / K, k = i % K;
-    for (int t = P; t < T; ++t)
-      s += y[(size_t)t * N + n] * sX[(t - 1 - p) * K + k] + y[(size_t)(t - 1 - p) * N + n] * sX[t * K + k];
-    Bt[(size_t)i * N + n] = s;
-  } else if (e < K + P * K + P * K * P) {
-    const int i = e - K - P * K, p = i / (K * P), k = (i / P) % K, q = i % P;
-    for (int t = P; t < T; ++t) s += y[(size_t)(t - 1 - p) * N + n] * sX[(t - 1 - q) * K + k];
-    Dt[(size_t)i * N + n] = s;
-  } else if (e == K + P * K + P * K * P) {
-    for (int t = P; t < T; ++t) s += y[(size_t)t * N + n] * y[(size_t)t * N + n];
-    YY[n] = s;
-  } else if (e < K + P * K + P * K * P + 1 + P) {
-    const int p = e - (K + P * K + P * K * P + 1);
-    for (int t = P; t < T; ++t) s += y[(size_t)(t - 1 - p) * N + n] * y[(size_t)t * N + n];
-    dY[(size_t)p * N + n] = s;
+constexpr int PMAX = 4;   // largest AR order
+
+// One wavefront per global tensor entry, the scans dealt to the lanes.  A
+// thread per entry walked T dependent loads in turn (85 us at K = 15, T = 200;
+// 8 us with the wavefront).
+__global__ __launch_bounds__(DT) void k_data_globals(int T, int K, int Ks, int P, const double* __restrict__ X,
+                                                     double* __restrict__ G) {
+  const int e = (blockIdx.x * DT + threadIdx.x) / 64, lane = threadIdx.x % 64;
+  const int nXX = K * K, nR = K * K * P, nS = P * K * K * P;
+  if (e >= nXX + nR + nS) return;
+  int k, l, a = 0, b = 0;   // sum over scans of X[t - a][k] X[t - b][l]
+  if (e < nXX) {
+    k = e / K;
+    l = e % K;
+  } else if (e < nXX + nR) {
+    const int i = e - nXX;
+    k = i / (K * P);
+    l = (i / P) % K;
+    b = 1 + i % P;
   } else {
-    const int i = e - (K + P * K + P * K * P + 1 + P), p = i / P, q = i % P;
-    for (int t = P; t < T; ++t) s += y[(size_t)(t - 1 - p) * N + n] * y[(size_t)(t - 1 - q) * N + n];
-    dd[(size_t)i * N + n] = s;
+    const int i = e - nXX - nR;
+    a = 1 + i / (K * K * P);
+    k = (i / (K * P)) % K;
+    l = (i / P) % K;
+    b = 1 + i % P;
   }
+  double s = 0.0;
+  for (int t = P + lane; t < T; t += 64) s += X[(t - a) * Ks + k] * X[(t - b) * Ks + l];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  if (lane == 0) G[e] = s;
+}
+
+// Per voxel, the sums C(a, b)[k] = sum_{t=P}^{T-1} y[t - a] X[t - b][k], a, b = 0..P,
+// that YX = C(0, 0), Bt = C(0, p + 1) + C(p + 1, 0) and Dt = C(p + 1, q + 1)
+// are made of, and the products of y with itself (YY, dY, dd).
+//
+// With j = t - b, C(a, b) runs over j = P - b .. T - 1 - b of y[j - d] X[j][k],
+// d = a - b: the scans j = P .. T - 1 - P belong to every pair of a lag d, so
+// 2P + 1 running sums serve all (P + 1)^2 pairs and the at most P scans at
+// either end are added per pair.  A lane holds one voxel, a window of 2P + 1
+// values of y in a ring of registers (loaded once per scan, coalesced) and the
+// sums of KC regressors; the design's rows (padded to whole chunks) are
+// wave-uniform: one 32-byte scalar load per scan.
+// Bound: the FP64 multiply-adds, (2P + 1) K T per voxel (about 30 us at
+// N = 52,740, K = 15, T = 200, P = 3), and the scalar loads of the design in
+// front of them.  120 us there; a workgroup per output entry, which read Y
+// once per entry (208 passes), took 2,427 us.
+// blockIdx.y = regressor chunk; the last one forms YY, dY and dd.
+constexpr int TENSOR_KC = 4;
+constexpr int TENSOR_WG = 64;
+
+template <int P>
+__device__ __forceinline__ void tensor_cross(int T, int K, int Ks, int N, int n, int k0, const double* __restrict__ X,
+                                             const double* __restrict__ Y, double* __restrict__ YX,
+                                             double* __restrict__ Bt, double* __restrict__ Dt) {
+  constexpr int W = 2 * P + 1, KC = TENSOR_KC;
+  const double* y = Y + n;
+  double acc[W][KC];   // acc[d + P][c] = sum_j y[j - d] X[j][k0 + c]
+#pragma unroll
+  for (int d = 0; d < W; ++d)
+#pragma unroll
+    for (int c = 0; c < KC; ++c) acc[d][c] = 0.0;
+  const int jend = T - 1 - P;
+  if (jend >= P) {
+    // y[m] of the window sits in ring[m % W]
+    double ring[W], nxt[W];
+#pragma unroll
+    for (int m = 0; m < 2 * P; ++m) ring[m] = y[(size_t)m * N];
+#pragma unroll
+    for (int i = 0; i < W; ++i) nxt[i] = y[(size_t)min(2 * P + i, T - 1) * N];
+    // scan j + i of a block: y[j + i + P] enters the ring
+    auto scan = [&](int j, int i, double yn) {
+      ring[(2 * P + i) % W] = yn;
+      const double* xr = X + (size_t)(j + i) * Ks + k0;
+      double x[KC];
+#pragma unroll
+      for (int c = 0; c < KC; ++c) x[c] = xr[c];
+#pragma unroll
+      for (int d = -P; d <= P; ++d) {
+        const double yv = ring[(P + i - d + W) % W];
+#pragma unroll
+        for (int c = 0; c < KC; ++c) acc[d + P][c] += yv * x[c];
+      }
+    };
+    int j = P;
+#pragma unroll 1
+    for (; j + W - 1 <= jend; j += W) {
+      double cur[W];
+#pragma unroll
+      for (int i = 0; i < W; ++i) cur[i] = nxt[i];
+      // the next W scans are loaded while these are used
+#pragma unroll
+      for (int i = 0; i < W; ++i) nxt[i] = y[(size_t)min(j + W + P + i, T - 1) * N];
+#pragma unroll
+      for (int i = 0; i < W; ++i) scan(j, i, cur[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < W - 1; ++i)
+      if (j + i <= jend) scan(j, i, nxt[i]);
+  }
+  // the scans at the ends: y[0 .. 2P) and y[T - 2P .. T), where they exist
+  constexpr int P2 = P > 0 ? 2 * P : 1, P1 = P > 0 ? P : 1;
+  double yl[P2], yh[P2], xl[P1][KC], xh[P1][KC];
+#pragma unroll
+  for (int m = 0; m < 2 * P; ++m) {
+    yl[m] = y[(size_t)min(m, T - 1) * N];
+    yh[m] = y[(size_t)max(T - 1 - m, 0) * N];
+  }
+#pragma unroll
+  for (int i = 0; i < P; ++i)
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      xl[i][c] = X[(size_t)min(i, T - 1) * Ks + k0 + c];
+      xh[i][c] = X[(size_t)max(T - 1 - i, 0) * Ks + k0 + c];
+    }
+  auto sum = [&](auto A, auto B, int c) {
+    constexpr int a = decltype(A)::v, b = decltype(B)::v;
+    double s = acc[a - b + P][c];
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      if (i >= P - b && i <= T - 1 - b) s += yl[i + b - a >= 0 ? i + b - a : 0] * xl[i][c];
+      if (i >= b && T - 1 - i >= P) s += yh[i - b + a >= 0 ? i - b + a : 0] * xh[i][c];
+    }
+    return s;
+  };
+#pragma unroll
+  for (int c = 0; c < KC; ++c) {
+    const int k = k0 + c;
+    if (k >= K) break;
+    YX[(size_t)k * N + n] = sum(Lag<0>{}, Lag<0>{}, c);
+    for_lags<P>([&](auto Pp) {
+      constexpr int p = decltype(Pp)::v;
+      Bt[((size_t)p * K + k) * N + n] = sum(Lag<0>{}, Lag<p + 1>{}, c) + sum(Lag<p + 1>{}, Lag<0>{}, c);
+      for_lags<P>([&](auto Q) {
+        constexpr int q = decltype(Q)::v;
+        Dt[(((size_t)p * K + k) * P + q) * N + n] = sum(Lag<p + 1>{}, Lag<q + 1>{}, c);
+      });
+    });
+  }
+}
+
+template <int P>
+__device__ __forceinline__ void tensor_auto(int T, int N, int n, const double* __restrict__ Y, double* __restrict__ YY,
+                                            double* __restrict__ dY, double* __restrict__ dd) {
+  constexpr int W = P + 1;
+  const double* y = Y + n;
+  double acc[W][W], ring[W];   // acc[a][b], a <= b: sum_t y[t - a] y[t - b]
+#pragma unroll
+  for (int a = 0; a < W; ++a)
+#pragma unroll
+    for (int b = 0; b < W; ++b) acc[a][b] = 0.0;
+#pragma unroll
+  for (int m = 0; m < P; ++m) ring[m] = y[(size_t)m * N];
+  for (int t = P; t < T; t += W) {
+    double cur[W];
+#pragma unroll
+    for (int i = 0; i < W; ++i) cur[i] = y[(size_t)min(t + i, T - 1) * N];
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      if (t + i >= T) break;
+      ring[(P + i) % W] = cur[i];
+#pragma unroll
+      for (int a = 0; a < W; ++a)
+#pragma unroll
+        for (int b = a; b < W; ++b) acc[a][b] += ring[(P + i - a + W) % W] * ring[(P + i - b + W) % W];
+    }
+  }
+  YY[n] = acc[0][0];
+#pragma unroll
+  for (int p = 0; p < P; ++p) dY[(size_t)p * N + n] = acc[0][p + 1];
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+#pragma unroll
+    for (int q = 0; q < P; ++q) dd[((size_t)p * P + q) * N + n] = acc[(p < q ? p : q) + 1][(p < q ? q : p) + 1];
+}
+
+template <int P>
+__global__ __launch_bounds__(TENSOR_WG) void k_data_tensors(int T, int K, int Ks, int N, const double* __restrict__ X,
+                                                            const double* __restrict__ Y, double* __restrict__ YX,
+                                                            double* __restrict__ Bt, double* __restrict__ Dt,
+                                                            double* __restrict__ YY, double* __restrict__ dY,
+                                                            double* __restrict__ dd) {
+  const int n = blockIdx.x * TENSOR_WG + threadIdx.x;
+  if (n >= N) return;
+  const int k0 = blockIdx.y * TENSOR_KC;
+  if (k0 < K)
+    tensor_cross<P>(T, K, Ks, N, n, k0, X, Y, YX, Bt, Dt);
+  else
+    tensor_auto<P>(T, N, n, Y, YY, dY, dd);
 }
 
 // One thread per (voxel, row k): row k of B_n and entry k of b_n.  The draws
@@ -98,8 +237,6 @@ __global__ __launch_bounds__(DT) void k_data_tensors(int T, int K, int P, int N,
 // m2 = mean_j a a' (both brackets are linear in them):
 //   B_kl = lambda (XX_kl - sum_p (R_klp + R_lkp) m1_p + sum_pq S_pklq m2_pq)
 //   b_k  = lambda (YX_k - sum_p Bt_pk m1_p + sum_pq Dt_pkq m2_pq).
-constexpr int PMAX = 4;   // largest AR order
-
 __global__ __launch_bounds__(DT) void k_data_assemble(int K, int P, int N, int Ns, const double* __restrict__ G,
                                                       const double* __restrict__ YX, const double* __restrict__ Bt,
                                                       const double* __restrict__ Dt,
@@ -332,14 +469,21 @@ __global__ __launch_bounds__(64) void k_quadform_final(int nrk, int ntiles, cons
 
 }  // namespace
 
+int data_design_stride(int K) { return (K + TENSOR_KC - 1) / TENSOR_KC * TENSOR_KC; }
+
 hipError_t launch_data_tensors(hipStream_t s, int T, int K, int P, int N, const double* X, const double* Y,
                                double* G, double* YX, double* Bt, double* Dt, double* YY, double* dY, double* dd) {
-  const int nG = K * K + K * K * P + P * K * K * P;
-  GP_LAUNCH(k_data_globals, dim3((nG + DT - 1) / DT), dim3(DT), 0, s, T, K, P, X, G);
+  const int nG = K * K + K * K * P + P * K * K * P, Ks = data_design_stride(K);
+  GP_LAUNCH(k_data_globals, dim3((nG + DT / 64 - 1) / (DT / 64)), dim3(DT), 0, s, T, K, Ks, P, X, G);
   if (hipError_t e = hipGetLastError()) return e;
-  const int entries = K + P * K + P * K * P + 1 + P + P * P;
-  GP_LAUNCH(k_data_tensors, dim3((N + DT - 1) / DT, entries), dim3(DT), (size_t)T * K * sizeof(double), s,
-                     T, K, P, N, X, Y, YX, Bt, Dt, YY, dY, dd);
+  const dim3 g((N + TENSOR_WG - 1) / TENSOR_WG, (K + TENSOR_KC - 1) / TENSOR_KC + 1), b(TENSOR_WG);
+  switch (P) {
+#define X_P(PP) \
+  case PP: GP_LAUNCH(k_data_tensors<PP>, g, b, 0, s, T, K, Ks, N, X, Y, YX, Bt, Dt, YY, dY, dd); break;
+    X_P(0) X_P(1) X_P(2) X_P(3) X_P(4)
+#undef X_P
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

@@ -54,6 +54,8 @@ hipError_t launch_finalize(hipStream_t s, int kind, const Prob* probs, int nprob
 int finalize_rhs_per_block();
 
 // k_data.hip: time-summed AR(P) data tensors and the data term assembled from them
+// X: [T][data_design_stride(K)], the columns past K zero
+int data_design_stride(int K);
 hipError_t launch_data_tensors(hipStream_t s, int T, int K, int P, int N, const double* X, const double* Y,
                                double* G, double* YX, double* Bt, double* Dt, double* YY, double* dY, double* dd);
 hipError_t launch_data_rss(hipStream_t s, int K, int P, int N, int Ns, const double* G, const double* YX,

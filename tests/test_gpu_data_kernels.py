@@ -1,0 +1,89 @@
+"""GPU parity of the data-term kernels at the edges of their tilings, against
+the explicit whitening of every scan (Appendix A.2) in NumPy: few scans (the
+lag windows of the two ends overlap), voxel counts around a wavefront, every
+AR order, K on both sides of the regressor chunk."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    return torch
+
+
+@pytest.fixture(scope="module")
+def g(built_library, torch_cuda):
+    from paper_1606_00980_amd import gmrf
+    return gmrf
+
+
+@pytest.fixture(scope="module")
+def ctx(g, torch_cuda):
+    h = g.gp_ctx_create(0, torch_cuda.cuda.current_stream().cuda_stream, 0)
+    yield h
+    torch_cuda.cuda.synchronize()
+    g.gp_ctx_destroy(h)
+
+
+def dev(torch, a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float64)).cuda()
+
+
+def whitened(Z, A, P):
+    """Z[t] - sum_p A[p] Z[t - 1 - p] over the scans t = P .. T - 1 (Z: (T, ...), A: (P, N))."""
+    out = Z[P:].copy()
+    for p in range(P):
+        out -= A[p] * Z[P - 1 - p:Z.shape[0] - 1 - p]
+    return out
+
+
+def problem(nx, K, T, P, Ns, seed):
+    r = np.random.default_rng(seed)
+    X = r.standard_normal((T, K))
+    Y = r.standard_normal((T, nx))
+    A = r.uniform(-0.4, 0.4, (Ns, P, nx))
+    lam = r.uniform(0.5, 2.0, nx)
+    return X, Y, A, lam
+
+
+CASES = [(P, T, nx, K) for P in range(5) for T, nx, K in
+         ((P + 1, 1, 1), (P + 2, 63, 2), (2 * P + 1, 64, 3), (2 * P + 2, 65, 5), (3 * P + 3, 130, 4), (41, 257, 9))]
+
+
+@pytest.mark.parametrize("P,T,nx,K", CASES)
+def test_tensors_at_the_edges(g, ctx, torch_cuda, P, T, nx, K):
+    """b_w and, where they are positive definite, the blocks from the tensors."""
+    X, Y, A, lam = problem(nx, K, T, P, 1, 100 * P + T + nx)
+    op = g.gp_op_create(ctx, np.ones((1, 1, nx), dtype=np.uint8), 4, K)
+    g.gp_op_set_alpha(op, np.zeros(K))
+    d = g.gp_data_create(op, T, P, X, dev(torch_cuda, Y))
+    bw = torch_cuda.zeros((K, nx), dtype=torch_cuda.float64, device="cuda")
+    # per voxel whitened design and data
+    Xw = whitened(np.repeat(X[:, :, None], nx, 2), A[0][:, None, :] if P else A[0], P)   # (T-P, K, N)
+    Yw = whitened(Y, A[0], P)
+    ref = lam * np.einsum("tkn,tn->kn", Xw, Yw)
+    B = lam[:, None, None] * np.einsum("tkn,tln->nkl", Xw, Xw)
+    spd = np.linalg.eigvalsh(B).min() > 1e-3
+    scale = lam * np.einsum("tkn,tn->kn", np.abs(Xw), np.abs(Yw)) + 1.0
+    try:
+        g.gp_data_assemble(d, dev(torch_cuda, lam), 1, dev(torch_cuda, A) if P else None, bw)
+        done = True
+    except g.GmrfError as e:
+        assert e.status == g.GP_ERR_NOT_SPD and not spd
+        done = False
+    # sums of at most 41 scans of order-one terms, expanded over (P + 1)^2 lag pairs
+    assert (np.abs(bw.cpu().numpy() - ref) / scale).max() < 1e-12
+    if done:
+        x = np.random.default_rng(1).standard_normal((1, K, nx))
+        y = torch_cuda.empty((1, K, nx), dtype=torch_cuda.float64, device="cuda")
+        g.gp_apply(op, 1, dev(torch_cuda, x), y)
+        want = np.einsum("nkl,ln->kn", B, x[0])
+        assert np.abs(y.cpu().numpy()[0] - want).max() < 1e-12 * max(1.0, np.abs(B).max() * K * 10)
+    g.gp_data_destroy(d)
+    g.gp_op_destroy(op)
