@@ -173,7 +173,11 @@ int         gp_version(void);
  * the library may allocate at `hbm_budget` (0 = no cap).                    */
 int gp_ctx_create(int device, void* hip_stream, size_t hbm_budget, gp_ctx** out);
 int gp_ctx_set_stream(gp_ctx* ctx, void* hip_stream);
-/* bytes currently allocated by the library for this context (host out)     */
+/* bytes currently allocated by the library for this context (host out).
+ * Device blocks given back (a destroyed dataset, temporary buffers) are kept
+ * for later allocations of the same size, at most 16 blocks and 1 GiB per
+ * context and inside its budget; they are not counted here and go back to the
+ * device when another allocation needs the room and with the context.       */
 int gp_ctx_memory(const gp_ctx* ctx, size_t* used, size_t* budget);
 int gp_ctx_destroy(gp_ctx* ctx);
 /* gp_ctx_profile: enable (1) or disable (0) per-launch event timing on this

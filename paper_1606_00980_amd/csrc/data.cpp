@@ -100,6 +100,7 @@ int gp_data_create(gp_op* op, int T, int P, const double* X_host, const double* 
     e = launch_data_tensors(c->stream, T, K, P, N, d->X, Y, d->G, d->YX, d->Bt, d->Dt, d->YY, d->dY, d->dd);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) {
+    (void)hipStreamSynchronize(c->stream);
     release(d);
     return fail(GP_ERR_DEVICE, std::string("data tensors: ") + hipGetErrorString(e));
   }
@@ -168,7 +169,8 @@ int gp_alpha_posterior(gp_op* op, int R, const double* W, double q1, double q2, 
   hipError_t e = launch_quadform(c->stream, op_dev(op), R, W, buf, buf + (size_t)nrk * nt);
   if (e == hipSuccess)
     e = hipMemcpyAsync(qf.data(), buf + (size_t)nrk * nt, nrk * sizeof(double), hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  const hipError_t ew = hipStreamSynchronize(c->stream);
+  if (e == hipSuccess) e = ew;
   dev_free(c, buf, bytes);
   if (e != hipSuccess) return fail(GP_ERR_DEVICE, std::string("quadratic forms: ") + hipGetErrorString(e));
   const double shape = 0.5 * op->N + q2;
@@ -329,6 +331,7 @@ int gp_gibbs_step(gp_data* d, const double* A, const double* z1, const double* z
   }
   {
     BusyGuard guard(c);
+    if (st != GP_OK) (void)hipStreamSynchronize(c->stream);
     dev_free(c, buf, bytes);
   }
   return st;

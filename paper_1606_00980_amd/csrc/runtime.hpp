@@ -7,6 +7,7 @@
 #include <atomic>
 #include <functional>
 #include <map>
+#include <mutex>
 #include <string>
 #include <utility>
 #include <vector>
@@ -42,6 +43,11 @@ struct gp_ctx {
   hipStream_t stream = nullptr;
   size_t budget = 0, used = 0;
   std::atomic<int> busy{0};
+  // device blocks given back and kept for the next allocation of the same
+  // size, oldest first (see dev_alloc); kept_mu also guards `used`
+  std::mutex kept_mu;
+  std::vector<std::pair<void*, size_t>> kept;
+  size_t kept_bytes = 0;
   // solver workspace arena (grown on demand, reused across calls)
   void* ws = nullptr;
   size_t ws_cap = 0;
@@ -219,6 +225,8 @@ void prof_add(gp_ctx* c, int kind, double units, double bytes);
 int set_device(gp_ctx* c);
 int dev_alloc(gp_ctx* c, size_t bytes, void** p);
 void dev_free(gp_ctx* c, void* p, size_t bytes);
+// gives the kept device blocks back to the device
+void release_kept(gp_ctx* c);
 OpDev op_dev(const gp_op* op);
 int build_precond(gp_op* op, int pc);
 // Grow the context's solver workspace to at least `bytes`.

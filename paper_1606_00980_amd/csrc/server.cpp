@@ -208,6 +208,7 @@ char* arena_take(gp_server* s, size_t n) {
     char* m = nullptr;
     if (hipMalloc((void**)&m, want) != hipSuccess) {
       (void)hipGetLastError();
+      release_kept(s->ctx);
       want = n;
       if (hipMalloc((void**)&m, want) != hipSuccess) {
         (void)hipGetLastError();

@@ -1,0 +1,55 @@
+"""Device blocks that a context keeps for reuse: inside the budget, not
+counted as used, and never in the way of an allocation that fits."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def g(built_library):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1606_00980_amd import gmrf
+    return gmrf
+
+
+@pytest.mark.parametrize("slack", [0, 1 << 20])
+def test_datasets_come_and_go_within_the_budget(g, slack):
+    """Datasets of changing shapes in a context whose budget holds one of them at a time."""
+    import torch
+    nx, K, T = 5000, 4, 40
+    r = np.random.default_rng(3)
+    mask = np.ones((1, 1, nx), dtype=np.uint8)
+    Y = torch.from_numpy(r.standard_normal((T, nx))).cuda()
+    lam = torch.ones(nx, dtype=torch.float64, device="cuda")
+    bw = torch.empty((K, nx), dtype=torch.float64, device="cuda")
+    X = r.standard_normal((T, K))
+    stream = torch.cuda.current_stream().cuda_stream
+    free = g.gp_ctx_create(0, stream, 0)   # what the largest dataset takes
+    op = g.gp_op_create(free, mask, 4, K)
+    base = g.gp_ctx_memory(free)[0]
+    d = g.gp_data_create(op, T, 4, X, Y)
+    most = g.gp_ctx_memory(free)[0]
+    g.gp_data_destroy(d)
+    assert g.gp_ctx_memory(free)[0] == base
+    g.gp_op_destroy(op)
+    assert g.gp_ctx_memory(free)[0] == 0
+    g.gp_ctx_destroy(free)
+    ctx = g.gp_ctx_create(0, stream, most + slack)
+    op = g.gp_op_create(ctx, mask, 4, K)
+    A = torch.zeros((1, 4, nx), dtype=torch.float64, device="cuda")
+    first = None
+    for P in (4, 1, 4, 0, 3, 4, 4):
+        d = g.gp_data_create(op, T, P, X, Y)
+        assert g.gp_ctx_memory(ctx)[0] <= most + slack
+        g.gp_data_assemble(d, lam, 1, A if P else None, bw)
+        g.gp_data_destroy(d)
+        assert g.gp_ctx_memory(ctx)[0] == base
+        if P == 4:   # the same bits from a new and a reused block
+            first = bw.clone() if first is None else first
+            assert torch.equal(bw, first)
+    g.gp_op_destroy(op)
+    assert g.gp_ctx_memory(ctx)[0] == 0
+    g.gp_ctx_destroy(ctx)
