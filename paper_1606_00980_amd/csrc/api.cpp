@@ -1172,6 +1172,10 @@ int install_blocks(gp_op* op, const double* B, int64_t* bad_voxel) {
     const double K = op->K, NB = K * (K + 1) / 2;
     prof_add(c, GP_KERNEL_PACK, op->N, (double)op->N * (K * K * 8 + NB * 20));
   }
+  return finish_blocks(op, bad_voxel);
+}
+
+int finish_blocks(gp_op* op, int64_t* bad_voxel) {
   int bad = INT_MAX;
   if (int st = read_bad(op, &bad)) return st;
   op->pc_built = -1;

@@ -20,16 +20,15 @@ struct gp_data {
   gp_op* op = nullptr;
   int T = 0, P = 0, K = 0, N = 0;
   double* X = nullptr;    // T x data_design_stride(K)
-  double* G = nullptr;    // [X'X | R | S]
+  double* G = nullptr;    // [X'X | R | S], coefficient table
   double* YX = nullptr;   // [K][N]
   double* Bt = nullptr;   // [P][K][N]
   double* Dt = nullptr;   // [P][K][P][N]
-  double* Bw = nullptr;   // [N][K][K] assembled blocks, before packing
   double* YY = nullptr;   // [N]
   double* dY = nullptr;   // [P][N]
   double* dd = nullptr;   // [P][P][N]
   double* Ja = nullptr;   // [N][P][P] assembled AR-coefficient blocks (allocated on first use)
-  size_t nX = 0, nG = 0, nYX = 0, nBt = 0, nDt = 0, nBw = 0, nYY = 0, ndY = 0, ndd = 0, nJa = 0;
+  size_t nX = 0, nG = 0, nYX = 0, nBt = 0, nDt = 0, nYY = 0, ndY = 0, ndd = 0, nJa = 0;
 };
 
 namespace {
@@ -41,7 +40,6 @@ void release(gp_data* d) {
   dev_free(c, d->YX, d->nYX * sizeof(double));
   dev_free(c, d->Bt, d->nBt * sizeof(double));
   dev_free(c, d->Dt, d->nDt * sizeof(double));
-  dev_free(c, d->Bw, d->nBw * sizeof(double));
   dev_free(c, d->YY, d->nYY * sizeof(double));
   dev_free(c, d->dY, d->ndY * sizeof(double));
   dev_free(c, d->dd, d->ndd * sizeof(double));
@@ -73,11 +71,10 @@ int gp_data_create(gp_op* op, int T, int P, const double* X_host, const double* 
   d->N = N;
   const int Ks = data_design_stride(K);
   d->nX = (size_t)T * Ks;
-  d->nG = (size_t)K * K + (size_t)K * K * P + (size_t)P * K * K * P;
+  d->nG = data_globals_size(K, P);
   d->nYX = (size_t)K * N;
   d->nBt = std::max<size_t>(1, (size_t)P * K * N);
   d->nDt = std::max<size_t>(1, (size_t)P * K * P * N);
-  d->nBw = (size_t)N * K * K;
   d->nYY = (size_t)N;
   d->ndY = std::max<size_t>(1, (size_t)P * N);
   d->ndd = std::max<size_t>(1, (size_t)P * P * N);
@@ -86,7 +83,6 @@ int gp_data_create(gp_op* op, int T, int P, const double* X_host, const double* 
       (st = dev_alloc(c, d->nYX * sizeof(double), (void**)&d->YX)) ||
       (st = dev_alloc(c, d->nBt * sizeof(double), (void**)&d->Bt)) ||
       (st = dev_alloc(c, d->nDt * sizeof(double), (void**)&d->Dt)) ||
-      (st = dev_alloc(c, d->nBw * sizeof(double), (void**)&d->Bw)) ||
       (st = dev_alloc(c, d->nYY * sizeof(double), (void**)&d->YY)) ||
       (st = dev_alloc(c, d->ndY * sizeof(double), (void**)&d->dY)) ||
       (st = dev_alloc(c, d->ndd * sizeof(double), (void**)&d->dd))) {
@@ -119,14 +115,16 @@ int gp_data_assemble(gp_data* d, const double* lambda, int Ns, const double* A, 
   if (!guard.ok) return fail(GP_ERR_BUSY, "context busy");
   if (int st = set_device(c)) return st;
   const int K = d->K, P = d->P, N = d->N;
+  if (int st = reset_bad(op)) return st;
   PROFILED(c, GP_KERNEL_DATA,
-           launch_data_assemble(c->stream, K, P, N, Ns, d->G, d->YX, d->Bt, d->Dt, lambda, A, d->Bw, bw));
+           launch_data_assemble(c->stream, K, P, N, Ns, d->G, d->YX, d->Bt, d->Dt, lambda, A, op->B64, op->B32,
+                                op->L64, op->d_bad, bw));
   {
-    // tensors and draws read, blocks (both triangles) and b_w written
-    const double per = (double)K + P * K + (double)P * K * P + 1 + (double)Ns * P + (double)K * K + (bw ? K : 0);
-    prof_add(c, GP_KERNEL_DATA, N, (double)N * per * 8.0);
+    // tensors (for b_w) and draws read, packed blocks (FP64, FP32), factors and b_w written
+    const double per = (bw ? (double)K + P * K + (double)P * K * P + K : 0.0) + 1 + (double)Ns * P;
+    prof_add(c, GP_KERNEL_DATA, N, (double)N * (per * 8.0 + K * (K + 1) / 2 * 20.0));
   }
-  return install_blocks(op, d->Bw, bad_voxel);
+  return finish_blocks(op, bad_voxel);
 }
 
 int gp_data_lambda(gp_data* d, int Ns, const double* W, const double* A, double u1, double u2, double* rss,

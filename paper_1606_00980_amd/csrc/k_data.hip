@@ -23,6 +23,7 @@
 
 #include "common.hpp"
 #include "launch.hpp"
+#include "spd.hpp"
 
 namespace gp {
 
@@ -71,6 +72,41 @@ __global__ __launch_bounds__(DT) void k_data_globals(int T, int K, int Ks, int P
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
   if (lane == 0) G[e] = s;
+}
+
+// Coefficient table of the voxel blocks, [K(K+1)/2][TAB]: packed entry (k, l) of
+// XX - [R a + (R a)'] + a'S a as a polynomial in a: the constant, the
+// coefficients of a_p (PMAX slots), then those of a_p a_q, p <= q (packed by
+// tab_pair(p, q, PMAX)); slots past P are zero.
+constexpr int TAB = 16;
+
+__host__ __device__ constexpr int tab_pair(int p, int q, int P) { return p * P - p * (p - 1) / 2 + q - p; }   // p <= q < P
+
+__global__ __launch_bounds__(DT) void k_data_table(int K, int P, const double* __restrict__ G,
+                                                   double* __restrict__ Tab) {
+  const int i = blockIdx.x * DT + threadIdx.x;
+  const int e = i / TAB, c = i % TAB;
+  if (e >= K * (K + 1) / 2) return;
+  int k = 0;
+  while ((k + 1) * (k + 2) / 2 <= e) ++k;
+  const int l = e - k * (k + 1) / 2;
+  const double* R = G + K * K;
+  const double* S = R + K * K * P;
+  double v = 0.0;
+  if (c == 0) {
+    v = G[k * K + l];
+  } else if (c <= PMAX) {
+    const int p = c - 1;
+    if (p < P) v = -(R[(k * K + l) * P + p] + R[(l * K + k) * P + p]);
+  } else {
+    for (int p = 0; p < P; ++p)
+      for (int q = p; q < P; ++q)
+        if (1 + PMAX + tab_pair(p, q, PMAX) == c) {
+          v = S[((p * K + k) * K + l) * P + q];
+          if (q != p) v += S[((q * K + k) * K + l) * P + p];
+        }
+  }
+  Tab[i] = v;
 }
 
 // Per voxel, the sums C(a, b)[k] = sum_{t=P}^{T-1} y[t - a] X[t - b][k], a, b = 0..P,
@@ -232,29 +268,34 @@ __global__ __launch_bounds__(TENSOR_WG) void k_data_tensors(int T, int K, int Ks
     tensor_auto<P>(T, N, n, Y, YY, dY, dd);
 }
 
-// One thread per (voxel, row k): row k of B_n and entry k of b_n.  The draws
-// enter through their first two moments at the voxel, m1 = mean_j a and
-// m2 = mean_j a a' (both brackets are linear in them):
+// One lane per voxel: the packed block B_n, stored as the operator holds it and
+// factored in place (B_n = L_n L_n'), and b_n.  The draws enter through
+// their first two moments at the voxel, m1 = mean_j a and m2 = mean_j a a'
+// (both brackets are linear in them):
 //   B_kl = lambda (XX_kl - sum_p (R_klp + R_lkp) m1_p + sum_pq S_pklq m2_pq)
 //   b_k  = lambda (YX_k - sum_p Bt_pk m1_p + sum_pq Dt_pkq m2_pq).
-__global__ __launch_bounds__(DT) void k_data_assemble(int K, int P, int N, int Ns, const double* __restrict__ G,
-                                                      const double* __restrict__ YX, const double* __restrict__ Bt,
-                                                      const double* __restrict__ Dt,
-                                                      const double* __restrict__ lambda,
-                                                      const double* __restrict__ A, double* __restrict__ Bout,
-                                                      double* __restrict__ bw) {
-  extern __shared__ double sG[];
-  const int nG = K * K + K * K * P + P * K * K * P;
-  for (int i = threadIdx.x; i < nG; i += DT) sG[i] = G[i];
-  __syncthreads();
-  const int n = blockIdx.x * DT + threadIdx.x;
-  if (n >= N) return;
-  const double* XX = sG;
-  const double* R = sG + K * K;
-  const double* S = R + K * K * P;
-  const int k = blockIdx.y;
-  const double lam = lambda[n];
-  double m1[PMAX] = {0.0, 0.0, 0.0, 0.0}, m2[PMAX][PMAX] = {};
+// blockIdx.y = 0: the block; with ASM_FUSED the others b_n, ASM_KC regressors
+// each.  From K = 11 on the block's registers leave one or two wavefronts a
+// SIMD, which b_n's loads then wait in: there it has a kernel of its own
+// (K = 15: 60 + 21 against 104 us fused; K = 6: 14 us fused against 13 + 12).
+// Bound: the tensors read for b_n and the three packed arrays written, all
+// coalesced (at K = 15, P = 3, N = 52,740: 225 MB, 45 us at 5 TB/s).
+// Measured there 81 us; the rows of [N][K][K] blocks written by one kernel
+// and gathered again by the packing kernel, a lane's rows K*K*8 bytes apart,
+// took 112 + 57 us (K = 6: 29 + 9 to 14 us).
+constexpr int ASM_WG = 64;
+constexpr int ASM_KC = 3;   // regressors of b_w per lane
+template <int K> constexpr bool ASM_FUSED = K <= 10;
+
+constexpr int ASM_NQ = PMAX * (PMAX + 1) / 2;
+
+// m1 = mean_j a and m2 = mean_j a a' (packed by tab_pair) at voxel n
+__device__ __forceinline__ void draw_moments(int P, int N, int n, int Ns, const double* __restrict__ A,
+                                             double (&m1)[PMAX], double (&m2)[ASM_NQ]) {
+#pragma unroll
+  for (int p = 0; p < PMAX; ++p) m1[p] = 0.0;
+#pragma unroll
+  for (int i = 0; i < ASM_NQ; ++i) m2[i] = 0.0;
   for (int j = 0; j < Ns; ++j) {
     double a[PMAX];
 #pragma unroll
@@ -263,100 +304,213 @@ __global__ __launch_bounds__(DT) void k_data_assemble(int K, int P, int N, int N
     for (int p = 0; p < PMAX; ++p) {
       m1[p] += a[p];
 #pragma unroll
-      for (int q = 0; q < PMAX; ++q) m2[p][q] += a[p] * a[q];
+      for (int q = p; q < PMAX; ++q) m2[tab_pair(p, q, PMAX)] += a[p] * a[q];
     }
   }
-  const double inv = Ns > 0 ? 1.0 / Ns : 0.0;
+  const double inv = 1.0 / Ns;
 #pragma unroll
-  for (int p = 0; p < PMAX; ++p) {
-    m1[p] *= inv;
+  for (int p = 0; p < PMAX; ++p) m1[p] *= inv;
 #pragma unroll
-    for (int q = 0; q < PMAX; ++q) m2[p][q] *= inv;
-  }
-  // b_k first: its loads are independent of each other
-  if (bw) {
-    double bt[PMAX], dt[PMAX][PMAX];
+  for (int i = 0; i < ASM_NQ; ++i) m2[i] *= inv;
+}
+
+// Entries k0 .. k0 + ASM_KC - 1 of b_n at voxel n.
+__device__ __forceinline__ void rhs_entries(int K, int P, int N, int n, int k0, double lam, const double (&m1)[PMAX],
+                                            const double (&m2)[ASM_NQ], const double* __restrict__ YX,
+                                            const double* __restrict__ Bt, const double* __restrict__ Dt,
+                                            double* __restrict__ bw) {
 #pragma unroll
-    for (int p = 0; p < PMAX; ++p) {
-      bt[p] = p < P ? Bt[((size_t)p * K + k) * N + n] : 0.0;
-#pragma unroll
-      for (int q = 0; q < PMAX; ++q) dt[p][q] = p < P && q < P ? Dt[(((size_t)p * K + k) * P + q) * N + n] : 0.0;
-    }
-    double acc = 0.0;
-#pragma unroll
-    for (int p = 0; p < PMAX; ++p) {
-      acc += bt[p] * m1[p];
-#pragma unroll
-      for (int q = 0; q < PMAX; ++q) acc -= dt[p][q] * m2[p][q];
-    }
-    bw[(size_t)k * N + n] = lam * (YX[(size_t)k * N + n] - acc);
-  }
-  double* row = Bout + ((size_t)n * K + k) * K;
-  for (int l = 0; l < K; ++l) {
-    double acc = 0.0;
+  for (int c = 0; c < ASM_KC; ++c) {
+    const int k = k0 + c;
+    if (k >= K) break;
+    double acc = YX[(size_t)k * N + n];
 #pragma unroll
     for (int p = 0; p < PMAX; ++p) {
       if (p < P) {
-        acc += (R[(k * K + l) * P + p] + R[(l * K + k) * P + p]) * m1[p];
+        acc -= Bt[((size_t)p * K + k) * N + n] * m1[p];
 #pragma unroll
-        for (int q = 0; q < PMAX; ++q)
-          if (q < P) acc -= S[((p * K + k) * K + l) * P + q] * m2[p][q];
+        for (int q = p; q < PMAX; ++q) {
+          if (q < P) {
+            double d = Dt[(((size_t)p * K + k) * P + q) * N + n];
+            if (q != p) d += Dt[(((size_t)q * K + k) * P + p) * N + n];
+            acc += d * m2[tab_pair(p, q, PMAX)];
+          }
+        }
       }
     }
-    row[l] = lam * (XX[k * K + l] - acc);
+    bw[(size_t)k * N + n] = lam * acc;
   }
 }
 
-// One thread per voxel: the Monte Carlo mean over the Ns pairs (W^j, A^j) of
-// the residual quadratic form, then the Gamma posterior of lambda_n:
-// 1/u1t = rss/2 + 1/u1, mean = u1t * u2t (u2t = (T-P)/2 + u2).
-__global__ __launch_bounds__(DT) void k_data_rss(int K, int P, int N, int Ns, const double* __restrict__ G,
-                                                 const double* __restrict__ YX, const double* __restrict__ Bt,
-                                                 const double* __restrict__ Dt, const double* __restrict__ YY,
-                                                 const double* __restrict__ dY, const double* __restrict__ dd,
-                                                 const double* __restrict__ Wall, const double* __restrict__ A,
-                                                 double u1, double u2t, double* __restrict__ rss_out,
-                                                 double* __restrict__ scale, double* __restrict__ mean) {
-  extern __shared__ double sG[];
-  const int nG = K * K + K * K * P + P * K * K * P;
-  for (int i = threadIdx.x; i < nG; i += DT) sG[i] = G[i];
+template <int K>
+__global__ __launch_bounds__(ASM_WG) void k_data_assemble(int P, int N, int Ns, const double* __restrict__ Tab,
+                                                          const double* __restrict__ YX,
+                                                          const double* __restrict__ Bt,
+                                                          const double* __restrict__ Dt,
+                                                          const double* __restrict__ lambda,
+                                                          const double* __restrict__ A, double* __restrict__ B64,
+                                                          float* __restrict__ B32, double* __restrict__ L64,
+                                                          int* __restrict__ bad, double* __restrict__ bw) {
+  // the coefficient table in LDS (every lane reads the same entry)
+  constexpr int NB = K * (K + 1) / 2;
+  __shared__ double tab[NB * TAB];
+  const bool rhs = ASM_FUSED<K> && blockIdx.y > 0;
+  if (!rhs)
+    for (int i = threadIdx.x; i < NB * TAB; i += ASM_WG) tab[i] = Tab[i];
   __syncthreads();
-  const int n = blockIdx.x * DT + threadIdx.x;
+  const int n = blockIdx.x * ASM_WG + threadIdx.x;
   if (n >= N) return;
-  const double* XX = sG;
-  const double* R = sG + K * K;
-  const double* S = R + K * K * P;
-  double w[KMAX], a[4];
+  const double lam = lambda[n];
+  double m1[PMAX], m2[ASM_NQ], a[NB];
+  draw_moments(P, N, n, Ns, A, m1, m2);
+  if (rhs) {
+    rhs_entries(K, P, N, n, ((int)blockIdx.y - 1) * ASM_KC, lam, m1, m2, YX, Bt, Dt, bw);
+    return;
+  }
+  auto entry = [&](int e) {
+    const double* t = tab + e * TAB;
+    double g = t[0];
+#pragma unroll
+    for (int p = 0; p < PMAX; ++p) g += t[1 + p] * m1[p];
+#pragma unroll
+    for (int i = 0; i < ASM_NQ; ++i) g += t[1 + PMAX + i] * m2[i];
+    return lam * g;
+  };
+  if constexpr (K <= KREG) {
+#pragma unroll
+    for (int e = 0; e < NB; ++e) a[e] = entry(e);
+  } else {
+#pragma unroll 1
+    for (int e = 0; e < NB; ++e) a[e] = entry(e);
+  }
+  pack_factor<K>(N, n, a, B64, B32, L64, bad);
+}
+
+// b_n alone, ASM_KC regressors per blockIdx.y (K where the assembly leaves it out)
+__global__ __launch_bounds__(ASM_WG) void k_data_rhs(int K, int P, int N, int Ns, const double* __restrict__ YX,
+                                                     const double* __restrict__ Bt, const double* __restrict__ Dt,
+                                                     const double* __restrict__ lambda, const double* __restrict__ A,
+                                                     double* __restrict__ bw) {
+  const int n = blockIdx.x * ASM_WG + threadIdx.x;
+  if (n >= N) return;
+  double m1[PMAX], m2[ASM_NQ];
+  draw_moments(P, N, n, Ns, A, m1, m2);
+  rhs_entries(K, P, N, n, (int)blockIdx.y * ASM_KC, lambda[n], m1, m2, YX, Bt, Dt, bw);
+}
+
+// The Monte Carlo mean over the Ns pairs (W^j, A^j) of the residual quadratic
+// form, then the Gamma posterior of lambda_n: 1/u1t = rss/2 + 1/u1, mean =
+// u1t * u2t (u2t = (T-P)/2 + u2).  A workgroup holds 64 voxels; its four
+// wavefronts take every fourth regressor row k each and are added in order.
+// Per draw, the quadratic part w'(XX - 2 R a + a'S a)w runs over the lower
+// triangle with the wave-uniform coefficient table (scalar loads) and the
+// lane's monomials of a, w in an LDS column of the lane; the parts linear in w
+// come from the draws' sums of w_k {1, a_p, a_p a_q}, so each tensor entry is
+// loaded once for all draws.
+// Bound: FP64 multiply-adds, K(K+1)/2 (P+1)(P+2)/2 per draw and voxel (about
+// 15 us at N = 52,740, K = 15, P = 3, five draws).  Measured there 64 us; one
+// thread per voxel over both triangles and all lag pairs, with w and a in
+// scratch memory (run-time K), took 1,541 us (K = 6, one draw: 68 to 12 us).
+constexpr int RSS_WAVES = 4;
+
+template <int P>
+__global__ __launch_bounds__(64 * RSS_WAVES) void k_data_rss(int K, int N, int Ns, const double* __restrict__ Tab,
+                                                             const double* __restrict__ YX,
+                                                             const double* __restrict__ Bt,
+                                                             const double* __restrict__ Dt,
+                                                             const double* __restrict__ YY,
+                                                             const double* __restrict__ dY,
+                                                             const double* __restrict__ dd,
+                                                             const double* __restrict__ W,
+                                                             const double* __restrict__ A, double u1, double u2t,
+                                                             double* __restrict__ rss_out, double* __restrict__ scale,
+                                                             double* __restrict__ mean) {
+  extern __shared__ double sw[];   // [K][64 * RSS_WAVES]: w of the lane
+  __shared__ double part[RSS_WAVES][64];
+  constexpr int P1 = P > 0 ? P : 1, NQ = P * (P + 1) / 2, Q1 = NQ > 0 ? NQ : 1, LDW = 64 * RSS_WAVES;
+  const int lane = threadIdx.x % 64, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+  const int n = blockIdx.x * 64 + lane;
+  const int nn = n < N ? n : N - 1;   // lanes past the end compute on the last voxel and store nothing
+  double* w = sw + threadIdx.x;
   double tot = 0.0;
   for (int j = 0; j < Ns; ++j) {
-    for (int k = 0; k < K; ++k) w[k] = Wall[((size_t)j * K + k) * N + n];
-    for (int p = 0; p < P; ++p) a[p] = A[((size_t)j * P + p) * N + n];
-    double v = YY[n];
-    for (int k = 0; k < K; ++k) {
-      double xw = 0.0;
-      for (int l = 0; l < K; ++l) xw += XX[k * K + l] * w[l];
-      v += w[k] * xw - 2.0 * YX[(size_t)k * N + n] * w[k];
+    double a[P1], aa[Q1];
+#pragma unroll
+    for (int p = 0; p < P; ++p) a[p] = A[((size_t)j * P + p) * N + nn];
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+      for (int q = p; q < P; ++q) aa[tab_pair(p, q, P)] = a[p] * a[q];
+#pragma unroll 4
+    for (int k = 0; k < K; ++k) w[k * LDW] = W[((size_t)j * K + k) * N + nn];
+    // coefficient of w_k w_l for packed entry e
+    auto coef = [&](int e) {
+      const double* t = Tab + (size_t)e * TAB;
+      double g = t[0];
+#pragma unroll
+      for (int p = 0; p < P; ++p) g += t[1 + p] * a[p];
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int q = p; q < P; ++q) g += t[1 + PMAX + tab_pair(p, q, PMAX)] * aa[tab_pair(p, q, P)];
+      return g;
+    };
+    for (int k = wv; k < K; k += RSS_WAVES) {
+      const double wk = w[k * LDW];
+      const int e0 = k * (k + 1) / 2;
+      double s = 0.0;
+#pragma unroll 4
+      for (int l = 0; l < k; ++l) s += coef(e0 + l) * w[l * LDW];
+      tot += wk * (2.0 * s + coef(e0 + k) * wk);
     }
-    for (int p = 0; p < P; ++p) {
-      v -= 2.0 * dY[(size_t)p * N + n] * a[p];
-      for (int q = 0; q < P; ++q) v += a[p] * dd[((size_t)p * P + q) * N + n] * a[q];
-      for (int k = 0; k < K; ++k) {
-        v += 2.0 * a[p] * Bt[((size_t)p * K + k) * N + n] * w[k];
-        for (int q = 0; q < P; ++q) v -= 2.0 * a[p] * Dt[(((size_t)p * K + k) * P + q) * N + n] * w[k] * a[q];
+    if (wv == 0) {
+      double v = YY[nn];
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        v -= 2.0 * dY[(size_t)p * N + nn] * a[p];
+#pragma unroll
+        for (int q = p; q < P; ++q)
+          v += (p == q ? 1.0 : 2.0) * dd[((size_t)p * P + q) * N + nn] * aa[tab_pair(p, q, P)];
       }
+      tot += v;
     }
-    for (int k = 0; k < K; ++k) {
-      for (int l = 0; l < K; ++l) {
-        double ra = 0.0, asa = 0.0;
-        for (int p = 0; p < P; ++p) {
-          ra += R[(k * K + l) * P + p] * a[p];
-          for (int q = 0; q < P; ++q) asa += a[p] * S[((p * K + k) * K + l) * P + q] * a[q];
-        }
-        v += w[k] * (asa - 2.0 * ra) * w[l];
-      }
-    }
-    tot += v;
   }
+  for (int k = wv; k < K; k += RSS_WAVES) {
+    double m0 = 0.0, m1[P1] = {0.0}, m2[Q1] = {0.0};
+#pragma unroll 2
+    for (int j = 0; j < Ns; ++j) {
+      const double wk = W[((size_t)j * K + k) * N + nn];
+      double a[P1];
+#pragma unroll
+      for (int p = 0; p < P; ++p) a[p] = A[((size_t)j * P + p) * N + nn];
+      m0 += wk;
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        const double wa = wk * a[p];
+        m1[p] += wa;
+#pragma unroll
+        for (int q = p; q < P; ++q) m2[tab_pair(p, q, P)] += wa * a[q];
+      }
+    }
+    double v = -YX[(size_t)k * N + nn] * m0;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      v += Bt[((size_t)p * K + k) * N + nn] * m1[p];
+#pragma unroll
+      for (int q = p; q < P; ++q) {
+        double d = Dt[(((size_t)p * K + k) * P + q) * N + nn];
+        if (q != p) d += Dt[(((size_t)q * K + k) * P + p) * N + nn];
+        v -= d * m2[tab_pair(p, q, P)];
+      }
+    }
+    tot += 2.0 * v;
+  }
+  part[wv][lane] = tot;
+  __syncthreads();
+  if (wv != 0 || n >= N) return;
+  tot = part[0][lane];
+#pragma unroll
+  for (int i = 1; i < RSS_WAVES; ++i) tot += part[i][lane];
   const double rss = tot / Ns;
   const double u1t = 1.0 / (0.5 * rss + 1.0 / u1);
   if (rss_out) rss_out[n] = rss;
@@ -469,12 +623,22 @@ __global__ __launch_bounds__(64) void k_quadform_final(int nrk, int ntiles, cons
 
 }  // namespace
 
+size_t data_table_at(int K, int P) {
+  const size_t n = (size_t)K * K + (size_t)K * K * P + (size_t)P * K * K * P;
+  return (n + TAB - 1) / TAB * TAB;
+}
+
+size_t data_globals_size(int K, int P) { return data_table_at(K, P) + (size_t)(K * (K + 1) / 2) * TAB; }
+
 int data_design_stride(int K) { return (K + TENSOR_KC - 1) / TENSOR_KC * TENSOR_KC; }
 
 hipError_t launch_data_tensors(hipStream_t s, int T, int K, int P, int N, const double* X, const double* Y,
                                double* G, double* YX, double* Bt, double* Dt, double* YY, double* dY, double* dd) {
   const int nG = K * K + K * K * P + P * K * K * P, Ks = data_design_stride(K);
   GP_LAUNCH(k_data_globals, dim3((nG + DT / 64 - 1) / (DT / 64)), dim3(DT), 0, s, T, K, Ks, P, X, G);
+  if (hipError_t e = hipGetLastError()) return e;
+  const int nT = K * (K + 1) / 2 * TAB;
+  GP_LAUNCH(k_data_table, dim3((nT + DT - 1) / DT), dim3(DT), 0, s, K, P, G, G + data_table_at(K, P));
   if (hipError_t e = hipGetLastError()) return e;
   const dim3 g((N + TENSOR_WG - 1) / TENSOR_WG, (K + TENSOR_KC - 1) / TENSOR_KC + 1), b(TENSOR_WG);
   switch (P) {
@@ -491,9 +655,19 @@ hipError_t launch_data_rss(hipStream_t s, int K, int P, int N, int Ns, const dou
                            const double* Bt, const double* Dt, const double* YY, const double* dY, const double* dd,
                            const double* W, const double* A, double u1, double u2t, double* rss, double* scale,
                            double* mean) {
-  const int nG = K * K + K * K * P + P * K * K * P;
-  GP_LAUNCH(k_data_rss, dim3((N + DT - 1) / DT), dim3(DT), (size_t)nG * sizeof(double), s, K, P, N, Ns, G, YX,
-                     Bt, Dt, YY, dY, dd, W, A, u1, u2t, rss, scale, mean);
+  const double* tab = G + data_table_at(K, P);
+  const dim3 g((N + 63) / 64), b(64 * RSS_WAVES);
+  const size_t lds = (size_t)K * 64 * RSS_WAVES * sizeof(double);
+  switch (P) {
+#define X_P(PP)                                                                                                  \
+  case PP:                                                                                                       \
+    GP_LAUNCH(k_data_rss<PP>, g, b, lds, s, K, N, Ns, tab, YX, Bt, Dt, YY, dY, dd, W, A, u1, u2t, rss, scale,    \
+              mean);                                                                                             \
+    break;
+    X_P(0) X_P(1) X_P(2) X_P(3) X_P(4)
+#undef X_P
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
@@ -509,11 +683,24 @@ hipError_t launch_quadform(hipStream_t s, const OpDev& op, int R, const double* 
 
 hipError_t launch_data_assemble(hipStream_t s, int K, int P, int N, int Ns, const double* G, const double* YX,
                                 const double* Bt, const double* Dt, const double* lambda, const double* A,
-                                double* Bout, double* bw) {
-  const int nG = K * K + K * K * P + P * K * K * P;
+                                double* B64, float* B32, double* L64, int* bad, double* bw) {
   if (P > PMAX) return hipErrorInvalidValue;
-  GP_LAUNCH(k_data_assemble, dim3((N + DT - 1) / DT, K), dim3(DT), (size_t)nG * sizeof(double), s, K,
-                     P, N, Ns, G, YX, Bt, Dt, lambda, A, Bout, bw);
+  const double* tab = G + data_table_at(K, P);
+  const dim3 g((N + ASM_WG - 1) / ASM_WG), b(ASM_WG);
+  const unsigned nrhs = bw ? (K + ASM_KC - 1) / ASM_KC : 0;
+  switch (K) {
+#define X(KK)                                                                                                      \
+  case KK:                                                                                                         \
+    if (!ASM_FUSED<KK> && bw)                                                                                      \
+      GP_LAUNCH(k_data_rhs, dim3(g.x, nrhs), b, 0, s, K, P, N, Ns, YX, Bt, Dt, lambda, A, bw);                     \
+    GP_LAUNCH(k_data_assemble<KK>, dim3(g.x, ASM_FUSED<KK> ? 1 + nrhs : 1), b, 0, s, P, N, Ns, tab, YX, Bt, Dt,     \
+              lambda, A, B64, B32, L64, bad, bw);                                                                  \
+    break;
+    X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16) X(17) X(18) X(19) X(20)
+    X(21) X(22) X(23) X(24)
+#undef X
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

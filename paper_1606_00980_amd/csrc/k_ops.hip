@@ -155,38 +155,7 @@ __global__ __launch_bounds__(TILE) void k_pack_blocks(int N, const double* __res
 #pragma unroll
     for (int j = 0; j <= k; ++j) a[pk(k, j)] = 0.5 * (Bn[k * K + j] + Bn[j * K + k]);
   }
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    B64[(size_t)i * N + n] = a[i];
-    B32[(size_t)i * N + n] = (float)a[i];
-  }
-  double L[NB];
-  bool ok = true;
-  if constexpr (K <= KREG) {
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      double dj = a[pk(j, j)];
-#pragma unroll
-      for (int l = 0; l < j; ++l) dj -= L[pk(j, l)] * L[pk(j, l)];
-      ok = ok && (dj > 0.0) && (dj == dj);
-      const double ljj = sqrt(dj > 0.0 ? dj : 1.0);
-      L[pk(j, j)] = ljj;
-#pragma unroll
-      for (int i = j + 1; i < K; ++i) {
-        double v = a[pk(i, j)];
-#pragma unroll
-        for (int l = 0; l < j; ++l) v -= L[pk(i, l)] * L[pk(j, l)];
-        L[pk(i, j)] = v / ljj;
-      }
-    }
-  } else {
-#pragma unroll 1
-    for (int i = 0; i < NB; ++i) L[i] = a[i];
-    ok = cholesky_dyn(K, L);
-  }
-#pragma unroll
-  for (int i = 0; i < NB; ++i) L64[(size_t)i * N + n] = L[i];
-  if (!ok) atomicMin(bad, n);
+  pack_factor<K>(N, n, a, B64, B32, L64, bad);
 }
 
 // Preconditioner from the voxel block of Q, M_n = B_n + diag_k(alpha_k deg_n):

@@ -56,6 +56,10 @@ int finalize_rhs_per_block();
 // k_data.hip: time-summed AR(P) data tensors and the data term assembled from them
 // X: [T][data_design_stride(K)], the columns past K zero
 int data_design_stride(int K);
+// doubles of G: the globals [X'X | R | S], then (from data_table_at) the table
+// of the voxel blocks' coefficients
+size_t data_globals_size(int K, int P);
+size_t data_table_at(int K, int P);
 hipError_t launch_data_tensors(hipStream_t s, int T, int K, int P, int N, const double* X, const double* Y,
                                double* G, double* YX, double* Bt, double* Dt, double* YY, double* dY, double* dd);
 hipError_t launch_data_rss(hipStream_t s, int K, int P, int N, int Ns, const double* G, const double* YX,
@@ -69,9 +73,10 @@ hipError_t launch_quadform(hipStream_t s, const OpDev& op, int R, const double* 
 hipError_t launch_data_assemble_ar(hipStream_t s, int K, int P, int N, int Ns, const double* G, const double* Bt,
                                    const double* Dt, const double* dY, const double* dd, const double* lambda,
                                    const double* W, double* Jout, double* ba);
+// packed blocks, their Cholesky factors (bad: smallest failing voxel) and b_w (may be null)
 hipError_t launch_data_assemble(hipStream_t s, int K, int P, int N, int Ns, const double* G, const double* YX,
                                 const double* Bt, const double* Dt, const double* lambda, const double* A,
-                                double* Bout, double* bw);
+                                double* B64, float* B32, double* L64, int* bad, double* bw);
 
 // k_rng.hip: Philox4x32-10 normals, Rademacher signs and raw words
 hipError_t launch_rng_normal(hipStream_t s, uint64_t seed, uint64_t stream, size_t n, double* out);

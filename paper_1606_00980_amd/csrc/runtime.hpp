@@ -237,6 +237,9 @@ int read_bad(gp_op* op, int* bad);
 // Pack, factor and SPD-check device blocks B ([N][K][K] FP64) into op, as
 // gp_op_set_blocks does (the caller holds the context).
 int install_blocks(gp_op* op, const double* B, int64_t* bad_voxel);
+// after a launch that packed and factored op's blocks (reset_bad before it):
+// reads the flag and marks the blocks installed or the failing voxel
+int finish_blocks(gp_op* op, int64_t* bad_voxel);
 bool valid_opts(const gp_opts& o, std::string* why);
 // Length and outer-step mask (bit i: the outer step precedes iteration i) of
 // the next solver round, planned from the right-hand sides' states.

@@ -125,4 +125,42 @@ __device__ inline bool spd_inverse_any(double (&a)[K * (K + 1) / 2], double (&in
     return spd_inverse_dyn(K, a, inv);
 }
 
+// Stores the packed block a of voxel n in FP64 and FP32 (entry i at i * N + n),
+// factors it in place and stores the factor; a block that is not positive
+// definite lowers *bad to n.
+template <int K>
+__device__ inline void pack_factor(int N, int n, double (&a)[K * (K + 1) / 2], double* __restrict__ B64,
+                                   float* __restrict__ B32, double* __restrict__ L64, int* __restrict__ bad) {
+  constexpr int NB = K * (K + 1) / 2;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    B64[(size_t)i * N + n] = a[i];
+    B32[(size_t)i * N + n] = (float)a[i];
+  }
+  bool ok = true;
+  if constexpr (K <= KREG) {
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+      double dj = a[pk(j, j)];
+#pragma unroll
+      for (int l = 0; l < j; ++l) dj -= a[pk(j, l)] * a[pk(j, l)];
+      ok = ok && (dj > 0.0) && (dj == dj);
+      const double ljj = sqrt(dj > 0.0 ? dj : 1.0), inv = 1.0 / ljj;
+      a[pk(j, j)] = ljj;
+#pragma unroll
+      for (int i = j + 1; i < K; ++i) {
+        double v = a[pk(i, j)];
+#pragma unroll
+        for (int l = 0; l < j; ++l) v -= a[pk(i, l)] * a[pk(j, l)];
+        a[pk(i, j)] = v * inv;
+      }
+    }
+  } else {
+    ok = cholesky_dyn(K, a);
+  }
+#pragma unroll
+  for (int i = 0; i < NB; ++i) L64[(size_t)i * N + n] = a[i];
+  if (!ok) atomicMin(bad, n);
+}
+
 }  // namespace gp

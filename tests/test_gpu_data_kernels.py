@@ -87,3 +87,40 @@ def test_tensors_at_the_edges(g, ctx, torch_cuda, P, T, nx, K):
         assert np.abs(y.cpu().numpy()[0] - want).max() < 1e-12 * max(1.0, np.abs(B).max() * K * 10)
     g.gp_data_destroy(d)
     g.gp_op_destroy(op)
+
+
+@pytest.mark.parametrize("P,Ns,nx,K", [(0, 1, 1, 1), (1, 2, 63, 2), (2, 3, 64, 3), (3, 1, 65, 4), (3, 5, 129, 15),
+                                       (4, 2, 200, 6), (4, 1, 70, 24), (1, 4, 130, 17)])
+def test_blocks_and_residual_sums_over_draws(g, ctx, torch_cuda, P, Ns, nx, K):
+    """Blocks, b_w and residual sums of squares as means over draws of the whitened products."""
+    T = 60
+    X, Y, A, lam = problem(nx, K, T, P, Ns, 7 * P + Ns + nx + K)
+    W = np.random.default_rng(K).standard_normal((Ns, K, nx))
+    op = g.gp_op_create(ctx, np.ones((1, 1, nx), dtype=np.uint8), 4, K)
+    g.gp_op_set_alpha(op, np.zeros(K))
+    d = g.gp_data_create(op, T, P, X, dev(torch_cuda, Y))
+    Ad = dev(torch_cuda, A) if P else None
+    bw = torch_cuda.zeros((K, nx), dtype=torch_cuda.float64, device="cuda")
+    g.gp_data_assemble(d, dev(torch_cuda, lam), Ns, Ad, bw)
+    B, b, rss = np.zeros((nx, K, K)), np.zeros((K, nx)), np.zeros(nx)
+    for j in range(Ns):
+        Xw = whitened(np.repeat(X[:, :, None], nx, 2), A[j][:, None, :] if P else A[j], P)
+        Yw = whitened(Y, A[j], P)
+        B += lam[:, None, None] * np.einsum("tkn,tln->nkl", Xw, Xw) / Ns
+        b += lam * np.einsum("tkn,tn->kn", Xw, Yw) / Ns
+        rss += ((Yw - np.einsum("tkn,kn->tn", Xw, W[j])) ** 2).sum(0) / Ns
+    assert np.abs(bw.cpu().numpy() - b).max() < 1e-12 * np.abs(b).max() * 10
+    x = np.random.default_rng(1).standard_normal((1, K, nx))
+    y = torch_cuda.empty((1, K, nx), dtype=torch_cuda.float64, device="cuda")
+    g.gp_apply(op, 1, dev(torch_cuda, x), y)
+    want = np.einsum("nkl,ln->kn", B, x[0])
+    assert np.abs(y.cpu().numpy()[0] - want).max() < 1e-12 * np.abs(want).max() * 10
+    out = [torch_cuda.empty(nx, dtype=torch_cuda.float64, device="cuda") for _ in range(3)]
+    g.gp_data_lambda(d, Ns, dev(torch_cuda, W), Ad, 10.0, 0.1, *out)
+    # the quadratic form cancels terms of up to about T K^2 against rss
+    assert (np.abs(out[0].cpu().numpy() - rss) / rss).max() < 1e-14 * T * K * K
+    u1t = 1.0 / (0.5 * out[0].cpu().numpy() + 0.1)
+    assert np.allclose(out[1].cpu().numpy(), u1t, rtol=1e-14, atol=0)
+    assert np.allclose(out[2].cpu().numpy(), u1t * (0.5 * (T - P) + 0.1), rtol=1e-14, atol=0)
+    g.gp_data_destroy(d)
+    g.gp_op_destroy(op)
