@@ -457,7 +457,7 @@ int enqueue_inner(gp_ctx* c, hipStream_t q, bool f32, int pc, const std::vector<
 }
 
 int enqueue_round(gp_ctx* c, hipStream_t q, bool f32, int pc, const std::vector<LaunchGroup>& gs,
-                  const Prob* d_probs, int chunk, uint64_t outer_mask, bool profiled) {
+                  const Prob* d_probs, int chunk, uint64_t outer_mask, bool profiled, bool tail) {
   if (chunk == 0)   // the outer step alone
     return (outer_mask & 1) ? enqueue_outer(c, q, f32, pc, gs, d_probs, profiled) : GP_OK;
   for (int i = 0; i < chunk; ++i) {
@@ -465,6 +465,7 @@ int enqueue_round(gp_ctx* c, hipStream_t q, bool f32, int pc, const std::vector<
       if (int e = enqueue_outer(c, q, f32, pc, gs, d_probs, profiled)) return e;
     if (int e = enqueue_inner(c, q, f32, pc, gs, d_probs, 1, profiled)) return e;
   }
+  if (tail && chunk < 64 && ((outer_mask >> chunk) & 1)) return enqueue_outer(c, q, f32, pc, gs, d_probs, profiled);
   return GP_OK;
 }
 
@@ -513,15 +514,15 @@ int ensure_rb_states(gp_ctx* c, size_t n) {
 }
 
 int enqueue_round_branched(gp_ctx* c, hipStream_t q, bool f32, int pc, const std::vector<LaunchGroup>& gs,
-                           const Prob* d_probs, int chunk, uint64_t outer_mask) {
-  if (gs.size() <= 1) return enqueue_round(c, q, f32, pc, gs, d_probs, chunk, outer_mask, false);
+                           const Prob* d_probs, int chunk, uint64_t outer_mask, bool tail) {
+  if (gs.size() <= 1) return enqueue_round(c, q, f32, pc, gs, d_probs, chunk, outer_mask, false, tail);
   if (int e = ensure_branches(c, gs.size())) return e;
   HIPTRY(hipEventRecord(c->branch_ev[0], q));
   for (size_t g = 0; g < gs.size(); ++g) {
     hipStream_t b = c->branch[g];
     HIPTRY(hipStreamWaitEvent(b, c->branch_ev[0], 0));
     const std::vector<LaunchGroup> one{gs[g]};
-    if (int e = enqueue_round(c, b, f32, pc, one, d_probs, chunk, outer_mask, false)) return e;
+    if (int e = enqueue_round(c, b, f32, pc, one, d_probs, chunk, outer_mask, false, tail)) return e;
     HIPTRY(hipEventRecord(c->branch_ev[1 + g], b));
   }
   for (size_t g = 0; g < gs.size(); ++g) HIPTRY(hipStreamWaitEvent(q, c->branch_ev[1 + g], 0));
@@ -765,7 +766,8 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
   hipStream_t s = c->stream;
   HIPTRY(hipMemcpyAsync(c->d_probs, c->h_probs, np * sizeof(Prob), hipMemcpyHostToDevice, s));
   HIPTRY(hipMemsetAsync(ws + st_all, 0, totalR * sizeof(RhsState), s));
-  for (int j = 0; j < np; ++j) HIPTRY(hipMemsetAsync(ws + lay[j].prof, 0, NPROF * sizeof(long long), s));
+  if (c->prof_on)
+    for (int j = 0; j < np; ++j) HIPTRY(hipMemsetAsync(ws + lay[j].prof, 0, NPROF * sizeof(long long), s));
 
   // One round = [x += d, refine, finalise] then a chunk of inner iterations
   // [matvec, finalise, update] x chunk.  Without profiling both are captured
@@ -790,6 +792,32 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
   // right-hand side iterates is the outer step alone
   int round_len = chunk;
   uint64_t round_mask = f32 && o.chunk > 0 ? ~0ull : 1ull;
+  // the first round replays the shape of every operator's previous solve at
+  // these settings, the final refinement included (one round and one wait, and
+  // no idle iterations, where the solve behaves as the previous one): the
+  // whole brain's FP64 solve, 13 iterations in four rounds of up to six, 415 to
+  // 290 us; 16 default samples 1,169 to 1,028 us; a 36-iteration slice solve and
+  // sample 1,154 to 675 us
+  bool tail = false;
+  auto shape = [&](int j) -> SolveShape& {
+    return items[order[j]].op->shape[o.precond == GP_PRECOND_BLOCK_JACOBI][f32];
+  };
+  if (o.chunk <= 0) {
+    bool have = true;
+    uint64_t m = 0;
+    int len = 0;
+    for (int j = 0; j < np; ++j) {
+      const SolveShape& sh = shape(j);
+      have = have && sh.mask && sh.len > 0 && sh.tol == o.tol && sh.inner_tol == o.inner_tol;
+      m |= sh.mask;
+      len = std::max(len, sh.len);
+    }
+    if (have) {
+      round_len = len;
+      round_mask = m;
+      tail = true;
+    }
+  }
   auto launch_round = [&](bool outer_only) -> int {
     if (outer_only) {
       if (!graphs) return enqueue_outer(c, s, f32, pc, groups, c->d_probs, true);
@@ -798,16 +826,19 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
     }
     const int n = round_len;
     const uint64_t m = round_mask;
-    if (!graphs) return enqueue_round(c, s, f32, pc, groups, c->d_probs, n, m, true);
-    return replay(layout_key + "|round" + std::to_string(n) + "/" + std::to_string(m),
-                  [&](hipStream_t q) { return enqueue_round_branched(c, q, f32, pc, groups, c->d_probs, n, m); });
+    const bool tl = tail;
+    if (!graphs) return enqueue_round(c, s, f32, pc, groups, c->d_probs, n, m, true, tl);
+    return replay(layout_key + "|round" + std::to_string(n) + "/" + std::to_string(m) + (tl ? "t" : ""),
+                  [&](hipStream_t q) { return enqueue_round_branched(c, q, f32, pc, groups, c->d_probs, n, m, tl); });
   };
   // host copy of every right-hand side's state
+  if (int e = ensure_rb_states(c, totalR)) return e;
   std::vector<RhsState> hs(totalR);
   int n_outer = (int)totalR, n_inner = 0;
   auto read_states = [&]() -> int {
-    HIPTRY(hipMemcpyAsync(hs.data(), ws + st_all, totalR * sizeof(RhsState), hipMemcpyDeviceToHost, s));
+    HIPTRY(hipMemcpyAsync(c->h_rbst, ws + st_all, totalR * sizeof(RhsState), hipMemcpyDeviceToHost, s));
     HIPTRY(hipStreamSynchronize(s));
+    std::memcpy(hs.data(), c->h_rbst, totalR * sizeof(RhsState));
     n_outer = n_inner = 0;
     for (const RhsState& h : hs) {
       n_outer += h.phase == PH_OUTER;
@@ -822,11 +853,23 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
   auto plan = [&]() { plan_round(hs, o, f32, chunk, &round_len, &round_mask); };
   while (n_outer > 0 || n_inner > 0) {
     if (++rounds > max_rounds) return fail(GP_ERR_DEVICE, "solver driver made no progress");
-    st = launch_round(!f32 && n_inner == 0);
+    st = launch_round(!f32 && n_inner == 0 && !tail);
     if (st) return st;
+    tail = false;
     st = read_states();
     if (st) return st;
     plan();
+  }
+  {
+    size_t at = 0;
+    for (int j = 0; j < np; ++j) {
+      uint64_t m = 0;
+      for (int r = 0; r < items[order[j]].R; ++r) m |= hs[at++].slots;
+      int len = 0;
+      while (len < 63 && (m >> (len + 1)) != 0) ++len;
+      // a shape that reaches the last bit (63 or more iterations) is not replayed
+      shape(j) = SolveShape{len < 63 ? m : 0, len, o.tol, o.inner_tol};
+    }
   }
   // results (hs holds the final states, in problem order)
   int ret = GP_OK;

@@ -83,7 +83,7 @@ struct gp_ctx {
   bool use_graphs = true;
   // autotuned configurations keyed by tune_key()
   std::map<std::string, TuneEntry> tuned;
-  // red-black solver: grouped-launch descriptors and a pinned copy of the states
+  // pinned copy of the states; red-black solver: grouped-launch descriptors
   gp::RbProb* d_rbp = nullptr;
   gp::RbProb* h_rbp = nullptr;
   size_t rbp_cap = 0;
@@ -96,6 +96,17 @@ namespace rt {
 struct RbData;
 }  // namespace rt
 }  // namespace gp
+
+// Shape of an operator's last solve at one preconditioner, precision and pair
+// of tolerances: the union over its right-hand sides of the iteration counts
+// after which they took an outer step (bit i: after i), and the largest such
+// count.  The first round of the next solve at the same settings replays it; a
+// solve that turns out longer goes on in planned rounds.
+struct SolveShape {
+  uint64_t mask = 0;   // 0: none
+  int len = 0;
+  double tol = 0.0, inner_tol = 0.0;
+};
 
 struct gp_op {
   gp_ctx* ctx = nullptr;
@@ -119,6 +130,7 @@ struct gp_op {
   bool have_blocks = false, have_alpha = false;
   int pc_built = -1;
   int pc_want = GP_PRECOND_BLOCK_JACOBI;
+  SolveShape shape[2][2];   // [Jacobi, block Jacobi][FP64, FP32]
   gp::rt::RbData* rb = nullptr;   // red-black split and its preconditioner, built on first use
   size_t bytes = 0;
 };
@@ -184,12 +196,12 @@ int enqueue_inner(gp_ctx* c, hipStream_t q, bool f32, int pc, const std::vector<
 // every few iterations, the host places it where inner solves are expected to
 // end, so a right-hand side rarely idles until the next round.
 int enqueue_round(gp_ctx* c, hipStream_t q, bool f32, int pc, const std::vector<LaunchGroup>& gs,
-                  const Prob* d_probs, int chunk, uint64_t outer_mask, bool profiled);
+                  const Prob* d_probs, int chunk, uint64_t outer_mask, bool profiled, bool tail = false);
 // The same round with each launch group on a branch stream forked from q and
 // joined back into it (used while capturing, so that the groups of an uneven
 // batch become parallel graph branches).
 int enqueue_round_branched(gp_ctx* c, hipStream_t q, bool f32, int pc, const std::vector<LaunchGroup>& gs,
-                           const Prob* d_probs, int chunk, uint64_t outer_mask);
+                           const Prob* d_probs, int chunk, uint64_t outer_mask, bool tail = false);
 
 // Branch streams (and fork/join events) for capturing n launch groups as
 // parallel graph branches.
