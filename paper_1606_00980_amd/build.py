@@ -30,7 +30,7 @@ OUT_SAN = os.path.join(HERE, "libgmrf_san.so")
 BUILD = os.path.join(HERE, "_build")
 BUILD_SAN = os.path.join(BUILD, "san")
 
-SOURCES = ["k_pcg_f32.hip", "k_pcg_f64.hip", "k_ops.hip", "k_rng.hip", "k_data.hip", "k_rbic_f32.hip",
+SOURCES = ["k_pcg_f32.hip", "k_pcg_f64.hip", "k_small.hip", "k_ops.hip", "k_rng.hip", "k_data.hip", "k_rbic_f32.hip",
            "k_rbic_f64.hip", "api.cpp", "server.cpp", "tune.cpp", "data.cpp", "rbic.cpp"]
 
 ARCH = "gfx950"

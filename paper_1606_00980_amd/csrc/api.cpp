@@ -674,7 +674,24 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
   std::vector<int> order;
   for (int i = 0; i < (int)items.size(); ++i)
     if (items[i].R > 0) order.push_back(i);
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return items[a].op->K < items[b].op->K; });
+  // an FP64 solve of an operator small enough runs as one launch (k_small.hip)
+  // after the others in the descriptor array, by K and voxels per lane, unless
+  // the caller asks for a launch configuration of the grouped kernels.  The
+  // rule looks at the operator alone, so that a right-hand side gets the same
+  // bits in any batch.
+  const int kpc = o.precond == GP_PRECOND_JACOBI ? PC_JACOBI : PC_BLOCK;
+  auto small_v = [&](int i) {
+    return !f32 && o.rhs_tile == 0 && o.wg_per_cu == 0 && o.matvec == GP_MATVEC_AUTO
+               ? small_lane_voxels(kpc, items[i].op->N, items[i].op->K)
+               : 0;
+  };
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+    const int va = small_v(a), vb = small_v(b), ka = items[a].op->K, kb = items[b].op->K;
+    if ((va > 0) != (vb > 0)) return vb > 0;
+    return ka != kb ? ka < kb : va < vb;
+  });
+  int nl = 0;   // problems of the grouped kernels: descriptors [0, nl)
+  while (nl < (int)order.size() && small_v(order[nl]) == 0) ++nl;
   const int np = (int)order.size();
   if (np == 0) {
     if (stats) {
@@ -707,13 +724,13 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
   }
   for (int j = 0; j < np; ++j) {
     const Item& it = items[order[j]];
-    const size_t nv = (size_t)it.R * it.op->K * it.op->N;
+    const size_t nv = j < nl ? (size_t)it.R * it.op->K * it.op->N : 0;
     for (int v = 0; v < NVEC; ++v) {
       lay[j].vec[v] = off;
       off = align_up(off + nv * tsz, 256);
     }
     lay[j].part = off;
-    off = align_up(off + (size_t)NPART * it.R * plans[j].pstride * sizeof(double), 256);
+    if (j < nl) off = align_up(off + (size_t)NPART * it.R * plans[j].pstride * sizeof(double), 256);
     lay[j].prof = off;
     off = align_up(off + NPROF * sizeof(long long), 256);
   }
@@ -724,6 +741,10 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
   char* ws = (char*)c->ws;
   // descriptors, one grouped launch per distinct K
   std::vector<LaunchGroup> groups;
+  struct SmallGroup {
+    int K, V, first, count, nrhs;
+  };
+  std::vector<SmallGroup> smalls;
   const SolveCfg cfg{o.tol, f32 ? o.inner_tol : 0.0, o.max_iter, o.max_outer, o.zero_guess ? 1 : 0, 0};
   const int fpb = finalize_rhs_per_block();
   for (int j = 0; j < np; ++j) {
@@ -741,6 +762,16 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
     p.part = (double*)(ws + lay[j].part);
     p.prof = c->prof_on ? (long long*)(ws + lay[j].prof) : nullptr;
     p.R = it.R;
+    if (j >= nl) {
+      p.cfg = cfg;
+      const int v = small_v(order[j]);
+      if (smalls.empty() || smalls.back().K != it.op->K || smalls.back().V != v)
+        smalls.push_back(SmallGroup{it.op->K, v, j, 0, 0});
+      p.sm_begin = smalls.back().nrhs;
+      smalls.back().nrhs += it.R;
+      smalls.back().count += 1;
+      continue;
+    }
     if (!groups.empty() && groups.back().K == it.op->K && groups.back().mv_mode != plans[j].mv_mode) {
       // one matvec kernel per grouped launch: follow the group's first problem
       gp_opts oj = popts[j];
@@ -777,7 +808,7 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
   std::string layout_key;
   if (graphs) {
     layout_key = std::to_string((uintptr_t)c->d_probs) + (f32 ? "f" : "d") + std::to_string(o.precond);
-    for (int j = 0; j < np; ++j) layout_key += ":" + std::to_string(plans[j].Rc);
+    for (int j = 0; j < nl; ++j) layout_key += ":" + std::to_string(plans[j].Rc);
     for (const LaunchGroup& g : groups)
       layout_key += "|" + std::to_string(g.K) + "," + std::to_string(g.count) + "," + std::to_string(g.W) + "," +
                     std::to_string(g.F) + "," + std::to_string(g.nblk) + "," + std::to_string(g.mv_mode) + "," +
@@ -806,7 +837,7 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
     bool have = true;
     uint64_t m = 0;
     int len = 0;
-    for (int j = 0; j < np; ++j) {
+    for (int j = 0; j < nl; ++j) {
       const SolveShape& sh = shape(j);
       have = have && sh.mask && sh.len > 0 && sh.tol == o.tol && sh.inner_tol == o.inner_tol;
       m |= sh.mask;
@@ -851,6 +882,29 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
   const long max_rounds = (long)o.max_iter + 4L * o.max_outer + 8;
   long rounds = 0;
   auto plan = [&]() { plan_round(hs, o, f32, chunk, &round_len, &round_mask); };
+  // small solves, a launch per (K, voxels per lane), several on branch streams
+  if (!smalls.empty()) {
+    if (smalls.size() == 1 || c->prof_on) {
+      for (const SmallGroup& g : smalls)
+        PROFILED_IF(c->prof_on, c, GP_KERNEL_MATVEC,
+                    launch_small(s, kpc, g.K, g.V, c->d_probs + g.first, g.count, g.nrhs));
+    } else {
+      if (int e = ensure_branches(c, smalls.size())) return e;
+      HIPTRY(hipEventRecord(c->branch_ev[0], s));
+      hipError_t le = hipSuccess;
+      for (size_t i = 0; i < smalls.size(); ++i) {
+        const SmallGroup& g = smalls[i];
+        HIPTRY(hipStreamWaitEvent(c->branch[i], c->branch_ev[0], 0));
+        const hipError_t e = launch_small(c->branch[i], kpc, g.K, g.V, c->d_probs + g.first, g.count, g.nrhs);
+        if (le == hipSuccess) le = e;
+        HIPTRY(hipEventRecord(c->branch_ev[1 + i], c->branch[i]));
+        HIPTRY(hipStreamWaitEvent(s, c->branch_ev[1 + i], 0));
+      }
+      HIPTRY(le);
+    }
+    if (nl == 0)
+      if (int e = read_states()) return e;
+  }
   while (n_outer > 0 || n_inner > 0) {
     if (++rounds > max_rounds) return fail(GP_ERR_DEVICE, "solver driver made no progress");
     st = launch_round(!f32 && n_inner == 0 && !tail);
@@ -862,7 +916,7 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
   }
   {
     size_t at = 0;
-    for (int j = 0; j < np; ++j) {
+    for (int j = 0; j < nl; ++j) {
       uint64_t m = 0;
       for (int r = 0; r < items[order[j]].R; ++r) m |= hs[at++].slots;
       int len = 0;

@@ -87,6 +87,7 @@ struct Prob {
   int R, Rc, nchunks, work_begin, work_count;   // matvec / update: Rc right-hand sides per work item
   int Rco, nchunks_o, work_begin_o, work_count_o;   // refine / addsol: Rco per work item
   int fin_begin;         // first finalising workgroup of this problem
+  int sm_begin;          // first workgroup of this problem in a launch of small solves
   int pstride;           // partials per (value, right-hand side): max(raster, z-march tiles)
   // z-marching matvec (mv_mode = 1): footprint tiles x segments of zs slices
   int mv_mode, zs, nseg, nyt, mv_tiles, mv_nchunks, mv_begin, mv_count;

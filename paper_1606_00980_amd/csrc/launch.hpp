@@ -103,6 +103,12 @@ hipError_t launch_addsol_f32(hipStream_t s, int K, const Prob* probs, int nprob,
 // right-hand sides per z-marching workgroup for K regressors
 int zm_rhs_per_block(int K);
 
+// k_small.hip: whole FP64 solves of small operators, one workgroup per
+// right-hand side (nrhs over the nprob problems, all of K regressors and V
+// voxels per lane)
+int small_lane_voxels(int pc, int N, int K);
+hipError_t launch_small(hipStream_t s, int pc, int K, int V, const Prob* probs, int nprob, int nrhs);
+
 // k_rbic_f32.hip / k_rbic_f64.hip: red-black incomplete Cholesky.  Vectors of
 // the black system are [R][K][NB], red ones [R][K][NR].  Set-up, split and
 // recovery take one operator's descriptor by value; the solver-round launches

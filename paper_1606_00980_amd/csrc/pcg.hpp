@@ -309,8 +309,7 @@ __device__ inline void prof_launch(const Prob& pr, int act, int phase) {
     atomicAdd((unsigned long long*)&pr.prof[act], 1ull);
 }
 
-__device__ inline void finalize_refine(const Prob& pr, int r, const double (&v)[3]) {
-  RhsState& s = pr.st[r];
+__device__ inline void finalize_refine(const Prob& pr, RhsState& s, const double (&v)[3]) {
   const double rr = v[0], bb = v[1], rz = v[2];
   prof_add(pr, PF_REFINE_RHS, 1);
   prof_add(pr, PF_ADDSOL_D, s.has_d);
@@ -351,8 +350,7 @@ __device__ inline void finalize_refine(const Prob& pr, int r, const double (&v)[
 }
 
 // v = (p'q, r'z, q'z, q't, r'r, q'r, q'q) of the step just taken.
-__device__ inline void finalize_matvec(const Prob& pr, int r, const double (&v)[7]) {
-  RhsState& s = pr.st[r];
+__device__ inline void finalize_matvec(const Prob& pr, RhsState& s, const double (&v)[7]) {
   prof_add(pr, PF_MATVEC_RHS, 1);
   const double sigma = v[0], rz = v[1];
   if (!(sigma > 0.0) || !finite(sigma) || !(rz > 0.0) || !finite(rz)) {
@@ -401,11 +399,11 @@ __global__ __launch_bounds__(FIN_WAVES * WAVE) void k_finalize(const Prob* __res
   if constexpr (KIND == 0) {
     double v[3];
     sum_partials<3>(pr.part, pr.R, pr.pstride, pr.op.ntiles, r, v);
-    if (lane == 0) finalize_refine(pr, r, v);
+    if (lane == 0) finalize_refine(pr, pr.st[r], v);
   } else {
     double v[7];
     sum_partials<7>(pr.part, pr.R, pr.pstride, pr.mv_mode ? pr.mv_tiles : pr.op.ntiles, r, v);
-    if (lane == 0) finalize_matvec(pr, r, v);
+    if (lane == 0) finalize_matvec(pr, pr.st[r], v);
   }
 }
 

@@ -949,11 +949,11 @@ __global__ __launch_bounds__(FIN_WAVES * WAVE) void k_rb_finalize(const RbProb* 
     sum_partials<3>(pr.part, pr.R, pr.pstride, ntB, r, v);
     sum_partials<1>(P.bb, 1, ntN, ntN, r, bb);
     v[1] = bb[0];
-    if (lane == 0) finalize_refine(pr, r, v);
+    if (lane == 0) finalize_refine(pr, pr.st[r], v);
   } else {
     double v[7];
     sum_partials<7>(pr.part, pr.R, pr.pstride, ntB, r, v);
-    if (lane == 0) finalize_matvec(pr, r, v);
+    if (lane == 0) finalize_matvec(pr, pr.st[r], v);
   }
 }
 

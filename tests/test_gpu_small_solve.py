@@ -1,0 +1,97 @@
+"""FP64 solves of small operators (one workgroup per right-hand side) against
+the oracle and the grouped kernels, at the edges of their voxel tilings."""
+import numpy as np
+import pytest
+
+from oracle import gmrf_oracle as orc
+from paper_1606_00980_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    return torch
+
+
+@pytest.fixture(scope="module")
+def g(built_library, torch_cuda):
+    from paper_1606_00980_amd import gmrf
+    return gmrf
+
+
+@pytest.fixture(scope="module")
+def ctx(g, torch_cuda):
+    h = g.gp_ctx_create(0, torch_cuda.cuda.current_stream().cuda_stream, 0)
+    yield h
+    torch_cuda.cuda.synchronize()
+    g.gp_ctx_destroy(h)
+
+
+def operator(nx, ny, K, seed):
+    """A box slice with random SPD blocks and alpha."""
+    r = np.random.default_rng(seed)
+    N = nx * ny
+    X = r.standard_normal((N, K + 3, K))
+    B = np.einsum("ntk,ntl->nkl", X, X) + 0.2 * np.eye(K)
+    return np.ones((1, ny, nx), dtype=np.uint8), B, r.gamma(2.0, 1.0, K), r.standard_normal((3, K, N))
+
+
+# (nx, ny): one voxel, around 512 voxels per workgroup sweep, several per lane
+@pytest.mark.parametrize("pc", ["JACOBI", "BLOCK_JACOBI"])
+@pytest.mark.parametrize("nx,ny,K", [(1, 1, 1), (7, 73, 2), (16, 32, 8), (27, 19, 7), (41, 25, 6), (37, 41, 5),
+                                     (43, 47, 4), (45, 57, 3), (61, 67, 2), (79, 77, 1)])
+def test_small_solves(g, ctx, torch_cuda, pc, nx, ny, K):
+    torch = torch_cuda
+    mask, B, alpha, b = operator(nx, ny, K, nx + ny + K)
+    op = g.gp_op_create(ctx, mask, 4, K)
+    Bd = torch.from_numpy(B).cuda()
+    g.gp_op_set_blocks(op, Bd)
+    g.gp_op_set_alpha(op, alpha)
+    Q = orc.precision(orc.grid(mask, 4), alpha, B)
+    ref = np.stack([orc.solve(Q, b[i:i + 1])[0] for i in range(3)])
+    bd = torch.from_numpy(b).cuda()
+    kw = dict(tol=1e-10, precision=g.GP_PREC_FP64, precond=getattr(g, "GP_PRECOND_" + pc))
+    x = torch.full_like(bd, float("nan"))
+    _, st = g.gp_solve(op, 3, bd, x, g.gp_opts_default(zero_guess=1, **kw))
+    grouped = torch.zeros_like(bd)
+    _, sg = g.gp_solve(op, 3, bd, grouped, g.gp_opts_default(rhs_tile=4, **kw))
+    for i in range(3):
+        scale = np.linalg.norm(ref[i])
+        assert st[i]["relres"] <= 1e-10
+        assert np.linalg.norm(x[i].cpu().numpy() - ref[i]) <= 1e-8 * scale
+        # the same iterates in exact arithmetic
+        assert abs(st[i]["inner_iters"] - sg[i]["inner_iters"]) <= 1
+        assert np.linalg.norm((x[i] - grouped[i]).cpu().numpy()) <= 1e-8 * scale
+    # alone and in a batch with another operator: the same bits
+    one = torch.zeros_like(bd[:1])
+    g.gp_solve(op, 1, bd[1:2], one, g.gp_opts_default(zero_guess=1, **kw))
+    assert torch.equal(one[0], x[1])
+    w = synth.tiny((13, 11, 7), 6, 3, seed=3)
+    other = g.gp_op_create(ctx, w.mask, w.conn, w.K)
+    wB, wb = torch.from_numpy(w.B).cuda(), torch.from_numpy(w.bw[None].copy()).cuda()
+    g.gp_op_set_blocks(other, wB)
+    g.gp_op_set_alpha(other, w.alpha)
+    x2, xo = torch.zeros_like(bd), torch.zeros_like(wb)
+    _, sb = g.gp_solve_batch(ctx, [(op, 3, bd, x2), (other, 1, wb, xo)], g.gp_opts_default(zero_guess=1, **kw))
+    assert torch.equal(x2, x) and all(s["status"] == g.GP_OK for s in sb)
+    # a warm start at the solution, b = 0, an iteration cap and a NaN
+    _, sw = g.gp_solve(op, 3, bd, x2, g.gp_opts_default(**kw))
+    assert all(s["inner_iters"] <= 1 for s in sw)
+    bd2 = bd.clone()
+    bd2[0] = 0.0
+    bd2[2, 0, 0] = float("nan")
+    x3 = torch.full_like(bd, float("nan"))
+    st3, s3 = g.gp_solve(op, 3, bd2, x3, g.gp_opts_default(zero_guess=1, **kw), check=False)
+    assert s3[0]["status"] == g.GP_OK and s3[0]["inner_iters"] == 0 and not x3[0].any()
+    assert s3[1]["status"] == g.GP_OK and torch.equal(x3[1], x[1])
+    assert s3[2]["status"] == g.GP_ERR_BREAKDOWN
+    if st[0]["inner_iters"] > 2:
+        _, sc = g.gp_solve(op, 3, bd, x3, g.gp_opts_default(zero_guess=1, max_iter=2, **kw), check=False)
+        assert sc[0]["status"] == g.GP_ERR_NOT_CONVERGED and sc[0]["inner_iters"] == 2
+    g.gp_op_destroy(other)
+    g.gp_op_destroy(op)
