@@ -447,7 +447,7 @@ int enqueue_inner(gp_ctx* c, hipStream_t q, bool f32, int pc, const std::vector<
         PROFILED_IF(pf, c, GP_KERNEL_MATVEC,
                     f32 ? launch_matvec_f32(q, pc, g.K, dp, g.count, g.W, g.nblk)
                         : launch_matvec_f64(q, pc, g.K, dp, g.count, g.W, g.nblk));
-      HIPTRY(launch_finalize(q, 1, dp, g.count, g.F));
+      if (g.need_fin) HIPTRY(launch_finalize(q, 1, dp, g.count, g.F));
       PROFILED_IF(pf, c, GP_KERNEL_UPDATE,
                   f32 ? launch_update_f32(q, pc, g.K, dp, g.count, g.W, g.nblk)
                       : launch_update_f64(q, pc, g.K, dp, g.count, g.W, g.nblk));
@@ -783,6 +783,8 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
     if (groups.empty() || groups.back().K != it.op->K)
       groups.push_back(LaunchGroup{it.op->K, j, 0, 0, 0, 0, 0, 0, plans[j].mv_mode, popts[j].wg_per_cu, 0, 0});
     LaunchGroup& g = groups.back();
+    p.fin = !plans[j].mv_mode && update_finalizes(it.op->ntiles, it.op->K);
+    g.need_fin = g.need_fin || !p.fin;
     p.work_begin = g.W;
     g.W += p.work_count;
     p.work_begin_o = g.Wo;
@@ -813,7 +815,7 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
       layout_key += "|" + std::to_string(g.K) + "," + std::to_string(g.count) + "," + std::to_string(g.W) + "," +
                     std::to_string(g.F) + "," + std::to_string(g.nblk) + "," + std::to_string(g.mv_mode) + "," +
                     std::to_string(g.Wmv) + "," + std::to_string(g.nblk_mv) + "," + std::to_string(g.Wo) + "," +
-                    std::to_string(g.nblk_o);
+                    std::to_string(g.nblk_o) + (g.need_fin ? "f" : "");
   }
   auto replay = [&](const std::string& key, const std::function<int(hipStream_t)>& enqueue) -> int {
     return graph_replay(c, key, enqueue);

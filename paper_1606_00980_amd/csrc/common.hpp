@@ -48,6 +48,11 @@ struct RhsState {
   int has_d;        // the inner correction d holds a valid sum
   int pend;         // a * p of the last iteration is still to be added to x
   int zero_b;
+  // the fields a step's finalisation reads, as they were when its matvec ran
+  // (written by the matvec): the update's workgroups each finalise the step
+  // from these while one of them advances the fields above
+  double step_target2;
+  int step_phase, step_inner, step_total, step_spare;
 };
 
 // Device view of one operator.
@@ -89,6 +94,7 @@ struct Prob {
   int fin_begin;         // first finalising workgroup of this problem
   int sm_begin;          // first workgroup of this problem in a launch of small solves
   int pstride;           // partials per (value, right-hand side): max(raster, z-march tiles)
+  int fin;               // the update launch finalises the step (no finalising launch)
   // z-marching matvec (mv_mode = 1): footprint tiles x segments of zs slices
   int mv_mode, zs, nseg, nyt, mv_tiles, mv_nchunks, mv_begin, mv_count;
   SolveCfg cfg;

@@ -74,9 +74,8 @@ __global__ __launch_bounds__(SM_WG) void k_small(const Prob* __restrict__ probs,
   auto neighbour = [&](int v, int d) { return (int)((nb[v][d / 2] >> (16 * (d % 2))) & 0xFFFFu); };
   double r[V][K], d[V][K], q[V][K];
   RhsState s{};
-  Prob quiet = pr;   // the finalisers count for the profiler on one lane
-  if (threadIdx.x != 0) quiet.prof = nullptr;
-  if (quiet.prof) {
+  long long* prof = threadIdx.x == 0 ? pr.prof : nullptr;   // the finalisers count for the profiler on one lane
+  if (prof) {
     atomicAdd((unsigned long long*)&pr.prof[PF_REFINE_ACT], 1ull);
     atomicAdd((unsigned long long*)&pr.prof[PF_MATVEC_ACT], 1ull);
     atomicAdd((unsigned long long*)&pr.prof[PF_UPDATE_ACT], 1ull);
@@ -172,7 +171,7 @@ __global__ __launch_bounds__(SM_WG) void k_small(const Prob* __restrict__ probs,
       }
       double tot[3];
       group_sums<3>(s_red, acc, tot);
-      finalize_refine(quiet, s, tot);
+      finalize_refine(cfg, prof, s, tot);
 #pragma unroll
       for (int v = 0; v < V; ++v)
         if (ok[v]) {
@@ -211,7 +210,7 @@ __global__ __launch_bounds__(SM_WG) void k_small(const Prob* __restrict__ probs,
       }
       double tot[NPART];
       group_sums<NPART>(s_red, acc, tot);
-      finalize_matvec(quiet, s, tot);
+      finalize_matvec(cfg, prof, s, tot);
       if (s.phase == PH_INNER) {
         // d += a p, r -= a q, p = M^{-1} r + beta p
         const bool first = s.inner_it == 1;

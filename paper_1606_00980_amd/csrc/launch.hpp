@@ -52,6 +52,15 @@ hipError_t launch_trace(hipStream_t s, const OpDev& op, int m, const int8_t* v, 
 // nblocks = sum over problems of ceil(R / finalize_rhs_per_block()).
 hipError_t launch_finalize(hipStream_t s, int kind, const Prob* probs, int nprob, int nblocks);
 int finalize_rhs_per_block();
+// Whether the update launch finalises a step itself (nt tiles, K regressors).
+// Each of its workgroups then sums the partials of its right-hand sides again,
+// 56 nt bytes each against the 28 K per voxel (FP32) that it moves anyway, and
+// a launch of 4 to 5 us is saved per step: the whole brain's FP64 solve (block
+// Jacobi, nt = 206, K = 6) 300 to 276 us, 16 default samples 1,047 to 1,018 us,
+// a Gibbs iteration 410 to 398 us, an FP64 trace 453 to 434 us.  The largest
+// operator (red-black, nt = 567, K = 10, 64 right-hand sides) would read 1.1 GB
+// of partials per step: 18.63 to 18.77 ms.
+inline bool update_finalizes(int nt, int K) { return nt <= 48 * K; }
 
 // k_data.hip: time-summed AR(P) data tensors and the data term assembled from them
 // X: [T][data_design_stride(K)], the columns past K zero

@@ -297,8 +297,8 @@ __device__ inline bool any_in_phase(const Prob& pr, int r0, int r1, int phase) {
 // Each finaliser advances one right-hand side from the per-tile partials of
 // the launch that just ended; it runs on lane 0 of the wavefront that summed
 // them.  Counters for the profiler are added with integer atomics.
-__device__ inline void prof_add(const Prob& pr, int slot, long long v) {
-  if (pr.prof && v) atomicAdd((unsigned long long*)&pr.prof[slot], (unsigned long long)v);
+__device__ inline void prof_add(long long* prof, int slot, long long v) {
+  if (prof && v) atomicAdd((unsigned long long*)&prof[slot], (unsigned long long)v);
 }
 
 // Counts a launch in slot `act` when any right-hand side of the problem is in
@@ -309,13 +309,13 @@ __device__ inline void prof_launch(const Prob& pr, int act, int phase) {
     atomicAdd((unsigned long long*)&pr.prof[act], 1ull);
 }
 
-__device__ inline void finalize_refine(const Prob& pr, RhsState& s, const double (&v)[3]) {
+__device__ inline void finalize_refine(const SolveCfg& cfg, long long* prof, RhsState& s, const double (&v)[3]) {
   const double rr = v[0], bb = v[1], rz = v[2];
-  prof_add(pr, PF_REFINE_RHS, 1);
-  prof_add(pr, PF_ADDSOL_D, s.has_d);
-  prof_add(pr, PF_ADDSOL_P, s.pend);
-  prof_add(pr, PF_REFINE_X0, pr.cfg.zero_guess && s.outer == 0);
-  prof_add(pr, PF_ADDSOL_FRESH, pr.cfg.zero_guess && s.outer == 1);
+  prof_add(prof, PF_REFINE_RHS, 1);
+  prof_add(prof, PF_ADDSOL_D, s.has_d);
+  prof_add(prof, PF_ADDSOL_P, s.pend);
+  prof_add(prof, PF_REFINE_X0, cfg.zero_guess && s.outer == 0);
+  prof_add(prof, PF_ADDSOL_FRESH, cfg.zero_guess && s.outer == 1);
   s.slots |= 1ull << (s.total_it < 63 ? s.total_it : 63);
   if (s.outer == 0) s.bnorm2 = bb;
   s.has_d = 0;
@@ -332,15 +332,15 @@ __device__ inline void finalize_refine(const Prob& pr, RhsState& s, const double
     s.relres = rel;
     if (!finite(rel)) {
       s.status = ST_BREAKDOWN; s.phase = PH_DONE;
-    } else if (rel <= pr.cfg.tol) {
+    } else if (rel <= cfg.tol) {
       s.status = ST_OK; s.phase = PH_DONE;
-    } else if (s.outer >= pr.cfg.max_outer || s.total_it >= pr.cfg.max_iter) {
+    } else if (s.outer >= cfg.max_outer || s.total_it >= cfg.max_iter) {
       s.status = ST_NOT_CONVERGED; s.phase = PH_DONE;
     } else if (!(rz > 0.0) || !finite(rz)) {
       s.status = ST_BREAKDOWN; s.phase = PH_DONE;
     } else {
-      const double it2 = pr.cfg.inner_tol * pr.cfg.inner_tol * rr;
-      const double ot2 = 0.25 * pr.cfg.tol * pr.cfg.tol * bn2;
+      const double it2 = cfg.inner_tol * cfg.inner_tol * rr;
+      const double ot2 = 0.25 * cfg.tol * cfg.tol * bn2;
       s.target2 = it2 > ot2 ? it2 : ot2;
       s.rho = rz;
       s.inner_it = 0;
@@ -350,8 +350,8 @@ __device__ inline void finalize_refine(const Prob& pr, RhsState& s, const double
 }
 
 // v = (p'q, r'z, q'z, q't, r'r, q'r, q'q) of the step just taken.
-__device__ inline void finalize_matvec(const Prob& pr, RhsState& s, const double (&v)[7]) {
-  prof_add(pr, PF_MATVEC_RHS, 1);
+__device__ inline void finalize_matvec(const SolveCfg& cfg, long long* prof, RhsState& s, const double (&v)[7]) {
+  prof_add(prof, PF_MATVEC_RHS, 1);
   const double sigma = v[0], rz = v[1];
   if (!(sigma > 0.0) || !finite(sigma) || !(rz > 0.0) || !finite(rz)) {
     if (s.inner_it == 0) {
@@ -369,16 +369,66 @@ __device__ inline void finalize_matvec(const Prob& pr, RhsState& s, const double
   s.total_it += 1;
   if (!finite(rho) || !finite(rr) || !finite(a)) {
     s.has_d = 0; s.status = ST_BREAKDOWN; s.phase = PH_DONE;
-  } else if (rr <= s.target2 || s.total_it >= pr.cfg.max_iter || !(rho > 0.0)) {
+  } else if (rr <= s.target2 || s.total_it >= cfg.max_iter || !(rho > 0.0)) {
     s.pend = 1;             // the final step a p is added to x with d
     s.phase = PH_OUTER;
   } else {
-    prof_add(pr, PF_UPDATE_RHS, 1);
-    prof_add(pr, PF_UPDATE_FRESH, s.inner_it == 1);
+    prof_add(prof, PF_UPDATE_RHS, 1);
+    prof_add(prof, PF_UPDATE_FRESH, s.inner_it == 1);
     s.beta = rho / rz;
     s.rho = rho;
     s.has_d = 1;            // the update launch writes d
   }
+}
+
+// Records the fields a step's finalisation reads, as its matvec finds them.
+__device__ inline void open_step(RhsState* st, int r0, int r1) {
+  for (int r = r0 + (int)threadIdx.x; r < r1; r += (int)blockDim.x) {
+    RhsState& s = st[r];
+    s.step_target2 = s.target2;
+    s.step_phase = s.phase;
+    s.step_inner = s.inner_it;
+    s.step_total = s.total_it;
+  }
+}
+
+// What the update needs of a right-hand side's step.
+struct StepRec {
+  double a, beta;
+  int go, first;   // the inner solve goes on; its first step
+};
+
+__device__ __forceinline__ bool step_active(const Prob& pr, int r) {
+  return (pr.fin ? pr.st[r].step_phase : pr.st[r].phase) == PH_INNER;
+}
+
+// The records of right-hand sides [r0, r1), for the whole workgroup: from the
+// finalised states or, with pr.fin, finalised here from the nt tiles'
+// partials (one wavefront per right-hand side in turn, in k_finalize's order);
+// the workgroup with `keep` advances the states.
+__device__ inline void step_records(const Prob& pr, int nt, int r0, int r1, bool keep, StepRec* rec) {
+  const int lane = threadIdx.x % WAVE;
+  for (int rl = threadIdx.x / WAVE; rl < r1 - r0; rl += TILE / WAVE) {
+    const int r = r0 + rl;
+    StepRec e{0.0, 0.0, 0, 0};
+    if (!pr.fin) {
+      const RhsState& s = pr.st[r];
+      e = StepRec{s.a, s.beta, s.phase == PH_INNER, s.inner_it == 1};
+    } else if (pr.st[r].step_phase == PH_INNER) {
+      double v[7];
+      sum_partials<7>(pr.part, pr.R, pr.pstride, nt, r, v);
+      RhsState s;
+      s.phase = PH_INNER;
+      s.target2 = pr.st[r].step_target2;
+      s.inner_it = pr.st[r].step_inner;
+      s.total_it = pr.st[r].step_total;
+      finalize_matvec(pr.cfg, nullptr, s, v);
+      e = StepRec{s.a, s.beta, s.phase == PH_INNER, s.inner_it == 1};
+      if (keep && lane == 0) finalize_matvec(pr.cfg, pr.prof, pr.st[r], v);
+    }
+    if (lane == 0) rec[rl] = e;
+  }
+  __syncthreads();
 }
 
 constexpr int FIN_WAVES = 4;   // right-hand sides finalised per workgroup
@@ -394,16 +444,17 @@ __global__ __launch_bounds__(FIN_WAVES * WAVE) void k_finalize(const Prob* __res
   const int r = (b - pr.fin_begin) * FIN_WAVES + (int)(threadIdx.x / WAVE);
   if (r >= pr.R) return;
   const int want = KIND == 0 ? PH_OUTER : PH_INNER;
+  if (KIND == 1 && pr.fin) return;   // the update finalises
   if (pr.st[r].phase != want) return;
   const int lane = threadIdx.x % WAVE;
   if constexpr (KIND == 0) {
     double v[3];
     sum_partials<3>(pr.part, pr.R, pr.pstride, pr.op.ntiles, r, v);
-    if (lane == 0) finalize_refine(pr, pr.st[r], v);
+    if (lane == 0) finalize_refine(pr.cfg, pr.prof, pr.st[r], v);
   } else {
     double v[7];
     sum_partials<7>(pr.part, pr.R, pr.pstride, pr.mv_mode ? pr.mv_tiles : pr.op.ntiles, r, v);
-    if (lane == 0) finalize_matvec(pr, pr.st[r], v);
+    if (lane == 0) finalize_matvec(pr.cfg, pr.prof, pr.st[r], v);
   }
 }
 
@@ -556,6 +607,7 @@ __global__ __launch_bounds__(TILE, (OccMV<T, K>::v)) void k_matvec(const Prob* _
     const int N = op.N;
     if (w.tile == 0 && w.chunk == 0) prof_launch(pr, PF_MATVEC_ACT, PH_INNER);
     const int r0 = w.r0, r1 = w.r1;
+    if (w.tile == 0 && pr.fin) open_step(pr.st, r0, r1);
     if (!any_in_phase(pr, r0, r1, PH_INNER)) continue;
     unsigned nb[6];
     voxel_offsets<sizeof(T)>(op, w.nn, nb);
@@ -640,6 +692,7 @@ __global__ __launch_bounds__(TILE, (OccMV<T, K>::v)) void k_matvec(const Prob* _
 template <typename T, int PC, int K>
 __global__ __launch_bounds__(TILE, (OccMV<T, K>::v)) void k_update(const Prob* __restrict__ probs, int nprob, int W) {
   constexpr int NP = PSize<PC, K>::n;
+  __shared__ StepRec rec[RCMAX];
   for (Sweep sw = sweep_begin(W); sw.item < sw.end; sw.item += sw.step) {
     const Where w = locate(probs, nprob, sw.item);
     const Prob& pr = probs[w.p];
@@ -647,7 +700,12 @@ __global__ __launch_bounds__(TILE, (OccMV<T, K>::v)) void k_update(const Prob* _
     const int N = op.N;
     if (w.tile == 0 && w.chunk == 0) prof_launch(pr, PF_UPDATE_ACT, PH_INNER);
     const int r0 = w.r0, r1 = w.r1;
-    if (!w.valid || !any_in_phase(pr, r0, r1, PH_INNER)) continue;
+    bool any = false;
+    for (int r = r0; r < r1; ++r) any = any || step_active(pr, r);
+    if (!any) continue;
+    __syncthreads();   // the previous item's records have been read
+    step_records(pr, op.ntiles, r0, r1, w.tile == 0, rec);
+    if (!w.valid) continue;
     const unsigned o = (unsigned)w.n * sizeof(T);
     const Slab<T> Ps(OpT<T>::P(op), NP, N);
     constexpr bool hold = HoldP<T, PC, K>::v;
@@ -655,10 +713,10 @@ __global__ __launch_bounds__(TILE, (OccMV<T, K>::v)) void k_update(const Prob* _
     if constexpr (hold) load_soa(Ps, o, P);
   #pragma unroll 1
     for (int r = r0; r < r1; ++r) {
-      const RhsState& s = pr.st[r];
-      if (s.phase != PH_INNER) continue;
+      const StepRec& s = rec[r - r0];
+      if (!s.go) continue;
       const T a = (T)s.a, beta = (T)s.beta;
-      const bool fresh = s.inner_it == 1;
+      const bool fresh = s.first != 0;
       const size_t off = (size_t)r * K * N;
       const Slab<T> ps((T*)pr.p + off, K, N), qs((const T*)pr.q + off, K, N), ds((T*)pr.d + off, K, N),
           rs((T*)pr.r + off, K, N);

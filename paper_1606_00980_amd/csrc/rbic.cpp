@@ -329,6 +329,8 @@ std::vector<RbGroup> rb_groups(RbProb* h, int n, int rhs_tile, bool outer_chunks
       // for pairs holds that layout too)
       if (P.Rc < 2) P.uw = 1;
       g.uw = std::max(g.uw, P.uw);
+      P.pr.fin = update_finalizes(P.rb.ntB, P.rb.K);
+      g.need_fin = g.need_fin || !P.pr.fin;
       P.wB = g.WB;
       g.WB += P.rb.ntB * P.nch;
       P.wR = g.WR;
@@ -366,7 +368,7 @@ template <typename T>
 int inner_step(gp_ctx* c, hipStream_t q, const RbGroup& g, const RbProb* dp, bool pf) {
   PROFILED_IF(pf, c, GP_KERNEL_RB_RED, launch_rbg_red<T>(q, g.K, dp, g.count, g.WR));
   PROFILED_IF(pf, c, GP_KERNEL_RB_MATVEC, launch_rbg_matvec<T>(q, g.K, dp, g.count, g.WB, g.uw == 2));
-  HIPTRY(launch_rbg_finalize(q, 1, dp, g.count, g.F));
+  if (g.need_fin) HIPTRY(launch_rbg_finalize(q, 1, dp, g.count, g.F));
   PROFILED_IF(pf, c, GP_KERNEL_RB_UPDATE, launch_rbg_update<T>(q, g.K, dp, g.count, g.WB));
   return GP_OK;
 }
@@ -613,7 +615,7 @@ int rb_solve_group(gp_ctx* c, const std::vector<RbOpItems>& ops_in, const gp_opt
                     (f32 ? "f" : "d");
   for (const RbGroup& g : groups)
     key += "|" + std::to_string(g.K) + "," + std::to_string(g.count) + "," + std::to_string(g.WB) + "," +
-           std::to_string(g.WR) + "," + std::to_string(g.WO) + "," + std::to_string(g.F) + "," + std::to_string(g.uw);
+           std::to_string(g.WR) + "," + std::to_string(g.WO) + "," + std::to_string(g.F) + "," + std::to_string(g.uw) + (g.need_fin ? "f" : "");
   auto run_round = [&](int len, uint64_t mask, bool tail, bool first) -> int {
     if (!graphs) return rb_enqueue_round(c, s, f32, groups, c->d_rbp, len, mask, tail, first, true, false);
     return graph_replay(c,

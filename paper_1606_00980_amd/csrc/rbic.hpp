@@ -734,6 +734,7 @@ __global__ __launch_bounds__(TILE) void k_rb_matvec(const RbProb* __restrict__ p
   const RbDev& rb = P.rb;
   const RhsState* st = P.pr.st;
   count_launch(P, w, PH_INNER, PF_MATVEC_ACT);
+  if (w.tile == 0 && P.pr.fin) open_step(P.pr.st, w.r0, w.r1);
   bool any = false;
   for (int r = w.r0; r < w.r1; ++r) any = any || st[r].phase == PH_INNER;
   if (!any) return;
@@ -805,20 +806,22 @@ __global__ __launch_bounds__(TILE) void k_rb_update(const RbProb* __restrict__ p
   const RbWork w = rb_item<RBW_BLACK>(probs, nprob);
   const RbProb& P = probs[w.p];
   const RbDev& rb = P.rb;
-  const RhsState* st = P.pr.st;
   count_launch(P, w, PH_INNER, PF_UPDATE_ACT);
   const int i = w.tile * TILE + threadIdx.x;
   bool any = false;
-  for (int r = w.r0; r < w.r1; ++r) any = any || st[r].phase == PH_INNER;
-  if (!any || i >= rb.NB) return;
+  for (int r = w.r0; r < w.r1; ++r) any = any || step_active(P.pr, r);
+  if (!any) return;
+  __shared__ StepRec rec[RCMAX];
+  step_records(P.pr, rb.ntB, w.r0, w.r1, w.tile == 0, rec);
+  if (i >= rb.NB) return;
   const unsigned oT = (unsigned)i * (unsigned)sizeof(T);
   const Packed<T, K, HOLD> S(RbT<T>::S(rb), rb.NB, oT);
 #pragma unroll 1
   for (int r = w.r0; r < w.r1; ++r) {
-    const RhsState& s = st[r];
-    if (s.phase != PH_INNER) continue;
+    const StepRec& s = rec[r - w.r0];
+    if (!s.go) continue;
     const T a = (T)s.a, beta = (T)s.beta;
-    const bool fresh = s.inner_it == 1;
+    const bool fresh = s.first != 0;
     const size_t off = (size_t)r * K * rb.NB;
     const RbVec<T, K> ds((T*)P.d + off, rb.NB), rs((T*)P.r + off, rb.NB), ps((T*)P.p + off, rb.NB),
         qs((T*)P.q + off, rb.NB);
@@ -941,6 +944,7 @@ __global__ __launch_bounds__(FIN_WAVES * WAVE) void k_rb_finalize(const RbProb* 
   const Prob& pr = P.pr;
   const int r = (b - pr.fin_begin) * FIN_WAVES + (int)(threadIdx.x / WAVE);
   if (r >= pr.R) return;
+  if (KIND == 1 && pr.fin) return;   // the update finalises
   if (pr.st[r].phase != (KIND == 0 ? PH_OUTER : PH_INNER)) return;
   const int lane = threadIdx.x % WAVE;
   const int ntB = P.rb.ntB, ntN = P.rb.ntN;
@@ -949,11 +953,11 @@ __global__ __launch_bounds__(FIN_WAVES * WAVE) void k_rb_finalize(const RbProb* 
     sum_partials<3>(pr.part, pr.R, pr.pstride, ntB, r, v);
     sum_partials<1>(P.bb, 1, ntN, ntN, r, bb);
     v[1] = bb[0];
-    if (lane == 0) finalize_refine(pr, pr.st[r], v);
+    if (lane == 0) finalize_refine(pr.cfg, pr.prof, pr.st[r], v);
   } else {
     double v[7];
     sum_partials<7>(pr.part, pr.R, pr.pstride, ntB, r, v);
-    if (lane == 0) finalize_matvec(pr, pr.st[r], v);
+    if (lane == 0) finalize_matvec(pr.cfg, pr.prof, pr.st[r], v);
   }
 }
 

@@ -176,6 +176,7 @@ void apply_plan(Prob& p, const Plan& pl);
 struct LaunchGroup {
   int K, first, count, W, F, nblk, Wmv, nblk_mv, mv_mode, wpc;
   int Wo, nblk_o;   // refine / addsol work items and workgroups
+  bool need_fin = false;   // some problem's steps take a finalising launch
 };
 // Number of inner vectors (d, r, p, q) per right-hand side in the inner precision.
 constexpr int NVEC = 4;
@@ -304,6 +305,7 @@ struct RbMember {
 struct RbGroup {
   int K, first, count, WB, WR, WO, F;
   int uw;   // 2 when some member stores the red-stage vector in pairs, else 1
+  bool need_fin = false;   // some member's steps take a finalising launch
 };
 // Device bytes of a member's vectors and partials (states excluded).
 size_t rb_member_bytes(const gp_op* op, int R, bool f32);

@@ -95,3 +95,34 @@ def test_small_solves(g, ctx, torch_cuda, pc, nx, ny, K):
         assert sc[0]["status"] == g.GP_ERR_NOT_CONVERGED and sc[0]["inner_iters"] == 2
     g.gp_op_destroy(other)
     g.gp_op_destroy(op)
+
+
+@pytest.mark.parametrize("pc,prec", [("BLOCK_JACOBI", "FP32_REFINE64"), ("JACOBI", "FP64"), ("RB_IC0", "FP32_REFINE64"),
+                                     ("RB_IC0", "FP64")])
+def test_both_finalisations_in_one_batch(g, ctx, torch_cuda, pc, prec):
+    """A K = 1 operator of more tiles than the update launch finalises itself
+    (its steps take the finalising launch) grouped with one of a few tiles:
+    each right-hand side converges and equals its solve alone, bitwise."""
+    torch = torch_cuda
+    kw = dict(tol=1e-8, precond=getattr(g, "GP_PRECOND_" + pc), precision=getattr(g, "GP_PREC_" + prec), rhs_tile=2,
+              zero_guess=1)
+    items, keep = [], []
+    for nx, ny, seed in ((170, 151, 1), (40, 31, 2)):   # 101 and 5 tiles (red-black: 51 and 3 a colour)
+        mask, B, alpha, b = operator(nx, ny, 1, seed)
+        op = g.gp_op_create(ctx, mask, 4, 1)
+        Bd, bd = torch.from_numpy(B).cuda(), torch.from_numpy(b).cuda()
+        g.gp_op_set_blocks(op, Bd)
+        g.gp_op_set_alpha(op, alpha)
+        items.append((op, 3, bd, torch.zeros_like(bd)))
+        keep.append((Bd, orc.precision(orc.grid(mask, 4), alpha, B), b))
+    _, st = g.gp_solve_batch(ctx, items, g.gp_opts_default(**kw))
+    at = 0
+    for (op, R, bd, x), (_, Q, b) in zip(items, keep):
+        alone = torch.zeros_like(bd)
+        _, sa = g.gp_solve(op, R, bd, alone, g.gp_opts_default(**kw))
+        assert torch.equal(alone, x)
+        for r in range(R):
+            res = np.linalg.norm(b[r].ravel() - Q @ x[r].cpu().numpy().ravel()) / np.linalg.norm(b[r])
+            assert res <= 1.01e-8 and st[at + r]["inner_iters"] == sa[r]["inner_iters"]
+        at += R
+        g.gp_op_destroy(op)
