@@ -187,12 +187,11 @@ __global__ __launch_bounds__(TILE) void k_precond(OpDev op, int pc, double* __re
     return;
   }
   // Cholesky M = L L', then M^{-1} = L^{-T} L^{-1}.
-  double inv[NB];
-  const bool ok = spd_inverse_any<K>(a, inv);
+  const bool ok = spd_inverse_any<K>(a);
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    P64[(size_t)i * N + n] = inv[i];
-    P32[(size_t)i * N + n] = (float)inv[i];
+    P64[(size_t)i * N + n] = a[i];
+    P32[(size_t)i * N + n] = (float)a[i];
   }
   if (!ok) atomicMin(bad, n);
 }

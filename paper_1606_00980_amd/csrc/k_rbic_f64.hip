@@ -8,12 +8,12 @@ namespace gp {
 
 hipError_t launch_rb_setup(hipStream_t s, const RbDev& rb, const double* B64, double* P64, float* P32,
                            double* D64, float* D32, double* S64, float* S32, int* bad) {
-  const int gr = (rb.NR + TILE - 1) / TILE, gb = (rb.NB + TILE - 1) / TILE;
+  const int gr = (rb.NR + SETUP_WG - 1) / SETUP_WG, gb = (rb.NB + SETUP_WG - 1) / SETUP_WG;
 #define X(KK)                                                                                         \
   case KK:                                                                                            \
-    if (gr > 0) GP_LAUNCH(k_rb_setup_red<KK>, dim3(gr), dim3(TILE), 0, s, rb, B64, P64, P32, bad); \
+    if (gr > 0) GP_LAUNCH(k_rb_setup_red<KK>, dim3(gr), dim3(SETUP_WG), 0, s, rb, B64, P64, P32, bad); \
     if (gb > 0)                                                                                       \
-      GP_LAUNCH(k_rb_setup_black<KK>, dim3(gb), dim3(TILE), 0, s, rb, B64, D64, D32, S64, S32, bad); \
+      GP_LAUNCH(k_rb_setup_black<KK>, dim3(gb), dim3(SETUP_WG), 0, s, rb, B64, D64, D32, S64, S32, bad); \
     break;
   RB_K_SWITCH(rb.K, X)
 #undef X

@@ -342,25 +342,29 @@ __device__ __forceinline__ void load_nb(const int* tab, int n, int i, int (&nb)[
 
 // ------------------------------------------------------------------ set-up
 // Red voxels: the packed inverse of Q_nn = B_n + diag(alpha) deg_n.
+// One wavefront per workgroup: the block's registers leave one or two
+// wavefronts a SIMD at large K, so whole tiles would leave compute units idle.
+constexpr int SETUP_WG = 64;
+
 template <int K>
-__global__ __launch_bounds__(TILE) void k_rb_setup_red(RbDev rb, const double* __restrict__ B64,
+__global__ __launch_bounds__(SETUP_WG) void k_rb_setup_red(RbDev rb, const double* __restrict__ B64,
                                                        double* __restrict__ P64, float* __restrict__ P32,
                                                        int* __restrict__ bad) {
   constexpr int NB = Tri<K>::NB;
-  const int j = blockIdx.x * TILE + threadIdx.x;
+  const int j = blockIdx.x * SETUP_WG + threadIdx.x;
   if (j >= rb.NR) return;
   const int n = rb.red[j];
   int deg = 0;
   for (int d = 0; d < 6; ++d) deg += rb.nbR[(size_t)d * rb.NR + j] >= 0;
-  double a[NB], inv[NB];
+  double a[NB];
   load_soa(B64, rb.N, n, a);
 #pragma unroll
   for (int k = 0; k < K; ++k) a[pk(k, k)] += rb.alpha64[k] * (double)deg;
-  const bool ok = spd_inverse_any<K>(a, inv);
+  const bool ok = spd_inverse_any<K>(a);
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    P64[(size_t)i * rb.NR + j] = inv[i];
-    P32[(size_t)i * rb.NR + j] = (float)inv[i];
+    P64[(size_t)i * rb.NR + j] = a[i];
+    P32[(size_t)i * rb.NR + j] = (float)a[i];
   }
   if (!ok) atomicMin(bad, n);
 }
@@ -369,12 +373,12 @@ __global__ __launch_bounds__(TILE) void k_rb_setup_red(RbDev rb, const double* _
 // S_m = Q_mm - sum_{n ~ m} diag(alpha) Q_nn^{-1} diag(alpha) (reads the red
 // inverses written by k_rb_setup_red).
 template <int K>
-__global__ __launch_bounds__(TILE) void k_rb_setup_black(RbDev rb, const double* __restrict__ B64,
+__global__ __launch_bounds__(SETUP_WG) void k_rb_setup_black(RbDev rb, const double* __restrict__ B64,
                                                          double* __restrict__ D64, float* __restrict__ D32,
                                                          double* __restrict__ S64, float* __restrict__ S32,
                                                          int* __restrict__ bad) {
   constexpr int NB = Tri<K>::NB;
-  const int i = blockIdx.x * TILE + threadIdx.x;
+  const int i = blockIdx.x * SETUP_WG + threadIdx.x;
   if (i >= rb.NB) return;
   const int m = rb.blk[i];
   int nb[6];
@@ -382,7 +386,7 @@ __global__ __launch_bounds__(TILE) void k_rb_setup_black(RbDev rb, const double*
   int deg = 0;
 #pragma unroll
   for (int d = 0; d < 6; ++d) deg += nb[d] >= 0;
-  double a[NB], inv[NB];
+  double a[NB];
   load_soa(B64, rb.N, m, a);
 #pragma unroll
   for (int k = 0; k < K; ++k) a[pk(k, k)] += rb.alpha64[k] * (double)deg;
@@ -391,21 +395,42 @@ __global__ __launch_bounds__(TILE) void k_rb_setup_black(RbDev rb, const double*
     D64[(size_t)e * rb.NB + i] = a[e];
     D32[(size_t)e * rb.NB + i] = (float)a[e];
   }
+  // A row of the block at a time, the entries of the row in chunks of SE: the
+  // gathers of a chunk's six neighbours are in flight together (a missing
+  // neighbour reads entry 0 and is dropped by a select).  Neighbour by
+  // neighbour behind a branch, with one neighbour's gathers in flight: 176 us
+  // at K = 15, N = 52,740 (52 so), 17 at K = 6 (12), 203 at K = 10,
+  // N = 289,592 (100).
+  const Slab<double> Ps(rb.P64, NB, rb.NR);
+  constexpr int SE = K <= 11 ? 8 : 4;
 #pragma unroll
-  for (int d = 0; d < 6; ++d) {
-    if (nb[d] < 0) continue;
+  for (int k = 0; k < K; ++k) {
+    const double ak = rb.alpha64[k];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
+    for (int j0 = 0; j0 <= k; j0 += SE) {
+      double v[SE][6];
 #pragma unroll
-      for (int l = 0; l <= k; ++l)
-        a[pk(k, l)] -= rb.alpha64[k] * rb.alpha64[l] * rb.P64[(size_t)pk(k, l) * rb.NR + nb[d]];
+      for (int c = 0; c < SE; ++c)
+#pragma unroll
+        for (int d = 0; d < 6; ++d)
+          if (j0 + c <= k) v[c][d] = Ps.ld(pk(k, j0 + c), nb[d] < 0 ? 0u : (unsigned)nb[d] * 8u);
+#pragma unroll
+      for (int c = 0; c < SE; ++c) {
+        if (j0 + c <= k) {
+          double s = 0.0;
+#pragma unroll
+          for (int d = 0; d < 6; ++d) s += nb[d] < 0 ? 0.0 : v[c][d];
+          a[pk(k, j0 + c)] -= ak * rb.alpha64[j0 + c] * s;
+        }
+      }
+      if constexpr (K > 11) __builtin_amdgcn_sched_barrier(0);
     }
   }
-  const bool ok = spd_inverse_any<K>(a, inv);
+  const bool ok = spd_inverse_any<K>(a);
 #pragma unroll
   for (int e = 0; e < NB; ++e) {
-    S64[(size_t)e * rb.NB + i] = inv[e];
-    S32[(size_t)e * rb.NB + i] = (float)inv[e];
+    S64[(size_t)e * rb.NB + i] = a[e];
+    S32[(size_t)e * rb.NB + i] = (float)a[e];
   }
   if (!ok) atomicMin(bad, m);
 }
