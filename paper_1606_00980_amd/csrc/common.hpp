@@ -118,7 +118,8 @@ struct RbDev {
   const float* P32;
   long long* prof;       // [NPROF] work counters while profiling, else null
   int NB, NR, ntB, ntR, N, K;
-  int ntN;               // tiles of 256 voxels over all N (split, recovery, ||b||^2 partials)
+  int ntN;               // tiles of 256 voxels over all N (recovery)
+  int ntS;               // ||b||^2 partials of the split: red tiles, then black ones
   int tbB, tbR;          // tiles per block of the work order (black, red)
   int zero_start;        // the start value is zero: x is not read
   double alpha64[KMAX];
@@ -132,7 +133,7 @@ struct RbDev {
 struct RbProb {
   RbDev rb;
   Prob pr;               // st, part, R, pstride, cfg, prof, fin_begin (the finalisers' view)
-  const double* bb;      // [R][ntN] ||b||^2 partials of the split
+  const double* bb;      // [R][ntS] ||b||^2 partials of the split
   const double* c64;     // [R][K][NB] black right-hand side of the Schur system
   double* xB;            // [R][K][NB] black solution (FP64)
   double* u64;           // [R][K][NR] red stage of the FP64 refinement

@@ -26,27 +26,27 @@ hipError_t launch_rb_split(hipStream_t s, const RbDev& rb, int R, const double* 
                            first.pstride, first.r0};
   const RbFirst<double> f64{first.f32 ? nullptr : (double*)first.r, (double*)first.p, first.part, first.vstride,
                             first.pstride, first.r0};
-  // right-hand sides per workgroup of the voxel pass (the red inverse held
+  // right-hand sides per workgroup of the red pass (the red inverse held
   // across them): the largest of 4, 2, 1 that leaves 1024 workgroups; the
   // black pass (its time is in the gathers of t) takes one
-  int rcv = 1;
+  int rcr = 1;
   for (int cand : {4, 2})
-    if ((long)rb.ntN * ((R + cand - 1) / cand) >= 1024) {
-      rcv = cand;
+    if ((long)rb.ntR * ((R + cand - 1) / cand) >= 1024) {
+      rcr = cand;
       break;
     }
-  const int rcb = 1;
-  const int nchv = (R + rcv - 1) / rcv, nchb = (R + rcb - 1) / rcb;
-#define X(KK)                                                                                              \
-  case KK:                                                                                                 \
-    GP_LAUNCH(k_rb_split_voxels<KK>, grid2(rb.ntN, nchv), dim3(TILE), 0, s, rb, R, rcv, b, x, zero_guess, t, c, \
-                       xB, bbpart);                                                                        \
-    if (rb.ntB > 0) {                                                                                      \
-      if (first.f32)                                                                                       \
-        GP_LAUNCH((k_rb_split_black<KK, float>), grid2(rb.ntB, nchb), dim3(TILE), 0, s, rb, R, rcb, t, c, f32); \
-      else                                                                                                 \
-        GP_LAUNCH((k_rb_split_black<KK, double>), grid2(rb.ntB, nchb), dim3(TILE), 0, s, rb, R, rcb, t, c, f64); \
-    }                                                                                                      \
+  const int wr = rb.ntR * ((R + rcr - 1) / rcr), wb = rb.ntB * R;
+#define X(KK)                                                                                                \
+  case KK:                                                                                                   \
+    if (wr > 0) GP_LAUNCH(k_rb_split_red<KK>, dim3(wr), dim3(TILE), 0, s, rb, R, rcr, b, t, bbpart);         \
+    if (wb > 0) {                                                                                            \
+      if (first.f32)                                                                                         \
+        GP_LAUNCH((k_rb_split_black<KK, float>), dim3(wb), dim3(TILE), 0, s, rb, R, 1, b, x, zero_guess, t, c, xB, \
+                  bbpart, f32);                                                                              \
+      else                                                                                                   \
+        GP_LAUNCH((k_rb_split_black<KK, double>), dim3(wb), dim3(TILE), 0, s, rb, R, 1, b, x, zero_guess, t, c, xB, \
+                  bbpart, f64);                                                                              \
+    }                                                                                                        \
     break;
   RB_K_SWITCH(rb.K, X)
 #undef X

@@ -143,6 +143,7 @@ RbDev rb_dev(const gp_op* op) {
   v.ntB = d.ntB;
   v.ntR = d.ntR;
   v.ntN = d.ntN;
+  v.ntS = d.ntR + d.ntB;
   v.N = op->N;
   v.K = op->K;
   // Work items run block by block: within a block of tiles, every chunk of
@@ -249,7 +250,7 @@ size_t rb_member_bytes(const gp_op* op, int R, bool f32) {
   const int pstride = std::max(d.ntB, 1);
   size_t b = 0;
   b += slot_bytes((size_t)NPART * R * pstride * 8);       // partials
-  b += slot_bytes((size_t)R * std::max(d.ntN, 1) * 8);    // ||b||^2 partials
+  b += slot_bytes((size_t)R * (d.ntR + d.ntB) * 8);    // ||b||^2 partials
   b += 2 * slot_bytes(nbv * 8);                           // c64, xB
   b += 2 * slot_bytes(nrv * 8);                           // u64, t64
   b += 4 * slot_bytes(nbv * tsz);                         // d, r, p, q
@@ -273,7 +274,7 @@ void rb_member(gp_op* op, int R, bool f32, char* mem, RhsState* st, const SolveC
   std::memset(&P, 0, sizeof(P));
   P.rb = rb_dev(op);
   P.pr.part = (double*)take((size_t)NPART * R * pstride * 8);
-  P.bb = (double*)take((size_t)R * std::max(d.ntN, 1) * 8);
+  P.bb = (double*)take((size_t)R * (d.ntR + d.ntB) * 8);
   P.c64 = (double*)take(nbv * 8);
   P.xB = (double*)take(nbv * 8);
   P.u64 = (double*)take(nrv * 8);
@@ -474,7 +475,7 @@ int rb_split_member(gp_ctx* c, hipStream_t s, const RbMember& m, int r0, int R, 
     PROFILED_IF(profiled && c->prof_on, c, GP_KERNEL_RB_EDGE,
                 launch_rb_split(s, P.rb, R, b, x, zero_guess ? 1 : 0, m.t64 + (size_t)r0 * K * NR,
                                 (double*)P.c64 + (size_t)r0 * K * NB, P.xB + (size_t)r0 * K * NB,
-                                (double*)P.bb + (size_t)r0 * P.rb.ntN, first));
+                                (double*)P.bb + (size_t)r0 * P.rb.ntS, first));
   return GP_OK;
 }
 
@@ -519,8 +520,8 @@ void rb_account(gp_ctx* c, const RbMember& m, size_t tsz, bool zero_guess, const
   const double ad = (double)pf[PF_ADDSOL_D], ap = (double)pf[PF_ADDSOL_P], af = (double)pf[PF_ADDSOL_FRESH];
   const double an = std::max(std::max(ad, ap), af);
   prof_add(c, GP_KERNEL_RB_ADDSOL, an * NB, an * K * NB * 16 - af * K * NB * 8 + (ad + ap) * K * NB * ts);
-  // split: b read, t written and read, x read and x_B written (unless the start
-  // value is zero), c written, the red inverses read, and from a zero start
+  // split: b read, t written and read, x_B's half of x read and x_B written (unless
+  // the start value is zero), c written, the red inverses read, and from a zero start
   // value r and p of the first refinement written; recovery: x_B, t and u
   // read, x written
   prof_add(c, GP_KERNEL_RB_EDGE, 2.0 * R * N,

@@ -87,6 +87,11 @@ struct ItemSums {
     mask |= 1u << rl;
   }
   __device__ void flush(double* part, size_t vstride, int r0, int nr, int pstride, int tile) {
+    flush_to(nr, [&](int i, int rl) { return part + (size_t)i * vstride + (size_t)(r0 + rl) * pstride + tile; });
+  }
+  // value i of right-hand side r0 + rl to *at(i, rl)
+  template <typename F>
+  __device__ void flush_to(int nr, const F& at) {
     __syncthreads();
     for (int t = threadIdx.x; t < nr * NV; t += TILE) {
       const int rl = t / NV, i = t % NV;
@@ -94,7 +99,7 @@ struct ItemSums {
       double s = 0.0;
 #pragma unroll
       for (int w = 0; w < TILE / WAVE; ++w) s += sh[rl][i][w];
-      part[(size_t)i * vstride + (size_t)(r0 + rl) * pstride + tile] = s;
+      *at(i, rl) = s;
     }
   }
 };
@@ -436,96 +441,99 @@ __global__ __launch_bounds__(SETUP_WG) void k_rb_setup_black(RbDev rb, const dou
 }
 
 // ------------------------------------------------------------------ solve
-// Split, in voxel order (reads of b and x coalesced): red voxels t = Q_nn^{-1}
-// b_n, black voxels c = b_m and x_B = x_m (x_B not written for a zero start
-// value); the per-tile partials of ||b||^2 into bbpart[r][tile].
-template <int K>
-__global__ __launch_bounds__(TILE) void k_rb_split_voxels(RbDev rb, int R, int rc, const double* __restrict__ b,
-                                                          const double* __restrict__ x, int zero_guess,
-                                                          double* __restrict__ t, double* __restrict__ c,
-                                                          double* __restrict__ xB, double* __restrict__ bbpart) {
-  const int n = blockIdx.x * TILE + threadIdx.x;
-  const int r0 = blockIdx.y * rc, r1 = min(R, r0 + rc);
-  const bool valid = n < rb.N;
-  const int nn = valid ? n : rb.N - 1;   // lanes past the end compute on the last voxel and store nothing
-  const unsigned on = (unsigned)nn * 8u;
-  const int vp = rb.vpos[nn], pos = vp >> 1;
-  const bool red = (vp & 1) == 0;
-  const unsigned op = (unsigned)pos * 8u;
-  // the red inverse, held across the work item's right-hand sides (black
-  // lanes hold red block 0 and do not use it)
-  const Packed<double, K, HoldRb<double, K, 1>::v> P(rb.P64, rb.NR, red ? op : 0u);
-  ItemSums<1> sums;
-#pragma unroll 1
-  for (int r = r0; r < r1; ++r) {
-    const size_t ur = (size_t)r * K * rb.N;
-    const Slab<double> bs(b + ur, K, rb.N);
-    double acc[1] = {0.0}, bv[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      bv[k] = bs.ld(k, on);
-      acc[0] += bv[k] * bv[k];
-    }
-    if (!valid) acc[0] = 0.0;
-    if (red) {
-      double tv[K];
-#pragma unroll
-      for (int k = 0; k < K; ++k) tv[k] = 0.0;
-      sym_apply<K>(P, bv, tv);
-      if (valid) {
-        const Slab<double> ts(t + (size_t)r * K * rb.NR, K, rb.NR);
-#pragma unroll
-        for (int k = 0; k < K; ++k) ts.st(k, op, tv[k]);
-      }
-    } else if (valid) {
-      const Slab<double> cs(c + (size_t)r * K * rb.NB, K, rb.NB);
-#pragma unroll
-      for (int k = 0; k < K; ++k) cs.st(k, op, bv[k]);
-      if (!zero_guess) {   // from a zero start value x_B is first written by x_B = d (+ a p)
-        const Slab<double> xu(x + ur, K, rb.N), xs(xB + (size_t)r * K * rb.NB, K, rb.NB);
-        double xv[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) xv[k] = xu.ld(k, on);
-#pragma unroll
-        for (int k = 0; k < K; ++k) xs.st(k, op, xv[k]);
-      }
-    }
-    sums.add(r - r0, acc);
-  }
-  sums.flush(bbpart, 0, r0, r1 - r0, rb.ntN, blockIdx.x);
+// Split of b and x, each colour in its own order, so that every lane works on
+// a block of its colour and c is formed at once; a line of b holds both
+// colours and is fetched twice, the second time mostly from a cache.  Items
+// run tile by tile within a chunk of right-hand sides and go to the XCDs in
+// contiguous ranges (z-neighbours then share an L2).  In voxel order half of
+// the lanes idled through the red blocks and c was written, read and written
+// again: 2283 us for 64 right-hand sides at K = 10, N = 289,592 (1850 so), 99
+// for five at K = 15, N = 52,740 (66), 82 for 32 at K = 6 (81).
+struct SplitItem {
+  int tile, r0, r1;
+};
+__device__ __forceinline__ SplitItem split_item(int nt, int R, int rc) {
+  const int wi = xcd_remap(blockIdx.x, gridDim.x);
+  const int chunk = wi / nt, r0 = chunk * rc;
+  return {wi - chunk * nt, r0, min(R, r0 + rc)};
 }
 
-// Black voxels: c += alpha .* sum_{n ~ m} t_n, which makes
-// c = b_B - E' D_R^{-1} b_R.
+// Red voxels: t = Q_nn^{-1} b_n; ||b||^2 partials bbpart[r][tile] of the red tiles.
+template <int K>
+__global__ __launch_bounds__(TILE) void k_rb_split_red(RbDev rb, int R, int rc, const double* __restrict__ b,
+                                                       double* __restrict__ t, double* __restrict__ bbpart) {
+  const SplitItem w = split_item(rb.ntR, R, rc);
+  const int j = w.tile * TILE + threadIdx.x;
+  const bool valid = j < rb.NR;
+  const int jj = valid ? j : rb.NR - 1;   // lanes past the end compute on the last voxel and store nothing
+  const unsigned on = (unsigned)rb.red[jj] * 8u, oj = (unsigned)jj * 8u;
+  // the red inverse, held across the work item's right-hand sides
+  const Packed<double, K, HoldRb<double, K, 1>::v> P(rb.P64, rb.NR, oj);
+  ItemSums<1> sums;
+#pragma unroll 1
+  for (int r = w.r0; r < w.r1; ++r) {
+    const Slab<double> bs(b + (size_t)r * K * rb.N, K, rb.N);
+    double acc[1] = {0.0}, bv[K], tv[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) bv[k] = bs.ld(k, on);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      acc[0] += bv[k] * bv[k];
+      tv[k] = 0.0;
+    }
+    if (!valid) acc[0] = 0.0;
+    sym_apply<K>(P, bv, tv);
+    if (valid) RbVec<double, K>(t + (size_t)r * K * rb.NR, rb.NR).store(j, tv);
+    sums.add(r - w.r0, acc);
+  }
+  sums.flush(bbpart, 0, w.r0, w.r1 - w.r0, rb.ntS, w.tile);
+}
+
+// Black voxels: c = b_m + alpha .* sum_{n ~ m} t_n (c = b_B - E' D_R^{-1} b_R),
+// x_B = x_m (not from a zero start value: x_B is then first written by x_B = d
+// (+ a p)) and, from a zero start value, the first refinement; ||b||^2
+// partials bbpart[r][ntR + tile].
 template <int K, typename T>
-__global__ __launch_bounds__(TILE) void k_rb_split_black(RbDev rb, int R, int rc, const double* __restrict__ t,
-                                                         double* __restrict__ c, RbFirst<T> first) {
-  const int i = blockIdx.x * TILE + threadIdx.x;
-  const int r0 = blockIdx.y * rc, r1 = min(R, r0 + rc);
+__global__ __launch_bounds__(TILE) void k_rb_split_black(RbDev rb, int R, int rc, const double* __restrict__ b,
+                                                         const double* __restrict__ x, int zero_guess,
+                                                         const double* __restrict__ t, double* __restrict__ c,
+                                                         double* __restrict__ xB, double* __restrict__ bbpart,
+                                                         RbFirst<T> first) {
+  const SplitItem w = split_item(rb.ntB, R, rc);
+  const int i = w.tile * TILE + threadIdx.x;
   const bool valid = i < rb.NB;
   const int ii = valid ? i : 0;   // lanes past the end compute on voxel 0 and store nothing
   int nb[6];
   load_nb(rb.nbB, rb.NB, ii, nb);
-  const unsigned oi = (unsigned)ii * 8u, oT = (unsigned)ii * (unsigned)sizeof(T);
+  const unsigned om = (unsigned)rb.blk[ii] * 8u, oi = (unsigned)ii * 8u, oT = (unsigned)ii * (unsigned)sizeof(T);
   // the Schur inverse for the first refinement, held across the work item
   const Packed<T, K, HoldRb<T, K, 1>::v> S(RbT<T>::S(rb), rb.NB, oT);
-  ItemSums<3> sums;
+  ItemSums<4> sums;
 #pragma unroll 1
-  for (int r = r0; r < r1; ++r) {
-    const Slab<double> ts(t + (size_t)r * K * rb.NR, K, rb.NR), cs(c + (size_t)r * K * rb.NB, K, rb.NB);
-    double s[K], cv[K];
+  for (int r = w.r0; r < w.r1; ++r) {
+    const Slab<double> bs(b + (size_t)r * K * rb.N, K, rb.N), ts(t + (size_t)r * K * rb.NR, K, rb.NR),
+        cs(c + (size_t)r * K * rb.NB, K, rb.NB);
+    double acc[4] = {0.0, 0.0, 0.0, 0.0}, s[K], cv[K], xv[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) cv[k] = cs.ld(k, oi);
+    for (int k = 0; k < K; ++k) cv[k] = bs.ld(k, om);
+    if (!zero_guess) {
+      const Slab<double> xu(x + (size_t)r * K * rb.N, K, rb.N);
+#pragma unroll
+      for (int k = 0; k < K; ++k) xv[k] = xu.ld(k, om);
+    }
     neighbour_sum<double, K>(nb, ts, s);
 #pragma unroll
-    for (int k = 0; k < K; ++k) cv[k] += rb.alpha64[k] * s[k];
+    for (int k = 0; k < K; ++k) {
+      acc[3] += cv[k] * cv[k];
+      cv[k] += rb.alpha64[k] * s[k];
+    }
     if (valid) {
 #pragma unroll
       for (int k = 0; k < K; ++k) cs.st(k, oi, cv[k]);
+      if (!zero_guess) RbVec<double, K>(xB + (size_t)r * K * rb.NB, rb.NB).store(ii, xv);
     }
     if (first.r) {
       // the first refinement from x_B = 0: its residual is c itself
-      double acc[3] = {0.0, 0.0, 0.0};
       T rt[K], zt[K];
 #pragma unroll
       for (int k = 0; k < K; ++k) {
@@ -539,13 +547,15 @@ __global__ __launch_bounds__(TILE) void k_rb_split_black(RbDev rb, int R, int rc
       if (valid) {
         RbVec<T, K>(first.r + (size_t)r * K * rb.NB, rb.NB).store(ii, rt);
         RbVec<T, K>(first.p + (size_t)r * K * rb.NB, rb.NB).store(ii, zt);
-      } else {
-        acc[0] = acc[2] = 0.0;
       }
-      sums.add(r - r0, acc);
     }
+    if (!valid) acc[0] = acc[2] = acc[3] = 0.0;
+    sums.add(r - w.r0, acc);
   }
-  if (first.r) sums.flush(first.part, first.vstride, first.r0 + r0, r1 - r0, first.pstride, blockIdx.x);
+  sums.flush_to(w.r1 - w.r0, [&](int v, int rl) {
+    if (v == 3 || !first.r) return bbpart + (size_t)(w.r0 + rl) * rb.ntS + rb.ntR + w.tile;
+    return first.part + (size_t)v * first.vstride + (size_t)(first.r0 + w.r0 + rl) * first.pstride + w.tile;
+  });
 }
 
 // Right-hand side r takes part in the red stage of phase `want` (nothing to do
@@ -959,7 +969,7 @@ __global__ __launch_bounds__(TILE) void k_rb_recover(RbDev rb, const RhsState* _
 // One wavefront per right-hand side of a member: reduce its black tiles'
 // partials in a fixed order and advance the state with the main solver's
 // rules.  For the refinement the ||b||^2 slot comes from the split partials
-// (ntN voxel tiles).
+// (the red tiles, then the black ones).
 template <int KIND>
 __global__ __launch_bounds__(FIN_WAVES * WAVE) void k_rb_finalize(const RbProb* __restrict__ probs, int nprob) {
   const int b = blockIdx.x;
@@ -972,11 +982,11 @@ __global__ __launch_bounds__(FIN_WAVES * WAVE) void k_rb_finalize(const RbProb* 
   if (KIND == 1 && pr.fin) return;   // the update finalises
   if (pr.st[r].phase != (KIND == 0 ? PH_OUTER : PH_INNER)) return;
   const int lane = threadIdx.x % WAVE;
-  const int ntB = P.rb.ntB, ntN = P.rb.ntN;
+  const int ntB = P.rb.ntB, ntS = P.rb.ntS;
   if constexpr (KIND == 0) {
     double v[3], bb[1];
     sum_partials<3>(pr.part, pr.R, pr.pstride, ntB, r, v);
-    sum_partials<1>(P.bb, 1, ntN, ntN, r, bb);
+    sum_partials<1>(P.bb, 1, ntS, ntS, r, bb);
     v[1] = bb[0];
     if (lane == 0) finalize_refine(pr.cfg, pr.prof, pr.st[r], v);
   } else {
