@@ -23,6 +23,7 @@
 
 #include "common.hpp"
 #include "launch.hpp"
+#include "pcg.hpp"
 #include "spd.hpp"
 
 namespace gp {
@@ -581,32 +582,45 @@ __global__ __launch_bounds__(DT) void k_data_assemble_ar(int K, int P, int N, in
 
 // Per (sample r, regressor k, tile): sum over the tile's voxels of the squared
 // differences to the in-mask +x, +y, +z neighbours (one term per adjacent
-// pair, so the total is W_k D_w W_k').  Fixed-order workgroup reduction.
+// pair, so the total is W_k D_w W_k').  A workgroup takes QK regressors of one
+// sample (blockIdx.y), whose lanes share the neighbour indices; fixed-order
+// workgroup reduction.  One regressor per workgroup, the indices read for each:
+// 25 us for five samples at K = 15, N = 52,740 (15 so).
+constexpr int QK = 4;
+
 __global__ __launch_bounds__(DT) void k_quadform_partials(OpDev op, const double* __restrict__ W,
                                                           double* __restrict__ part) {
-  __shared__ double s_red[DT / 64];
-  const int N = op.N;
-  const int tile = blockIdx.x, rk = blockIdx.y;
+  __shared__ double s_red[QK * (DT / 64)];
+  const int N = op.N, K = op.K, nk = (K + QK - 1) / QK;
+  const int tile = blockIdx.x, r = blockIdx.y / nk, k0 = (int)blockIdx.y % nk * QK;
   const int n = tile * DT + threadIdx.x;
-  double v = 0.0;
-  if (n < N) {
-    const double* w = W + (size_t)rk * N;
-    const double c = w[n];
-    for (int d = 0; d < op.dirs; ++d) {
-      const int m = op.nbr[(size_t)(2 * d + 1) * N + n];
-      if (m != n) {
-        const double e = c - w[m];
-        v += e * e;
+  const bool valid = n < N;
+  const int nn = valid ? n : N - 1;
+  const double* w = W + ((size_t)r * K + k0) * N;
+  int m[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) m[d] = d < op.dirs ? op.nbr[(size_t)(2 * d + 1) * N + nn] : nn;
+  double v[QK];
+#pragma unroll
+  for (int c = 0; c < QK; ++c) {
+    v[c] = 0.0;
+    if (k0 + c < K) {
+      const double* wk = w + (size_t)c * N;
+      const double x = wk[nn];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {   // an absent neighbour is the voxel itself
+        const double e = x - wk[m[d]];
+        v[c] += m[d] != nn ? e * e : 0.0;
       }
     }
+    if (!valid) v[c] = 0.0;
   }
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  if ((threadIdx.x & 63) == 0) s_red[threadIdx.x / 64] = v;
+  wave_deposit<QK>(s_red, 0, v);
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < QK && k0 + (int)threadIdx.x < K) {
     double t = 0.0;
-    for (int i = 0; i < DT / 64; ++i) t += s_red[i];
-    part[(size_t)rk * gridDim.x + tile] = t;
+    for (int i = 0; i < DT / 64; ++i) t += s_red[threadIdx.x * (DT / 64) + i];
+    part[((size_t)r * K + k0 + threadIdx.x) * gridDim.x + tile] = t;
   }
 }
 
@@ -675,7 +689,7 @@ int quadform_tiles(int N) { return (N + DT - 1) / DT; }
 
 hipError_t launch_quadform(hipStream_t s, const OpDev& op, int R, const double* W, double* part, double* out) {
   const int nt = quadform_tiles(op.N), nrk = R * op.K;
-  GP_LAUNCH(k_quadform_partials, dim3(nt, nrk), dim3(DT), 0, s, op, W, part);
+  GP_LAUNCH(k_quadform_partials, dim3(nt, R * ((op.K + QK - 1) / QK)), dim3(DT), 0, s, op, W, part);
   if (hipError_t e = hipGetLastError()) return e;
   GP_LAUNCH(k_quadform_final, dim3(nrk), dim3(64), 0, s, nrk, nt, part, out);
   return hipGetLastError();
