@@ -236,7 +236,6 @@ __global__ __launch_bounds__(TILE) void k_perturb(OpDev op, const double* __rest
                                                   const double* __restrict__ z1,
                                                   const double* __restrict__ z2,
                                                   double* __restrict__ b, int R, int tb) {
-  constexpr int NB = Tri<K>::NB;
   const int N = op.N, dirs = op.dirs;
   // items (right-hand side, tile) by blocks of tb tiles: every right-hand
   // side sweeps a block's tiles before the next one starts, and the items go
@@ -255,41 +254,56 @@ __global__ __launch_bounds__(TILE) void k_perturb(OpDev op, const double* __rest
   int nb[6];
 #pragma unroll
   for (int d = 0; d < 6; ++d) nb[d] = op.nbr[(size_t)d * N + n];
-  double L[NB];
-  load_soa(op.L64, N, n, L);
   double zz[K];
 #pragma unroll
   for (int j = 0; j < K; ++j) zz[j] = z2[((size_t)r * K + j) * N + n];
-  // every z1 load issued unconditionally before any use (a missing neighbour
-  // is the voxel itself, so each address is valid; its term is dropped by a
-  // select), so the loads of all regressors and directions are in flight together
-  double hv[K][3], lv[K][3];
+  // KG regressors at a time, all of them up to K = 9: their factor rows and z1
+  // entries are loaded together before any use (a missing neighbour is the
+  // voxel itself, so each address is valid; its term is dropped by a select).
+  // From K = 10 on the loads of all take the registers of most wavefronts of a
+  // SIMD (K = 15, five right-hand sides: 100 us, by groups 72; K = 10 127 and
+  // 113); at K = 9 the one group is faster (86 against 91).
+  constexpr int NG = K <= 9 ? 1 : (K + 5) / 6, KG = (K + NG - 1) / NG;
+  double Lh[NG == 1 ? Tri<K>::NB : 1];
+  if constexpr (NG == 1) load_soa(op.L64, N, n, Lh);
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const double* zk = z1 + ((size_t)r * K + k) * dirs * N;
+  for (int g = 0; g < NG; ++g) {
+    if (g > 0) __builtin_amdgcn_sched_barrier(0);
+    const int k0 = g * KG;
+    double hv[KG][3], lv[KG][3], L[NG > 1 ? KG : 1][K], bwv[KG];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const int dd = d < dirs ? d : 0;
-      hv[k][d] = zk[(size_t)dd * N + n];
-      lv[k][d] = zk[(size_t)dd * N + nb[2 * dd]];
+    for (int c = 0; c < KG; ++c) {
+      const int k = k0 + c;
+      if (k < K) {
+        const double* zk = z1 + ((size_t)r * K + k) * dirs * N;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          const int dd = d < dirs ? d : 0;
+          hv[c][d] = zk[(size_t)dd * N + n];
+          lv[c][d] = zk[(size_t)dd * N + nb[2 * dd]];
+        }
+        if constexpr (NG > 1) {
+#pragma unroll
+          for (int j = 0; j <= k; ++j) L[c][j] = op.L64[(size_t)pk(k, j) * N + n];
+          bwv[c] = bw[(size_t)k * N + n];
+        }
+      }
     }
-  }
-  double pr[K];
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    pr[k] = 0.0;
+    for (int c = 0; c < KG; ++c) {
+      const int k = k0 + c;
+      if (k < K) {
+        double pr = 0.0, dt = 0.0;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      pr[k] += d < dirs && nb[2 * d + 1] != n ? hv[k][d] : 0.0;
-      pr[k] -= d < dirs && nb[2 * d] != n ? lv[k][d] : 0.0;
+        for (int d = 0; d < 3; ++d) {
+          pr += d < dirs && nb[2 * d + 1] != n ? hv[c][d] : 0.0;
+          pr -= d < dirs && nb[2 * d] != n ? lv[c][d] : 0.0;
+        }
+#pragma unroll
+        for (int j = 0; j <= k; ++j) dt += (NG == 1 ? Lh[NG == 1 ? pk(k, j) : 0] : L[NG > 1 ? c : 0][j]) * zz[j];
+        b[((size_t)r * K + k) * N + n] = (NG > 1 ? bwv[c] : bw[(size_t)k * N + n]) + sqrt(op.alpha64[k]) * pr + dt;
+      }
     }
-  }
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    double dt = 0.0;
-#pragma unroll
-    for (int j = 0; j <= k; ++j) dt += L[pk(k, j)] * zz[j];
-    b[((size_t)r * K + k) * N + n] = bw[(size_t)k * N + n] + sqrt(op.alpha64[k]) * pr[k] + dt;
   }
 }
 
