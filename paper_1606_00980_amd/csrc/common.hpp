@@ -20,6 +20,8 @@ enum ProfSlot : int {
 };
 constexpr int RCMAX = 16;    // right-hand sides per workgroup, upper bound
 constexpr int UPAIR_KMAX = 10;   // FP32 red-stage vectors stored in right-hand-side pairs up to this K
+// the red-black solver's FP64 outer step takes two right-hand sides at a time
+constexpr bool outer_pairs(int K) { return K >= 9 && K <= 12; }
 constexpr int PC_JACOBI = 0; // preconditioner kinds as seen by the kernels
 constexpr int PC_BLOCK = 1;
 

@@ -488,6 +488,35 @@ __device__ __forceinline__ void sym_apply(const GetS& s, const V (&x)[K], V (&y)
   }
 }
 
+// Ties the computation of v to this place (no instruction): where only the
+// valid lanes use a value, the compiler otherwise moves all arithmetic into
+// that branch, past the loads, whose results then all wait in registers.
+template <typename V>
+__device__ __forceinline__ void pin(V& v) {
+  asm volatile("" : "+v"(v));
+}
+
+// y[m] += S x[m] for two right-hand sides, each entry of S read once for both
+// (for each the operations of sym_apply in its order).  Rows go in groups of
+// about G entries: the loads of a group are in flight together, and none of a
+// later one takes registers before.
+template <int K, int G, typename V, typename GetS>
+__device__ __forceinline__ void sym_apply2(const GetS& s, const V (&x)[2][K], V (&y)[2][K]) {
+  #pragma unroll
+  for (int k = 0; k < K; ++k) {
+  #pragma unroll
+    for (int j = 0; j <= k; ++j) {
+      const V v = s(pk(k, j));
+  #pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        y[m][k] = fma_of(v, x[m][j], y[m][k]);
+        if (j != k) y[m][j] = fma_of(v, x[m][k], y[m][j]);
+      }
+    }
+    if (pk(k + 1, 0) / G != pk(k, 0) / G) __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // Refinement of right-hand side r at voxel w.nn: r64 = b - Q x (Q x = 0 for a
 // zero start value), r = T(r64), p = M^{-1} r; acc = (||r64||^2, ||b||^2, r'p).
 // getB(i), getP(i): packed entry i of the voxel's FP64 block and preconditioner.

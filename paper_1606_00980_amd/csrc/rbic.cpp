@@ -320,6 +320,9 @@ std::vector<RbGroup> rb_groups(RbProb* h, int n, int rhs_tile, bool outer_chunks
           break;
         }
       }
+    long pairs = 0;
+    for (int j = g.first; j < g.first + g.count; ++j) pairs += (long)h[j].rb.ntB * ((h[j].pr.R + 1) / 2);
+    const int Ro = outer_pairs(g.K) && pairs >= 1024 ? 2 : 1;
     int F = 0;
     for (int j = g.first; j < g.first + g.count; ++j) {
       RbProb& P = h[j];
@@ -338,10 +341,11 @@ std::vector<RbGroup> rb_groups(RbProb* h, int n, int rhs_tile, bool outer_chunks
       g.WR += P.rb.ntR * P.nch;
       // the FP64 refinement and x_B += d: one right-hand side per work item
       // (holding the FP64 blocks across several costs the refinement
-      // occupancy), or the inner chunks when most right-hand sides of a launch
-      // are not in the outer phase (the serving loop), so that the launch does
-      // not consist of empty workgroups
-      P.Rco = outer_chunks ? P.Rc : 1;
+      // occupancy), two where the refinement takes two together and that
+      // leaves four workgroups per compute unit, or the inner chunks when most
+      // right-hand sides of a launch are not in the outer phase (the serving
+      // loop), so that the launch does not consist of empty workgroups
+      P.Rco = outer_chunks ? P.Rc : std::min(Ro, P.pr.R);
       P.ncho = (P.pr.R + P.Rco - 1) / P.Rco;
       P.wO = g.WO;
       g.WO += P.rb.ntB * P.ncho;

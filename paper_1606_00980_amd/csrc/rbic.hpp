@@ -196,6 +196,42 @@ struct RbFirst {
   int pstride, r0;
 };
 
+// neighbour_sum of two right-hand sides (vs(m): vector m), G values (rows times
+// right-hand sides) at a time: their six loads each are in flight together,
+// and none of a later group takes registers before (the additions in
+// neighbour_sum's order).
+template <int K, int G, typename T, typename VS>
+__device__ __forceinline__ void neighbour_sum2(const int (&nb)[6], const VS& vs, T (&s)[2][K]) {
+  constexpr int C = G / 2;
+#pragma unroll
+  for (int k0 = 0; k0 < K; k0 += C) {
+    T t[2][C][6];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const Slab<T> v = vs(m);
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+#pragma unroll
+        for (int d = 0; d < 6; ++d)
+          if (k0 + c < K) t[m][c][d] = v.ld(k0 + c, nb[d] < 0 ? 0u : (unsigned)nb[d] * (unsigned)sizeof(T));
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        if (k0 + c < K) {
+          T a = 0;
+#pragma unroll
+          for (int d = 0; d < 6; ++d) a += nb[d] < 0 ? (T)0 : t[m][c][d];
+          s[m][k0 + c] = a;
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // Right-hand sides the refinement step works on: those in the outer phase,
 // except the first step from a zero start value, which the split takes.
 __device__ __forceinline__ bool refine_active(const RbDev& rb, const RhsState& s) {
@@ -558,6 +594,37 @@ __global__ __launch_bounds__(TILE) void k_rb_split_black(RbDev rb, int R, int rc
   });
 }
 
+// f(rr) for the right-hand sides of [r0, r1) that are on(), two at a time; a
+// last one alone comes twice (its values are formed and stored twice).  The
+// FP64 stages of the outer step take two for K = 9..12: at one right-hand
+// side they read 660 bytes of voxel blocks beside 320 of vectors (K = 10), and
+// the registers kept few loads in flight.  Two share the blocks, and the loads
+// go in groups whose size is set here (rows of gathers, block entries): the
+// compiler's own order held either too few or, moved past one another, all of
+// them.  64 right-hand sides, K = 10, N = 289,592: refinement 1628 -> 1115 us,
+// red stage 915 -> 787; 32, N = 52,740: refinement 184 -> 124 at K = 11, 205 ->
+// 163 at K = 12; at K = 6 no gain (105 and 103, and more while few right-hand
+// sides are left), and beyond K = 12 their registers leave one wavefront.
+constexpr int OUTER_GATHER = 6, OUTER_ENTRIES = 20;
+// FP32 inner red stage at K = 10, both of a pair together: 381 -> 357 us at the
+// size above; at K = 6 and 8 one after the other is faster (32.1 against 33.4).
+constexpr int RED_GATHER = 10, RED_KMIN = 10;
+template <typename On, typename F>
+__device__ __forceinline__ void for_pairs(int r0, int r1, const On& on, const F& f) {
+#pragma unroll 1
+  for (int r = r0; r < r1; ++r) {
+    if (!on(r)) continue;
+    int q = r + 1;
+    while (q < r1 && !on(q)) ++q;
+    // (uniform, but found from memory: else every buffer access loops over lanes)
+    r = __builtin_amdgcn_readfirstlane(r);
+    q = __builtin_amdgcn_readfirstlane(q);
+    const int rr[2] = {r, q < r1 ? q : r};
+    f(rr);
+    r = q;
+  }
+}
+
 // Right-hand side r takes part in the red stage of phase `want` (nothing to do
 // for the first refinement from a zero start value: S 0 = 0).
 __device__ __forceinline__ bool red_active(const RbDev& rb, const RhsState& s, int want) {
@@ -598,6 +665,22 @@ __global__ __launch_bounds__(TILE) void k_rb_red(const RbProb* __restrict__ prob
     }
     sym_apply<K>(Pn, s, y);
   };
+  // the same for two right-hand sides together
+  auto stage2 = [&](const int (&rr)[2], T (&y)[2][K]) {
+#pragma clang fp contract(off)
+    T s[2][K];
+    neighbour_sum2<K, OUTER ? OUTER_GATHER : RED_GATHER>(
+        nb, [&](int m) { return Slab<T>(v + (size_t)rr[m] * K * rb.NB, K, rb.NB); }, s);
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        s[m][k] *= RbT<T>::alpha(rb, k);
+        y[m][k] = 0;
+      }
+    }
+    sym_apply2<K, OUTER_ENTRIES>(Pn, s, y);
+  };
   if constexpr (!OUTER && UPaired<T, K>::v) {
     // both right-hand sides of a pair in the item: one 8-byte store per row
     // (an inactive partner's half written as zero: no kernel reads it before
@@ -610,17 +693,24 @@ __global__ __launch_bounds__(TILE) void k_rb_red(const RbProb* __restrict__ prob
         const bool a0 = red_active(rb, st[r], want), a1 = red_active(rb, st[r + 1], want);
         if (a0 || a1) {
           T y0[K], y1[K];
-          if (a0) {
+          if (K >= RED_KMIN && a0 && a1) {
+            const int rr[2] = {r, r + 1};
+            T y[2][K];
+            stage2(rr, y);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+              y0[k] = y[0][k];
+              y1[k] = y[1][k];
+            }
+          } else if (a0) {
             stage(r, y0);
+#pragma unroll
+            for (int k = 0; k < K; ++k) y1[k] = 0;
+            if (a1) stage(r + 1, y1);
           } else {
 #pragma unroll
             for (int k = 0; k < K; ++k) y0[k] = 0;
-          }
-          if (a1) {
             stage(r + 1, y1);
-          } else {
-#pragma unroll
-            for (int k = 0; k < K; ++k) y1[k] = 0;
           }
 #pragma unroll
           for (int k = 0; k < K; ++k) up.st2(k, j, y0[k], y1[k]);
@@ -636,6 +726,13 @@ __global__ __launch_bounds__(TILE) void k_rb_red(const RbProb* __restrict__ prob
         r += 1;
       }
     }
+  } else if constexpr (OUTER && outer_pairs(K)) {
+    for_pairs(w.r0, w.r1, [&](int r) { return red_active(rb, st[r], want); }, [&](const int (&rr)[2]) {
+      T y[2][K];
+      stage2(rr, y);
+#pragma unroll
+      for (int m = 0; m < 2; ++m) RbVec<T, K>(u + (size_t)rr[m] * K * rb.NR, rb.NR).store(j, y[m]);
+    });
   } else {
 #pragma unroll 1
     for (int r = w.r0; r < w.r1; ++r) {
@@ -675,45 +772,101 @@ __global__ __launch_bounds__(TILE) void k_rb_refine(const RbProb* __restrict__ p
   const Packed<double, K, HOLD> D(rb.D64, rb.NB, o8);
   const Packed<T, K, HOLD> S(RbT<T>::S(rb), rb.NB, oT);
   ItemSums<3> sums;
+  if constexpr (outer_pairs(K)) {
+    for_pairs(w.r0, w.r1, [&](int r) { return refine_active(rb, st[r]); }, [&](const int (&rr)[2]) {
+      double r64[2][K];
+      {
+        double xv[2][K], y[2][K];
+        neighbour_sum2<K, OUTER_GATHER>(
+            nb, [&](int m) { return Slab<double>(P.u64 + (size_t)rr[m] * K * rb.NR, K, rb.NR); }, y);
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          const Slab<double> xs(P.xB + (size_t)rr[m] * K * rb.NB, K, rb.NB);
+#pragma unroll
+          for (int k = 0; k < K; ++k) {
+            xv[m][k] = xs.ld(k, o8);
+            y[m][k] *= -rb.alpha64[k];
+          }
+        }
+        sym_apply2<K, OUTER_ENTRIES>(D, xv, y);
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          const Slab<double> cs(P.c64 + (size_t)rr[m] * K * rb.NB, K, rb.NB);
+#pragma unroll
+          for (int k = 0; k < K; ++k) {
+            r64[m][k] = cs.ld(k, o8) - y[m][k];
+            pin(r64[m][k]);
+          }
+        }
+      }
+      double acc[2][3];
+      T rt[2][K], zt[2][K];
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        acc[m][0] = acc[m][1] = acc[m][2] = 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          acc[m][0] += r64[m][k] * r64[m][k];
+          rt[m][k] = (T)r64[m][k];
+          zt[m][k] = 0;
+        }
+      }
+      sym_apply2<K, 2 * OUTER_ENTRIES>(S, rt, zt);
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) acc[m][2] += (double)rt[m][k] * (double)zt[m][k];
+        if (valid) {   // (a lone right-hand side writes the same values twice)
+          const size_t off = (size_t)rr[m] * K * rb.NB;
+          RbVec<T, K>((T*)P.r + off, rb.NB).store(ii, rt[m]);
+          RbVec<T, K>((T*)P.p + off, rb.NB).store(ii, zt[m]);
+        } else {
+          acc[m][0] = acc[m][2] = 0.0;
+        }
+        sums.add(rr[m] - w.r0, acc[m]);
+      }
+    });
+  } else {
 #pragma unroll 1
-  for (int r = w.r0; r < w.r1; ++r) {
-    const RhsState& sr = st[r];
-    if (!refine_active(rb, sr)) continue;
-    const size_t off = (size_t)r * K * rb.NB;
-    const Slab<double> cs(P.c64 + off, K, rb.NB), xs(P.xB + off, K, rb.NB),
-        us(P.u64 + (size_t)r * K * rb.NR, K, rb.NR);
-    const RbVec<T, K> rs((T*)P.r + off, rb.NB), ps((T*)P.p + off, rb.NB);
-    double r64[K];
-    {
-      double xv[K], y[K], s[K];
+    for (int r = w.r0; r < w.r1; ++r) {
+      const RhsState& sr = st[r];
+      if (!refine_active(rb, sr)) continue;
+      const size_t off = (size_t)r * K * rb.NB;
+      const Slab<double> cs(P.c64 + off, K, rb.NB), xs(P.xB + off, K, rb.NB),
+          us(P.u64 + (size_t)r * K * rb.NR, K, rb.NR);
+      const RbVec<T, K> rs((T*)P.r + off, rb.NB), ps((T*)P.p + off, rb.NB);
+      double r64[K];
+      {
+        double xv[K], y[K], s[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          xv[k] = xs.ld(k, o8);
+          y[k] = 0.0;
+        }
+        sym_apply<K>(D, xv, y);
+        neighbour_sum<double, K>(nb, us, s);
+#pragma unroll
+        for (int k = 0; k < K; ++k) r64[k] = cs.ld(k, o8) - (y[k] - rb.alpha64[k] * s[k]);
+      }
+      double acc[3] = {0.0, 0.0, 0.0};
+      T rt[K], zt[K];
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        xv[k] = xs.ld(k, o8);
-        y[k] = 0.0;
+        acc[0] += r64[k] * r64[k];
+        rt[k] = (T)r64[k];
+        zt[k] = 0;
       }
-      sym_apply<K>(D, xv, y);
-      neighbour_sum<double, K>(nb, us, s);
+      sym_apply<K>(S, rt, zt);
 #pragma unroll
-      for (int k = 0; k < K; ++k) r64[k] = cs.ld(k, o8) - (y[k] - rb.alpha64[k] * s[k]);
+      for (int k = 0; k < K; ++k) acc[2] += (double)rt[k] * (double)zt[k];
+      if (valid) {
+        rs.store(ii, rt);
+        ps.store(ii, zt);
+      } else {
+        acc[0] = acc[2] = 0.0;
+      }
+      sums.add(r - w.r0, acc);
     }
-    double acc[3] = {0.0, 0.0, 0.0};
-    T rt[K], zt[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      acc[0] += r64[k] * r64[k];
-      rt[k] = (T)r64[k];
-      zt[k] = 0;
-    }
-    sym_apply<K>(S, rt, zt);
-#pragma unroll
-    for (int k = 0; k < K; ++k) acc[2] += (double)rt[k] * (double)zt[k];
-    if (valid) {
-      rs.store(ii, rt);
-      ps.store(ii, zt);
-    } else {
-      acc[0] = acc[2] = 0.0;
-    }
-    sums.add(r - w.r0, acc);
   }
   sums.flush(P.pr.part, (size_t)R * pstride, w.r0, w.r1 - w.r0, pstride, w.tile);
 }
