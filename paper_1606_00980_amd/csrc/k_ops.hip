@@ -197,32 +197,56 @@ __global__ __launch_bounds__(TILE) void k_precond(OpDev op, int pc, double* __re
 }
 
 // ----------------------------------------------------------------- apply
+// Items (rc right-hand sides, tile) run by blocks of tb tiles, every chunk of
+// right-hand sides over a block's tiles before the next block, and go to the
+// XCDs in contiguous ranges (as k_perturb's).  The vectors are read through
+// buffer descriptors: with a 64-bit address per gather the loads of few
+// neighbours were in flight at a time, and every right-hand side read the
+// blocks again: 25.1 us for 8 right-hand sides at K = 6, N = 52,740 (18.7 so:
+// 2.6 TB/s of its 49 MB), 98 for 16 at K = 10 (58).  A block is held across an
+// item's right-hand sides up to K = 9.
 template <int K>
-__global__ __launch_bounds__(TILE) void k_apply(OpDev op, const double* __restrict__ x,
-                                                double* __restrict__ y) {
+__global__ __launch_bounds__(TILE) void k_apply(OpDev op, const double* __restrict__ x, double* __restrict__ y, int R,
+                                                int rc, int tb) {
   constexpr int NB = Tri<K>::NB;
-  const int N = op.N;
-  const int n = blockIdx.x * TILE + threadIdx.x;
-  const int r = blockIdx.y;
+  constexpr bool HOLD = K <= 9;
+  const int N = op.N, nch = (R + rc - 1) / rc;
+  const int item = xcd_remap(blockIdx.x, gridDim.x);
+  const int per = tb * nch;
+  const int blk = item / per, rem = item - blk * per;
+  const int len = min(tb, op.ntiles - blk * tb);
+  const int r0 = rem / len * rc, r1 = min(R, r0 + rc);
+  const int n = (blk * tb + rem % len) * TILE + threadIdx.x;
   if (n >= N) return;
-  int nb[6];
+  const unsigned o = (unsigned)n * 8u;
+  unsigned nb[6];
 #pragma unroll
-  for (int d = 0; d < 6; ++d) nb[d] = op.nbr[(size_t)d * N + n];
-  double B[NB];
-  load_soa(op.B64, N, n, B);
-  const double* xr = x + (size_t)r * K * N;
-  double xo[K];
+  for (int d = 0; d < 6; ++d) nb[d] = (unsigned)op.nbr[(size_t)d * N + n] * 8u;
+  const Slab<double> Bs(op.B64, NB, N);
+  double Bh[HOLD ? NB : 1];
+  if constexpr (HOLD) {
 #pragma unroll
-  for (int k = 0; k < K; ++k) xo[k] = xr[(size_t)k * N + n];
+    for (int e = 0; e < NB; ++e) Bh[e] = Bs.ld(e, o);
+  }
+#pragma unroll 1
+  for (int r = r0; r < r1; ++r) {
+    const Slab<double> xs(x + (size_t)r * K * N, K, N), ys(y + (size_t)r * K * N, K, N);
+    double xo[K], s6[K];
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    double s6 = 0.0;
+    for (int k = 0; k < K; ++k) xo[k] = xs.ld(k, o);
 #pragma unroll
-    for (int d = 0; d < 6; ++d) s6 += xo[k] - xr[(size_t)k * N + nb[d]];
-    double v = op.alpha64[k] * s6;
+    for (int k = 0; k < K; ++k) {
+      s6[k] = 0.0;
 #pragma unroll
-    for (int j = 0; j < K; ++j) v += B[pk(k, j)] * xo[j];
-    y[(size_t)r * K * N + (size_t)k * N + n] = v;
+      for (int d = 0; d < 6; ++d) s6[k] += xo[k] - xs.ld(k, nb[d]);
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      double v = op.alpha64[k] * s6[k];
+#pragma unroll
+      for (int j = 0; j < K; ++j) v += (HOLD ? Bh[HOLD ? pk(k, j) : 0] : Bs.ld(pk(k, j), o)) * xo[j];
+      ys.st(k, o, v);
+    }
   }
 }
 
@@ -447,10 +471,29 @@ hipError_t launch_precond(hipStream_t s, const OpDev& op, int pc, double* P64, f
   return hipGetLastError();
 }
 
+// Tiles per block of an item order: two planes of voxels and two tiles, the
+// block's packed matrices at most 1.5 MB.
+static int tiles_per_block(const OpDev& op) {
+  const long reach = ((long)op.N / (op.nz > 0 ? op.nz : 1) + TILE - 1) / TILE;
+  const long cap = std::max(4L, (long)(1536 << 10) / ((long)(op.K * (op.K + 1) / 2) * TILE * 8));
+  return (int)std::max(1L, std::min({2 * reach + 2, cap, (long)op.ntiles}));
+}
+
 hipError_t launch_apply(hipStream_t s, const OpDev& op, int R, const double* x, double* y) {
-  const dim3 g((op.N + TILE - 1) / TILE, R), b(TILE);
+  if (op.ntiles == 0 || R == 0) return hipSuccess;
+  // right-hand sides per workgroup (their block read once): the largest of 4, 2,
+  // 1 that leaves two workgroups per compute unit (16 at K = 10, N = 52,740:
+  // 68, 62 and 58 us at 1, 2 and 4; 8 at K = 6: 18.7 at each)
+  int rc = 1;
+  for (int cand : {4, 2})
+    if ((long)op.ntiles * ((R + cand - 1) / cand) >= 512) {
+      rc = cand;
+      break;
+    }
+  const dim3 g((unsigned)((long)op.ntiles * ((R + rc - 1) / rc))), b(TILE);
+  const int tb = tiles_per_block(op);
   switch (op.K) {
-#define X(KK) case KK: GP_LAUNCH(k_apply<KK>, g, b, 0, s, op, x, y); break;
+#define X(KK) case KK: GP_LAUNCH(k_apply<KK>, g, b, 0, s, op, x, y, R, rc, tb); break;
     GP_K_CASES(X)
 #undef X
     default: return hipErrorInvalidValue;
@@ -462,11 +505,7 @@ hipError_t launch_perturb(hipStream_t s, const OpDev& op, int R, const double* b
                           const double* z2, double* b) {
   if (op.ntiles == 0 || R == 0) return hipSuccess;
   const dim3 g((unsigned)((long)op.ntiles * R)), bl(TILE);
-  // tiles per block: two planes of voxels and two tiles, the block's packed
-  // factors at most 1.5 MB
-  const long reach = ((long)op.N / (op.nz > 0 ? op.nz : 1) + TILE - 1) / TILE;
-  const long cap = std::max(4L, (long)(1536 << 10) / ((long)(op.K * (op.K + 1) / 2) * TILE * 8));
-  const int tb = (int)std::max(1L, std::min({2 * reach + 2, cap, (long)op.ntiles}));
+  const int tb = tiles_per_block(op);
   switch (op.K) {
 #define X(KK) case KK: GP_LAUNCH(k_perturb<KK>, g, bl, 0, s, op, bw, z1, z2, b, R, tb); break;
     GP_K_CASES(X)

@@ -82,3 +82,29 @@ def test_outer_step_in_pairs(g, ctx, torch_cuda, K, R, dims):
     finally:
         torch_cuda.cuda.synchronize()
         g.gp_op_destroy(op)
+
+
+@pytest.mark.parametrize("K,R,dims", [(1, 1, (3, 1, 1)), (6, 3, (13, 11, 7)), (9, 5, (48, 46, 37)), (9, 7, (48, 46, 37)),
+                                      (10, 7, (48, 46, 37)), (24, 2, (9, 8, 4))])
+def test_product_of_several_right_hand_sides(g, ctx, torch_cuda, K, R, dims):
+    """One, two and four right-hand sides to a workgroup, the last ones fewer."""
+    N = dims[0] * dims[1] * dims[2]
+    r = np.random.default_rng(3 * K + R)
+    A = r.standard_normal((N, K, K + 2))
+    B = np.matmul(A, A.transpose(0, 2, 1)) / (K + 2)
+    alpha = r.uniform(0.5, 3.0, K)
+    x = r.standard_normal((R, K, N))
+    op = g.gp_op_create(ctx, np.ones(dims[::-1], dtype=np.uint8), 6, K)
+    try:
+        g.gp_op_set_blocks(op, torch_cuda.from_numpy(B).cuda())
+        g.gp_op_set_alpha(op, alpha)
+        y = torch_cuda.empty((R, K, N), dtype=torch_cuda.float64, device="cuda")
+        g.gp_apply(op, R, torch_cuda.from_numpy(x).cuda(), y)
+        ys = y.cpu().numpy()
+        for i in range(R):
+            # sums of K + 6 products in another order
+            scale = np.einsum("nkl,ln->kn", np.abs(B), np.abs(x[i])) + 12 * alpha[:, None] * np.abs(x).max()
+            assert (np.abs(ys[i] - q_times(B, alpha, x[i], dims)) <= 1e-15 * 2 * (K + 6) * scale).all()
+    finally:
+        torch_cuda.cuda.synchronize()
+        g.gp_op_destroy(op)
