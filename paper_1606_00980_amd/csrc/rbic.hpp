@@ -196,6 +196,8 @@ struct RbFirst {
   int pstride, r0;
 };
 
+constexpr int OUTER_GATHER = 6, OUTER_ENTRIES = 20;   // values whose gathers, entries whose loads are issued together
+
 // neighbour_sum of two right-hand sides (vs(m): vector m), G values (rows times
 // right-hand sides) at a time: their six loads each are in flight together,
 // and none of a later group takes registers before (the additions in
@@ -483,8 +485,8 @@ __global__ __launch_bounds__(SETUP_WG) void k_rb_setup_black(RbDev rb, const dou
 // run tile by tile within a chunk of right-hand sides and go to the XCDs in
 // contiguous ranges (z-neighbours then share an L2).  In voxel order half of
 // the lanes idled through the red blocks and c was written, read and written
-// again: 2283 us for 64 right-hand sides at K = 10, N = 289,592 (1850 so), 99
-// for five at K = 15, N = 52,740 (66), 82 for 32 at K = 6 (81).
+// again: 2283 us for 64 right-hand sides at K = 10, N = 289,592 (1566 so), 99
+// for five at K = 15, N = 52,740 (59), 82 for 32 at K = 6 (80).
 struct SplitItem {
   int tile, r0, r1;
 };
@@ -494,7 +496,29 @@ __device__ __forceinline__ SplitItem split_item(int nt, int R, int rc) {
   return {wi - chunk * nt, r0, min(R, r0 + rc)};
 }
 
-// Red voxels: t = Q_nn^{-1} b_n; ||b||^2 partials bbpart[r][tile] of the red tiles.
+// f on the right-hand sides of [r0, r1), two at a time when TWO (a last one alone)
+template <bool TWO, typename F>
+__device__ __forceinline__ void each_or_two(int r0, int r1, const F& f) {
+#pragma unroll 1
+  for (int r = r0; r < r1;) {
+    if constexpr (TWO) {
+      if (r + 1 < r1) {
+        const int rr[2] = {r, r + 1};
+        f(rr);
+        r += 2;
+        continue;
+      }
+    }
+    const int rr[1] = {r};
+    f(rr);
+    r += 1;
+  }
+}
+
+// Red voxels: t = Q_nn^{-1} b_n; ||b||^2 partials bbpart[r][tile] of the red
+// tiles.  From K = 9 to 12 two right-hand sides share the reading of the
+// inverse, and the product is pinned before the branch that stores it: 878 ->
+// 595 us for 64 at K = 10, N = 289,592, 38 -> 30 for five at K = 15, N = 52,740.
 template <int K>
 __global__ __launch_bounds__(TILE) void k_rb_split_red(RbDev rb, int R, int rc, const double* __restrict__ b,
                                                        double* __restrict__ t, double* __restrict__ bbpart) {
@@ -506,22 +530,38 @@ __global__ __launch_bounds__(TILE) void k_rb_split_red(RbDev rb, int R, int rc, 
   // the red inverse, held across the work item's right-hand sides
   const Packed<double, K, HoldRb<double, K, 1>::v> P(rb.P64, rb.NR, oj);
   ItemSums<1> sums;
-#pragma unroll 1
-  for (int r = w.r0; r < w.r1; ++r) {
-    const Slab<double> bs(b + (size_t)r * K * rb.N, K, rb.N);
-    double acc[1] = {0.0}, bv[K], tv[K];
+  auto pass = [&](const auto& rr) {
+    constexpr int M = sizeof(rr) / sizeof(rr[0]);
+    double acc[M][1], bv[M][K], tv[M][K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) bv[k] = bs.ld(k, on);
+    for (int m = 0; m < M; ++m) {
+      const Slab<double> bs(b + (size_t)rr[m] * K * rb.N, K, rb.N);
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      acc[0] += bv[k] * bv[k];
-      tv[k] = 0.0;
+      for (int k = 0; k < K; ++k) bv[m][k] = bs.ld(k, on);
     }
-    if (!valid) acc[0] = 0.0;
-    sym_apply<K>(P, bv, tv);
-    if (valid) RbVec<double, K>(t + (size_t)r * K * rb.NR, rb.NR).store(j, tv);
-    sums.add(r - w.r0, acc);
-  }
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      acc[m][0] = 0.0;
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        acc[m][0] += bv[m][k] * bv[m][k];
+        tv[m][k] = 0.0;
+      }
+      if (!valid) acc[m][0] = 0.0;
+    }
+    if constexpr (M == 2)
+      sym_apply2<K, OUTER_ENTRIES>(P, bv, tv);
+    else
+      sym_apply<K>(P, bv[0], tv[0]);
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) pin(tv[m][k]);
+      if (valid) RbVec<double, K>(t + (size_t)rr[m] * K * rb.NR, rb.NR).store(j, tv[m]);
+      sums.add(rr[m] - w.r0, acc[m]);
+    }
+  };
+  each_or_two<outer_pairs(K)>(w.r0, w.r1, pass);
   sums.flush(bbpart, 0, w.r0, w.r1 - w.r0, rb.ntS, w.tile);
 }
 
@@ -602,10 +642,9 @@ __global__ __launch_bounds__(TILE) void k_rb_split_black(RbDev rb, int R, int rc
 // go in groups whose size is set here (rows of gathers, block entries): the
 // compiler's own order held either too few or, moved past one another, all of
 // them.  64 right-hand sides, K = 10, N = 289,592: refinement 1628 -> 1115 us,
-// red stage 915 -> 787; 32, N = 52,740: refinement 184 -> 124 at K = 11, 205 ->
+// red stage 915 -> 800; 32, N = 52,740: refinement 184 -> 124 at K = 11, 205 ->
 // 163 at K = 12; at K = 6 no gain (105 and 103, and more while few right-hand
 // sides are left), and beyond K = 12 their registers leave one wavefront.
-constexpr int OUTER_GATHER = 6, OUTER_ENTRIES = 20;
 // FP32 inner red stage at K = 10, both of a pair together: 381 -> 357 us at the
 // size above; at K = 6 and 8 one after the other is faster (32.1 against 33.4).
 constexpr int RED_GATHER = 10, RED_KMIN = 10;
@@ -728,6 +767,12 @@ __global__ __launch_bounds__(TILE) void k_rb_red(const RbProb* __restrict__ prob
     }
   } else if constexpr (OUTER && outer_pairs(K)) {
     for_pairs(w.r0, w.r1, [&](int r) { return red_active(rb, st[r], want); }, [&](const int (&rr)[2]) {
+      if (rr[0] == rr[1]) {
+        T y[K];
+        stage(rr[0], y);
+        RbVec<T, K>(u + (size_t)rr[0] * K * rb.NR, rb.NR).store(j, y);
+        return;
+      }
       T y[2][K];
       stage2(rr, y);
 #pragma unroll
