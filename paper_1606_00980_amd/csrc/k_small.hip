@@ -15,6 +15,8 @@
 // iteration against 8.7 in the grouped kernels; a solve and a sample 264 us
 // against 675 (with replayed rounds; 16 wavefronts a workgroup instead of
 // eight, with spills and the blocks read per use, 360 us).
+#include <utility>
+
 #include "launch.hpp"
 #include "pcg.hpp"
 
@@ -245,21 +247,28 @@ __global__ __launch_bounds__(SM_WG) void k_small(const Prob* __restrict__ probs,
 // 440 us), beyond it the blocks, then read from L2 by one compute unit, cost
 // more than the launches (K = 8, N = 820, 192 doubles, 632 against 554 us).
 constexpr int SM_MOST = 128;
+constexpr int SM_KMOST = 10;   // largest K with a kernel
+constexpr int SM_V[] = {1, 2, 3, 4, 5, 6, 8, 12};   // voxels per lane with a kernel
 constexpr int lane_doubles(int pc, int K, int V) {
   return V * (K * (K + 1) / 2 + (pc == PC_BLOCK ? K * (K + 1) / 2 : K) + 3 * K);
 }
 
+// What the rule may return and the launcher can run, for V out of SM_V.  (Up
+// to 512 voxels Jacobi stays within SM_MOST at K = 11 and 12 too: those have no
+// kernel and take the grouped ones.)
+constexpr bool small_kernel(int pc, int K, int V) { return K <= SM_KMOST && lane_doubles(pc, K, V) <= SM_MOST; }
+
 // Voxels per lane, 0 where the grouped kernels take the solve.
 int small_lane_voxels(int pc, int N, int K) {
-  for (int v : {1, 2, 3, 4, 5, 6, 8, 12})
-    if (N <= v * SM_WG) return lane_doubles(pc, K, v) <= SM_MOST ? v : 0;
+  for (int v : SM_V)
+    if (N <= v * SM_WG) return small_kernel(pc, K, v) ? v : 0;
   return 0;
 }
 
 namespace {
 template <int PC, int K, int V>
 bool try_small(hipStream_t s, int pc, int k, int v, const Prob* probs, int nprob, int nrhs) {
-  if constexpr (lane_doubles(PC, K, V) <= SM_MOST) {
+  if constexpr (small_kernel(PC, K, V)) {
     if (pc == PC && k == K && v == V) {
       GP_LAUNCH((k_small<PC, K, V>), dim3(nrhs), dim3(SM_WG), 0, s, probs, nprob);
       return true;
@@ -267,26 +276,23 @@ bool try_small(hipStream_t s, int pc, int k, int v, const Prob* probs, int nprob
   }
   return false;
 }
-template <int K, int V>
-bool try_small_pc(hipStream_t s, int pc, int k, int v, const Prob* probs, int nprob, int nrhs) {
-  return try_small<PC_BLOCK, K, V>(s, pc, k, v, probs, nprob, nrhs) ||
-         try_small<PC_JACOBI, K, V>(s, pc, k, v, probs, nprob, nrhs);
+template <int K, int... I>
+bool try_small_k(std::integer_sequence<int, I...>, hipStream_t s, int pc, int k, int v, const Prob* probs, int nprob,
+                 int nrhs) {
+  return (try_small<PC_BLOCK, K, SM_V[I]>(s, pc, k, v, probs, nprob, nrhs) || ...) ||
+         (try_small<PC_JACOBI, K, SM_V[I]>(s, pc, k, v, probs, nprob, nrhs) || ...);
 }
-template <int K>
-bool try_small_k(hipStream_t s, int pc, int k, int v, const Prob* probs, int nprob, int nrhs) {
-  return try_small_pc<K, 1>(s, pc, k, v, probs, nprob, nrhs) || try_small_pc<K, 2>(s, pc, k, v, probs, nprob, nrhs) ||
-         try_small_pc<K, 3>(s, pc, k, v, probs, nprob, nrhs) || try_small_pc<K, 4>(s, pc, k, v, probs, nprob, nrhs) ||
-         try_small_pc<K, 5>(s, pc, k, v, probs, nprob, nrhs) || try_small_pc<K, 6>(s, pc, k, v, probs, nprob, nrhs) ||
-         try_small_pc<K, 8>(s, pc, k, v, probs, nprob, nrhs) || try_small_pc<K, 12>(s, pc, k, v, probs, nprob, nrhs);
+// every K up to SM_KMOST with every V
+template <int... I>
+bool try_small_all(std::integer_sequence<int, I...>, hipStream_t s, int pc, int k, int v, const Prob* probs, int nprob,
+                   int nrhs) {
+  constexpr int NV = sizeof(SM_V) / sizeof(SM_V[0]);
+  return (try_small_k<I + 1>(std::make_integer_sequence<int, NV>{}, s, pc, k, v, probs, nprob, nrhs) || ...);
 }
 }  // namespace
 
 hipError_t launch_small(hipStream_t s, int pc, int K, int V, const Prob* probs, int nprob, int nrhs) {
-  if (!(try_small_k<1>(s, pc, K, V, probs, nprob, nrhs) || try_small_k<2>(s, pc, K, V, probs, nprob, nrhs) ||
-        try_small_k<3>(s, pc, K, V, probs, nprob, nrhs) || try_small_k<4>(s, pc, K, V, probs, nprob, nrhs) ||
-        try_small_k<5>(s, pc, K, V, probs, nprob, nrhs) || try_small_k<6>(s, pc, K, V, probs, nprob, nrhs) ||
-        try_small_k<7>(s, pc, K, V, probs, nprob, nrhs) || try_small_k<8>(s, pc, K, V, probs, nprob, nrhs) ||
-        try_small_k<9>(s, pc, K, V, probs, nprob, nrhs) || try_small_k<10>(s, pc, K, V, probs, nprob, nrhs)))
+  if (!try_small_all(std::make_integer_sequence<int, SM_KMOST>{}, s, pc, K, V, probs, nprob, nrhs))
     return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -126,3 +126,31 @@ def test_both_finalisations_in_one_batch(g, ctx, torch_cuda, pc, prec):
             assert res <= 1.01e-8 and st[at + r]["inner_iters"] == sa[r]["inner_iters"]
         at += R
         g.gp_op_destroy(op)
+
+
+@pytest.mark.parametrize("K,N", [(10, 512), (11, 512), (11, 513), (12, 1), (12, 512), (13, 512)])
+def test_jacobi_around_the_largest_k(g, ctx, torch_cuda, K, N):
+    """Jacobi solves in FP64 on either side of the largest K that the
+    one-workgroup kernel exists for, alone and in one batch with an operator
+    that it takes."""
+    torch = torch_cuda
+    kw = dict(tol=1e-10, precision=g.GP_PREC_FP64, precond=g.GP_PRECOND_JACOBI, zero_guess=1)
+    items, refs, keep = [], [], []
+    for nx, k in ((N, K), (70, 2)):
+        mask, B, alpha, b = operator(nx, 1, k, nx + k)
+        op = g.gp_op_create(ctx, mask, 4, k)
+        Bd, bd = torch.from_numpy(B).cuda(), torch.from_numpy(b).cuda()
+        g.gp_op_set_blocks(op, Bd)
+        g.gp_op_set_alpha(op, alpha)
+        Q = orc.precision(orc.grid(mask, 4), alpha, B)
+        refs.append(np.stack([orc.solve(Q, b[i:i + 1])[0] for i in range(3)]))
+        items.append((op, 3, bd, torch.full_like(bd, float("nan"))))
+        keep.append(Bd)
+    _, st = g.gp_solve_batch(ctx, items, g.gp_opts_default(**kw))
+    assert all(s["status"] == g.GP_OK and s["relres"] <= 1e-10 for s in st)
+    for (op, R, bd, x), ref in zip(items, refs):
+        assert np.linalg.norm(x.cpu().numpy() - ref) <= 1e-8 * np.linalg.norm(ref)
+        alone = torch.zeros_like(bd)
+        g.gp_solve(op, R, bd, alone, g.gp_opts_default(**kw))
+        assert torch.equal(alone, x)
+        g.gp_op_destroy(op)
