@@ -89,7 +89,7 @@ struct ItemSums {
   __device__ void flush(double* part, size_t vstride, int r0, int nr, int pstride, int tile) {
     flush_to(nr, [&](int i, int rl) { return part + (size_t)i * vstride + (size_t)(r0 + rl) * pstride + tile; });
   }
-  // value i of right-hand side r0 + rl to *at(i, rl)
+  // value i of right-hand side r0 + rl to *at(i, rl), not stored where at returns null
   template <typename F>
   __device__ void flush_to(int nr, const F& at) {
     __syncthreads();
@@ -99,7 +99,7 @@ struct ItemSums {
       double s = 0.0;
 #pragma unroll
       for (int w = 0; w < TILE / WAVE; ++w) s += sh[rl][i][w];
-      *at(i, rl) = s;
+      if (double* p = at(i, rl)) *p = s;
     }
   }
 };
@@ -628,8 +628,9 @@ __global__ __launch_bounds__(TILE) void k_rb_split_black(RbDev rb, int R, int rc
     if (!valid) acc[0] = acc[2] = acc[3] = 0.0;
     sums.add(r - w.r0, acc);
   }
-  sums.flush_to(w.r1 - w.r0, [&](int v, int rl) {
-    if (v == 3 || !first.r) return bbpart + (size_t)(w.r0 + rl) * rb.ntS + rb.ntR + w.tile;
+  sums.flush_to(w.r1 - w.r0, [&](int v, int rl) -> double* {
+    if (v == 3) return bbpart + (size_t)(w.r0 + rl) * rb.ntS + rb.ntR + w.tile;
+    if (!first.r) return nullptr;   // the refinement forms these from a start value
     return first.part + (size_t)v * first.vstride + (size_t)(first.r0 + w.r0 + rl) * first.pstride + w.tile;
   });
 }

@@ -518,3 +518,39 @@ def test_many_operators_and_items_match_alone_bitwise(g, ctx, torch_cuda, precis
         torch_cuda.cuda.synchronize()
         for op in ops:
             g.gp_op_destroy(op)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("dims,conn,K", [((23, 19, 9), 6, 3), ((29, 23, 17), 6, 1), ((41, 33, 1), 4, 2),
+                                         ((21, 19, 13), 6, 10), ((13, 11, 7), 6, 15)])
+def test_relative_residual_from_a_start_value(g, ctx, torch_cuda, precision, dims, conn, K):
+    """The reported relative residual of a solve from a start value, stopped
+    after three iterations, against ||b - Q x|| / ||b|| on the host, for
+    right-hand sides that live on one colour only (each colour's tiles carry a
+    part of ||b||) and on both.  The host's residual and the device's agree to
+    the rounding of Q x, taken as 1e-12 of ||Q|| ||x||."""
+    w = synth.tiny(dims, conn, K, seed=11 + K)
+    op = make_op(g, ctx, torch_cuda, w)
+    try:
+        z, y, x_ = np.nonzero(w.mask)
+        black = (z + y + x_) % 2 == 1
+        rng = np.random.default_rng(7)
+        b = rng.standard_normal((4, w.K, w.N))
+        b[0][:, ~black] = 0.0
+        b[1][:, black] = 0.0
+        x0 = 0.1 * rng.standard_normal(b.shape)
+        x = dev(torch_cuda, x0)
+        prec = g.GP_PREC_FP64 if precision == "fp64" else g.GP_PREC_FP32_REFINE64
+        _, st = g.gp_solve(op, 4, dev(torch_cuda, b), x,
+                           g.gp_opts_default(tol=1e-13, precision=prec, precond=g.GP_PRECOND_RB_IC0, max_iter=3),
+                           check=False)
+        Q = orc.precision(orc.grid(w.mask, w.conn), w.alpha, w.B)
+        qn = abs(Q).sum(axis=1).max()
+        for r in range(4):
+            xr = x[r].cpu().numpy().ravel()
+            nb = np.linalg.norm(b[r])
+            rel = np.linalg.norm(b[r].ravel() - Q @ xr) / nb
+            assert st[r]["status"] == g.GP_ERR_NOT_CONVERGED and st[r]["inner_iters"] == 3
+            assert abs(st[r]["relres"] - rel) <= 1e-12 * qn * np.linalg.norm(xr) / nb, (r, st[r]["relres"], rel)
+    finally:
+        g.gp_op_destroy(op)
