@@ -76,8 +76,13 @@ int set_device(gp_ctx* c) {
 // 230 MB in all, took 1.3 to 3.5 ms of a 1.5 to 3.8 ms pass in these calls).
 // At most KEPT_BLOCKS blocks and KEPT_BYTES are kept, counted against the
 // context's budget: a request that would exceed it (or that the device cannot
-// place) releases them first, and gp_ctx_destroy releases all.  A block is
-// only given back after the work that uses it has been waited for.
+// place) releases them first, and gp_ctx_destroy releases all.
+// A kept block may be written by the next call on the context's stream, so
+// nothing may use it any more.  Temporaries of a call that has waited for its
+// stream can be given back as they are.  An operator's, a dataset's and the
+// context's own buffers may still be read elsewhere (asynchronous calls on a
+// stream that the context has left, a caller's graph of them): wait_device
+// comes first, as hipFree's own wait did.
 constexpr size_t KEPT_BLOCKS = 16, KEPT_BYTES = (size_t)1 << 30;
 
 namespace {
@@ -122,12 +127,18 @@ int dev_alloc(gp_ctx* c, size_t bytes, void** p) {
   return GP_OK;
 }
 
-void dev_free(gp_ctx* c, void* p, size_t bytes) {
+bool wait_device() {
+  if (hipDeviceSynchronize() == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
+void dev_free(gp_ctx* c, void* p, size_t bytes, bool keep) {
   if (!p) return;
   bytes = align_up(std::max<size_t>(bytes, 1), 256);
   std::lock_guard<std::mutex> lk(c->kept_mu);
   c->used -= std::min(c->used, bytes);
-  if (bytes > KEPT_BYTES) {
+  if (!keep || bytes > KEPT_BYTES) {
     (void)hipFree(p);
     return;
   }
@@ -149,9 +160,9 @@ int op_alloc(gp_op* op, size_t count, T** p) {
 }
 
 template <typename T>
-void op_free(gp_op* op, T*& p, size_t count) {
+void op_free(gp_op* op, T*& p, size_t count, bool keep) {
   if (!p) return;
-  dev_free(op->ctx, p, count * sizeof(T));
+  dev_free(op->ctx, p, count * sizeof(T), keep);
   p = nullptr;
 }
 
@@ -159,7 +170,8 @@ int ensure_ws(gp_ctx* c, size_t bytes) {
   if (bytes <= c->ws_cap) return GP_OK;
   if (c->ws) {
     HIPTRY(hipStreamSynchronize(c->stream));
-    dev_free(c, c->ws, c->ws_cap);
+    const bool idle = wait_device();
+    dev_free(c, c->ws, c->ws_cap, idle);
     c->ws = nullptr;
     c->ws_cap = 0;
   }
@@ -179,7 +191,8 @@ int ensure_rhs(gp_ctx* c, size_t count) {
   if (count <= c->rhs_cap) return GP_OK;
   if (c->rhs) {
     HIPTRY(hipStreamSynchronize(c->stream));
-    dev_free(c, c->rhs, c->rhs_cap * sizeof(double));
+    const bool idle = wait_device();
+    dev_free(c, c->rhs, c->rhs_cap * sizeof(double), idle);
     c->rhs = nullptr;
     c->rhs_cap = 0;
   }
@@ -194,7 +207,8 @@ int ensure_buf(gp_ctx* c, T*& buf, size_t& cap, size_t count) {
   if (count <= cap) return GP_OK;
   if (buf) {
     HIPTRY(hipStreamSynchronize(c->stream));
-    dev_free(c, buf, cap * sizeof(T));
+    const bool idle = wait_device();
+    dev_free(c, buf, cap * sizeof(T), idle);
     buf = nullptr;
     cap = 0;
   }
@@ -208,7 +222,8 @@ int ensure_probs(gp_ctx* c, size_t n) {
   if (n <= c->probs_cap) return GP_OK;
   if (c->d_probs) {
     HIPTRY(hipStreamSynchronize(c->stream));
-    dev_free(c, c->d_probs, c->probs_cap * sizeof(Prob));
+    const bool idle = wait_device();
+    dev_free(c, c->d_probs, c->probs_cap * sizeof(Prob), idle);
     (void)hipHostFree(c->h_probs);
     c->d_probs = nullptr;
     c->h_probs = nullptr;
@@ -487,7 +502,8 @@ int ensure_rb_probs(gp_ctx* c, size_t n) {
   if (n <= c->rbp_cap) return GP_OK;
   if (c->d_rbp) {
     HIPTRY(hipStreamSynchronize(c->stream));
-    dev_free(c, c->d_rbp, c->rbp_cap * sizeof(RbProb));
+    const bool idle = wait_device();
+    dev_free(c, c->d_rbp, c->rbp_cap * sizeof(RbProb), idle);
     (void)hipHostFree(c->h_rbp);
     c->d_rbp = nullptr;
     c->h_rbp = nullptr;
@@ -1096,14 +1112,14 @@ int gp_ctx_profile_read(gp_ctx* c, int kind, gp_prof* out) {
 int gp_ctx_destroy(gp_ctx* c) {
   if (!c) return GP_OK;
   (void)hipSetDevice(c->device);
-  (void)hipStreamSynchronize(c->stream);
-  if (c->ws) dev_free(c, c->ws, c->ws_cap);
-  if (c->rhs) dev_free(c, c->rhs, c->rhs_cap * sizeof(double));
-  if (c->zbuf) dev_free(c, c->zbuf, c->zcap * sizeof(double));
-  if (c->pbuf) dev_free(c, c->pbuf, c->pcap * sizeof(int8_t));
-  if (c->d_probs) dev_free(c, c->d_probs, c->probs_cap * sizeof(Prob));
+  const bool idle = wait_device();
+  if (c->ws) dev_free(c, c->ws, c->ws_cap, idle);
+  if (c->rhs) dev_free(c, c->rhs, c->rhs_cap * sizeof(double), idle);
+  if (c->zbuf) dev_free(c, c->zbuf, c->zcap * sizeof(double), idle);
+  if (c->pbuf) dev_free(c, c->pbuf, c->pcap * sizeof(int8_t), idle);
+  if (c->d_probs) dev_free(c, c->d_probs, c->probs_cap * sizeof(Prob), idle);
   if (c->h_probs) (void)hipHostFree(c->h_probs);
-  if (c->d_rbp) dev_free(c, c->d_rbp, c->rbp_cap * sizeof(RbProb));
+  if (c->d_rbp) dev_free(c, c->d_rbp, c->rbp_cap * sizeof(RbProb), idle);
   if (c->h_rbp) (void)hipHostFree(c->h_rbp);
   if (c->h_rbst) (void)hipHostFree(c->h_rbst);
   release_kept(c);
@@ -1229,21 +1245,21 @@ int gp_op_destroy(gp_op* op) {
   if (!op) return GP_OK;
   gp_ctx* c = op->ctx;
   (void)hipSetDevice(c->device);
-  (void)hipStreamSynchronize(c->stream);
+  const bool idle = wait_device();
   const size_t NB = (size_t)op->K * (op->K + 1) / 2, N = (size_t)op->N;
-  op_free(op, op->nbr, 6 * N);
-  op_free(op, op->lin, N);
-  op_free(op, op->B64, NB * N);
-  op_free(op, op->B32, NB * N);
-  op_free(op, op->L64, NB * N);
-  op_free(op, op->P64, NB * N);
-  op_free(op, op->P32, NB * N);
-  op_free(op, op->d_bad, 1);
-  op_free(op, op->gmap, op->ncell);
-  op_free(op, op->tr_part, op->tr_cap);
+  op_free(op, op->nbr, 6 * N, idle);
+  op_free(op, op->lin, N, idle);
+  op_free(op, op->B64, NB * N, idle);
+  op_free(op, op->B32, NB * N, idle);
+  op_free(op, op->L64, NB * N, idle);
+  op_free(op, op->P64, NB * N, idle);
+  op_free(op, op->P32, NB * N, idle);
+  op_free(op, op->d_bad, 1, idle);
+  op_free(op, op->gmap, op->ncell, idle);
+  op_free(op, op->tr_part, op->tr_cap, idle);
   if (op->h_bad) (void)hipHostFree(op->h_bad);
   if (op->h_out) (void)hipHostFree(op->h_out);
-  rb_release(op);
+  rb_release(op, idle);
   delete op;
   return GP_OK;
 }
@@ -1430,7 +1446,7 @@ static int trace_reduce_impl(gp_op* op, int m, const int8_t* probes, const doubl
   const size_t need = (size_t)2 * m * op->K * op->ntiles + (size_t)2 * m * op->K + 1 + 2 * KMAX;
   if (need > op->tr_cap) {
     HIPTRY(hipStreamSynchronize(c->stream));
-    op_free(op, op->tr_part, op->tr_cap);
+    op_free(op, op->tr_part, op->tr_cap, wait_device());
     op->tr_cap = 0;
     if (int st = op_alloc(op, need, &op->tr_part)) return st;
     op->tr_cap = need;

@@ -33,17 +33,18 @@ struct gp_data {
 
 namespace {
 
-void release(gp_data* d) {
+// idle: nothing uses the dataset's blocks any more
+void release(gp_data* d, bool idle) {
   gp_ctx* c = d->op->ctx;
-  dev_free(c, d->X, d->nX * sizeof(double));
-  dev_free(c, d->G, d->nG * sizeof(double));
-  dev_free(c, d->YX, d->nYX * sizeof(double));
-  dev_free(c, d->Bt, d->nBt * sizeof(double));
-  dev_free(c, d->Dt, d->nDt * sizeof(double));
-  dev_free(c, d->YY, d->nYY * sizeof(double));
-  dev_free(c, d->dY, d->ndY * sizeof(double));
-  dev_free(c, d->dd, d->ndd * sizeof(double));
-  dev_free(c, d->Ja, d->nJa * sizeof(double));
+  dev_free(c, d->X, d->nX * sizeof(double), idle);
+  dev_free(c, d->G, d->nG * sizeof(double), idle);
+  dev_free(c, d->YX, d->nYX * sizeof(double), idle);
+  dev_free(c, d->Bt, d->nBt * sizeof(double), idle);
+  dev_free(c, d->Dt, d->nDt * sizeof(double), idle);
+  dev_free(c, d->YY, d->nYY * sizeof(double), idle);
+  dev_free(c, d->dY, d->ndY * sizeof(double), idle);
+  dev_free(c, d->dd, d->ndd * sizeof(double), idle);
+  dev_free(c, d->Ja, d->nJa * sizeof(double), idle);
   delete d;
 }
 
@@ -86,7 +87,7 @@ int gp_data_create(gp_op* op, int T, int P, const double* X_host, const double* 
       (st = dev_alloc(c, d->nYY * sizeof(double), (void**)&d->YY)) ||
       (st = dev_alloc(c, d->ndY * sizeof(double), (void**)&d->dY)) ||
       (st = dev_alloc(c, d->ndd * sizeof(double), (void**)&d->dd))) {
-    release(d);
+    release(d, true);
     return st;
   }
   std::vector<double> Xp(d->nX, 0.0);
@@ -96,8 +97,7 @@ int gp_data_create(gp_op* op, int T, int P, const double* X_host, const double* 
     e = launch_data_tensors(c->stream, T, K, P, N, d->X, Y, d->G, d->YX, d->Bt, d->Dt, d->YY, d->dY, d->dd);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) {
-    (void)hipStreamSynchronize(c->stream);
-    release(d);
+    release(d, wait_device());
     return fail(GP_ERR_DEVICE, std::string("data tensors: ") + hipGetErrorString(e));
   }
   *out = d;
@@ -357,8 +357,7 @@ int gp_data_destroy(gp_data* d) {
   BusyGuard guard(c);
   if (!guard.ok) return fail(GP_ERR_BUSY, "context busy");
   (void)set_device(c);
-  (void)hipStreamSynchronize(c->stream);
-  release(d);
+  release(d, wait_device());
   return GP_OK;
 }
 

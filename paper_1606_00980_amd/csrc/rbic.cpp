@@ -167,9 +167,9 @@ RbDev rb_dev(const gp_op* op) {
   return v;
 }
 
-void rb_release(gp_op* op) {
+void rb_release(gp_op* op, bool idle) {
   if (!op->rb) return;
-  for (auto& a : op->rb->allocs) dev_free(op->ctx, a.first, a.second);
+  for (auto& a : op->rb->allocs) dev_free(op->ctx, a.first, a.second, idle);
   if (op->rb->h_bad) (void)hipHostFree(op->rb->h_bad);
   delete op->rb;
   op->rb = nullptr;
@@ -180,7 +180,7 @@ namespace {
 int rb_lists(gp_op* op) {
   if (op->rb) return GP_OK;
   if (int st = build_lists(op)) {
-    rb_release(op);
+    rb_release(op, wait_device());
     return st;
   }
   return GP_OK;

@@ -237,7 +237,12 @@ void prof_add(gp_ctx* c, int kind, double units, double bytes);
 
 int set_device(gp_ctx* c);
 int dev_alloc(gp_ctx* c, size_t bytes, void** p);
-void dev_free(gp_ctx* c, void* p, size_t bytes);
+// keep: nothing uses the block any more, so the context may hand it out again
+// (else it goes back to the device at once)
+void dev_free(gp_ctx* c, void* p, size_t bytes, bool keep = true);
+// Waits for all streams of the current device; false where that cannot be done
+// (a stream capture under way).
+bool wait_device();
 // gives the kept device blocks back to the device
 void release_kept(gp_ctx* c);
 OpDev op_dev(const gp_op* op);
@@ -271,7 +276,7 @@ int rb_build_ops(gp_ctx* c, const std::vector<gp_op*>& ops);
 // Reads the set-up's positive-definiteness flag if it has not been read yet
 // (waits for the stream); GP_ERR_NOT_SPD when a block failed.
 int rb_check_built(gp_op* op);
-void rb_release(gp_op* op);
+void rb_release(gp_op* op, bool idle);   // idle: nothing uses its blocks any more
 RbDev rb_dev(const gp_op* op);
 // One caller batch item of an operator: R right-hand sides b, solutions x,
 // and where their statistics go.

@@ -53,3 +53,62 @@ def test_datasets_come_and_go_within_the_budget(g, slack):
     g.gp_op_destroy(op)
     assert g.gp_ctx_memory(ctx)[0] == 0
     g.gp_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("how", ["left stream", "graph"])
+def test_an_operator_given_back_while_its_product_is_queued(g, how):
+    """A product queued behind other work on a stream that the context has left
+    (or replayed from a caller's graph there), its operator destroyed and
+    another of the same sizes made with other blocks: the product is the first
+    operator's, bitwise, in every replay."""
+    import torch
+    dims, K, R = (40, 36, 24), 6, 4
+    N = dims[0] * dims[1] * dims[2]
+    r = np.random.default_rng(5)
+    mask = np.ones(dims[::-1], dtype=np.uint8)
+    x = torch.from_numpy(r.standard_normal((R, K, N))).cuda()
+    eye = torch.eye(K, dtype=torch.float64, device="cuda")
+    busy = torch.randn((4096, 4096), device="cuda")
+    first, other = torch.cuda.Stream(), torch.cuda.Stream()
+    ctx = g.gp_ctx_create(0, first.cuda_stream, 0)
+
+    def operator(scale):
+        op = g.gp_op_create(ctx, mask, 6, K)
+        blocks = (scale * eye)[None].repeat(N, 1, 1).contiguous()
+        torch.cuda.synchronize()
+        g.gp_op_set_blocks(op, blocks)
+        g.gp_op_set_alpha(op, np.full(K, scale))
+        return op
+
+    op = operator(1.0)
+    want, y = torch.empty_like(x), torch.zeros_like(x)
+    torch.cuda.synchronize()
+    g.gp_apply(op, R, x, want)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    if how == "graph":
+        with torch.cuda.graph(graph, stream=other):
+            g.gp_ctx_set_stream(ctx, torch.cuda.current_stream().cuda_stream)
+            g.gp_apply(op, R, x, y)
+        y.zero_()
+        torch.cuda.synchronize()
+        for _ in range(3):
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(y, want)
+            y.zero_()
+        torch.cuda.synchronize()
+    with torch.cuda.stream(first):
+        for _ in range(20):
+            busy = busy @ busy * 1e-4
+        if how == "graph":
+            graph.replay()
+        else:
+            g.gp_apply(op, R, x, y)
+    g.gp_ctx_set_stream(ctx, other.cuda_stream)
+    g.gp_op_destroy(op)
+    op = operator(7.0)
+    torch.cuda.synchronize()
+    assert torch.equal(y, want)
+    g.gp_op_destroy(op)
+    g.gp_ctx_destroy(ctx)
