@@ -177,7 +177,8 @@ int gp_ctx_set_stream(gp_ctx* ctx, void* hip_stream);
  * Device blocks given back (a destroyed dataset, temporary buffers) are kept
  * for later allocations of the same size, at most 16 blocks and 1 GiB per
  * context and inside its budget; they are not counted here and go back to the
- * device when another allocation needs the room and with the context.       */
+ * device when an allocation of any context of this library on the device needs
+ * the room and with the context.                                            */
 int gp_ctx_memory(const gp_ctx* ctx, size_t* used, size_t* budget);
 int gp_ctx_destroy(gp_ctx* ctx);
 /* gp_ctx_profile: enable (1) or disable (0) per-launch event timing on this

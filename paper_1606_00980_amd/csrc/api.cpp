@@ -75,8 +75,9 @@ int set_device(gp_ctx* c) {
 // shape then allocate nothing (the K = 15 whole-brain dataset, nine buffers of
 // 230 MB in all, took 1.3 to 3.5 ms of a 1.5 to 3.8 ms pass in these calls).
 // At most KEPT_BLOCKS blocks and KEPT_BYTES are kept, counted against the
-// context's budget: a request that would exceed it (or that the device cannot
-// place) releases them first, and gp_ctx_destroy releases all.
+// context's budget: a request that would exceed it releases them first, one
+// that the device cannot place those of every context on it (the serving
+// loop's own allocations too), and gp_ctx_destroy releases all.
 // A kept block may be written by the next call on the context's stream, so
 // nothing may use it any more.  Temporaries of a call that has waited for its
 // stream can be given back as they are.  An operator's, a dataset's and the
@@ -93,37 +94,76 @@ void release_locked(gp_ctx* c) {
 }
 }  // namespace
 
-void release_kept(gp_ctx* c) {
-  std::lock_guard<std::mutex> lk(c->kept_mu);
+// Every live context, for the allocation that the device cannot place: its own
+// and the other contexts' kept blocks on that device go back first.
+namespace {
+struct Live {
+  std::mutex mu;
+  std::vector<gp_ctx*> ctxs;
+};
+Live& live() {   // never destroyed: a context may outlive the library's statics
+  static Live* l = new Live();
+  return *l;
+}
+}  // namespace
+
+void ctx_enter(gp_ctx* c) {
+  std::lock_guard<std::mutex> lk(live().mu);
+  live().ctxs.push_back(c);
+}
+
+void ctx_leave(gp_ctx* c) {
+  std::lock_guard<std::mutex> lk(live().mu);
+  std::vector<gp_ctx*>& v = live().ctxs;
+  v.erase(std::remove(v.begin(), v.end(), c), v.end());
+  std::lock_guard<std::mutex> lk2(c->kept_mu);
   release_locked(c);
+}
+
+hipError_t device_malloc(gp_ctx* c, void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipSuccess) return e;
+  (void)hipGetLastError();
+  bool any = false;
+  {
+    std::lock_guard<std::mutex> lk(live().mu);
+    for (gp_ctx* o : live().ctxs) {
+      std::lock_guard<std::mutex> lk2(o->kept_mu);
+      if (o->device != c->device || o->kept.empty()) continue;
+      release_locked(o);
+      any = true;
+    }
+  }
+  if (!any) return e;
+  e = hipMalloc(p, bytes);
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
 }
 
 int dev_alloc(gp_ctx* c, size_t bytes, void** p) {
   bytes = align_up(std::max<size_t>(bytes, 1), 256);
-  std::lock_guard<std::mutex> lk(c->kept_mu);
-  if (c->budget && c->used + bytes > c->budget)
-    return fail(GP_ERR_OOM, "HBM budget exceeded: need " + std::to_string(bytes) + " more bytes, " +
-                                std::to_string(c->budget - c->used) + " left");
-  for (size_t i = c->kept.size(); i-- > 0;) {
-    if (c->kept[i].second != bytes) continue;
-    *p = c->kept[i].first;
-    c->kept.erase(c->kept.begin() + (long)i);
-    c->kept_bytes -= bytes;
+  {
+    std::lock_guard<std::mutex> lk(c->kept_mu);
+    if (c->budget && c->used + bytes > c->budget)
+      return fail(GP_ERR_OOM, "HBM budget exceeded: need " + std::to_string(bytes) + " more bytes, " +
+                                  std::to_string(c->budget - c->used) + " left");
+    for (size_t i = c->kept.size(); i-- > 0;) {
+      if (c->kept[i].second != bytes) continue;
+      *p = c->kept[i].first;
+      c->kept.erase(c->kept.begin() + (long)i);
+      c->kept_bytes -= bytes;
+      c->used += bytes;
+      return GP_OK;
+    }
+    if (c->budget && c->used + c->kept_bytes + bytes > c->budget) release_locked(c);
     c->used += bytes;
-    return GP_OK;
   }
-  if (c->budget && c->used + c->kept_bytes + bytes > c->budget) release_locked(c);
-  hipError_t e = hipMalloc(p, bytes);
-  if (e != hipSuccess && !c->kept.empty()) {
-    (void)hipGetLastError();
-    release_locked(c);
-    e = hipMalloc(p, bytes);
-  }
+  const hipError_t e = device_malloc(c, p, bytes);
   if (e != hipSuccess) {
-    (void)hipGetLastError();
+    std::lock_guard<std::mutex> lk(c->kept_mu);
+    c->used -= bytes;
     return fail(GP_ERR_OOM, std::string("hipMalloc failed: ") + hipGetErrorString(e));
   }
-  c->used += bytes;
   return GP_OK;
 }
 
@@ -1067,6 +1107,7 @@ int gp_ctx_create(int device, void* hip_stream, size_t hbm_budget, gp_ctx** out)
     delete c;
     return fail(GP_ERR_DEVICE, "could not create the capture stream");
   }
+  ctx_enter(c);
   *out = c;
   return GP_OK;
 }
@@ -1122,7 +1163,7 @@ int gp_ctx_destroy(gp_ctx* c) {
   if (c->d_rbp) dev_free(c, c->d_rbp, c->rbp_cap * sizeof(RbProb), idle);
   if (c->h_rbp) (void)hipHostFree(c->h_rbp);
   if (c->h_rbst) (void)hipHostFree(c->h_rbst);
-  release_kept(c);
+  ctx_leave(c);
   for (hipEvent_t e : c->evpool) (void)hipEventDestroy(e);
   for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second.exec);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);

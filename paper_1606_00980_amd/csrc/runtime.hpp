@@ -243,8 +243,9 @@ void dev_free(gp_ctx* c, void* p, size_t bytes, bool keep = true);
 // Waits for all streams of the current device; false where that cannot be done
 // (a stream capture under way).
 bool wait_device();
-// gives the kept device blocks back to the device
-void release_kept(gp_ctx* c);
+// hipMalloc on the context's device; where it cannot place the block, once more
+// after the kept blocks of every context there have gone back.
+hipError_t device_malloc(gp_ctx* c, void** p, size_t bytes);
 OpDev op_dev(const gp_op* op);
 int build_precond(gp_op* op, int pc);
 // Grow the context's solver workspace to at least `bytes`.

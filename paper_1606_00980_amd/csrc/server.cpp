@@ -206,14 +206,9 @@ char* arena_take(gp_server* s, size_t n) {
     if (s->slab_bytes + n > s->cfg.hbm_budget) return nullptr;
     size_t want = std::max(n, std::min(SLAB_BYTES, s->cfg.hbm_budget - s->slab_bytes));
     char* m = nullptr;
-    if (hipMalloc((void**)&m, want) != hipSuccess) {
-      (void)hipGetLastError();
-      release_kept(s->ctx);
+    if (device_malloc(s->ctx, (void**)&m, want) != hipSuccess) {
       want = n;
-      if (hipMalloc((void**)&m, want) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-      }
+      if (device_malloc(s->ctx, (void**)&m, want) != hipSuccess) return nullptr;
     }
     s->slabs.emplace_back(m, want);
     s->slab_bytes += want;
@@ -308,10 +303,10 @@ int ensure_descriptors(gp_server* s, int n) {
   s->h_rbp = nullptr;
   s->probs_cap = std::max(n, 2 * s->probs_cap);
   if (s->rb) {
-    HIPTRY(hipMalloc((void**)&s->d_rbp, (size_t)s->probs_cap * sizeof(RbProb)));
+    HIPTRY(device_malloc(s->ctx, (void**)&s->d_rbp, (size_t)s->probs_cap * sizeof(RbProb)));
     HIPTRY(hipHostMalloc((void**)&s->h_rbp, (size_t)s->probs_cap * sizeof(RbProb), hipHostMallocDefault));
   } else {
-    HIPTRY(hipMalloc((void**)&s->d_probs, (size_t)s->probs_cap * sizeof(Prob)));
+    HIPTRY(device_malloc(s->ctx, (void**)&s->d_probs, (size_t)s->probs_cap * sizeof(Prob)));
     HIPTRY(hipHostMalloc((void**)&s->h_probs, (size_t)s->probs_cap * sizeof(Prob), hipHostMallocDefault));
   }
   return GP_OK;
@@ -722,7 +717,7 @@ int gp_server_create(gp_ctx* ctx, int nops, gp_op* const* ops, const double* con
   }
   if (hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) != hipSuccess)
     return bail(fail(GP_ERR_DEVICE, "could not create the server stream"));
-  if (hipMalloc((void**)&s->d_states, (size_t)c.max_active_rhs * sizeof(RhsState)) != hipSuccess)
+  if (device_malloc(s->ctx, (void**)&s->d_states, (size_t)c.max_active_rhs * sizeof(RhsState)) != hipSuccess)
     return bail(fail(GP_ERR_OOM, "could not allocate the state table"));
   if (hipHostMalloc((void**)&s->h_states, (size_t)c.max_active_rhs * sizeof(RhsState), hipHostMallocDefault) !=
       hipSuccess)

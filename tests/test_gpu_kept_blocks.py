@@ -112,3 +112,32 @@ def test_an_operator_given_back_while_its_product_is_queued(g, how):
     assert torch.equal(y, want)
     g.gp_op_destroy(op)
     g.gp_ctx_destroy(ctx)
+
+
+def test_an_allocation_that_fails_takes_every_contexts_kept_blocks(g):
+    """A context asked for more than the device has fails with GP_ERR_OOM, after
+    the blocks that another context keeps have gone back to the device."""
+    import torch
+    dims, K, R = (64, 64, 32), 6, 65535
+    mask = np.ones(dims[::-1], dtype=np.uint8)
+    N = mask.size
+    stream = torch.cuda.current_stream().cuda_stream
+    keeper, other = g.gp_ctx_create(0, stream, 0), g.gp_ctx_create(0, stream, 0)
+    blocks = torch.eye(K, dtype=torch.float64, device="cuda")[None].repeat(N, 1, 1).contiguous()
+    op = g.gp_op_create(other, mask, 6, K)
+    g.gp_op_set_blocks(op, blocks)
+    g.gp_op_set_alpha(op, np.ones(K))
+    bw = torch.zeros((K, N), dtype=torch.float64, device="cuda")
+    w = torch.zeros(1, dtype=torch.float64, device="cuda")   # not reached
+    g.gp_op_destroy(g.gp_op_create(keeper, mask, 6, K))
+    kept = 8 * N * K * (K + 1) // 2 * 4   # its blocks, factors and preconditioner, FP64 and FP32
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    assert R * K * N * 8 > torch.cuda.mem_get_info()[1]
+    st = g.lib.gp_sample(op, R, bw.data_ptr(), None, None, w.data_ptr(), None, None)
+    assert st == g.GP_ERR_OOM
+    assert torch.cuda.mem_get_info()[0] >= before + kept
+    assert g.gp_ctx_memory(keeper)[0] == 0
+    g.gp_op_destroy(op)
+    g.gp_ctx_destroy(keeper)
+    g.gp_ctx_destroy(other)
