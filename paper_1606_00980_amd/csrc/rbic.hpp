@@ -442,7 +442,7 @@ __global__ __launch_bounds__(SETUP_WG) void k_rb_setup_black(RbDev rb, const dou
   // gathers of a chunk's six neighbours are in flight together (a missing
   // neighbour reads entry 0 and is dropped by a select).  Neighbour by
   // neighbour behind a branch, with one neighbour's gathers in flight: 176 us
-  // at K = 15, N = 52,740 (52 so), 17 at K = 6 (12), 203 at K = 10,
+  // at K = 15, N = 52,740 (56 so), 17 at K = 6 (12), 203 at K = 10,
   // N = 289,592 (100).
   const Slab<double> Ps(rb.P64, NB, rb.NR);
   constexpr int SE = K <= 11 ? 8 : 4;

@@ -6,12 +6,23 @@
 
 namespace gp {
 
+// v / l from inv = 1 / l correctly rounded: the product's exact remainder times
+// inv corrects it to the rounding of the division itself (Markstein 1990), in
+// five instructions instead of a dozen.  v * inv alone is up to an ulp off:
+// the factors were 10 to 17 % further from 64-bit exact ones, their inverses
+// 8 to 22 %.  An overflowed product or an infinite l (inv = 0) has no finite
+// remainder and gives v * inv, which is v / l there.
+__device__ __forceinline__ double div_by(double v, double l, double inv) {
+  const double q = v * inv, rem = __builtin_fma(-q, l, v);
+  return __builtin_isfinite(rem) ? __builtin_fma(rem, inv, q) : q;
+}
+
 // Replaces the packed SPD block a by its inverse and returns whether every
 // pivot was positive and finite.  A failed pivot is replaced by one so that
-// the arithmetic stays finite.  The diagonal holds reciprocals from the
-// factorisation on, so that a block costs K divisions (separate arrays for L,
-// its inverse and the result and a division per entry: the red set-up took
-// 34 us at K = 15, N = 52,740; 24 so).
+// the arithmetic stays finite.  A row or column divides by one pivot, so that
+// a block costs 2 K divisions (separate arrays for L, its inverse and the
+// result and a division per entry: the red set-up took 34 us at K = 15,
+// N = 52,740; 29 so).
 template <int K>
 __device__ inline bool spd_inverse(double (&a)[K * (K + 1) / 2]) {
   bool ok = true;
@@ -21,26 +32,28 @@ __device__ inline bool spd_inverse(double (&a)[K * (K + 1) / 2]) {
 #pragma unroll
     for (int l = 0; l < j; ++l) dj -= a[pk(j, l)] * a[pk(j, l)];
     ok = ok && (dj > 0.0) && (dj == dj);
-    const double inv = 1.0 / sqrt(dj > 0.0 ? dj : 1.0);
-    a[pk(j, j)] = inv;
+    const double ljj = sqrt(dj > 0.0 ? dj : 1.0), inv = 1.0 / ljj;
+    a[pk(j, j)] = ljj;
 #pragma unroll
     for (int i = j + 1; i < K; ++i) {
       double v = a[pk(i, j)];
 #pragma unroll
       for (int l = 0; l < j; ++l) v -= a[pk(i, l)] * a[pk(j, l)];
-      a[pk(i, j)] = v * inv;
+      a[pk(i, j)] = div_by(v, ljj, inv);
     }
   }
   // L^{-1}, row by row (row i from row i of L and the rows of L^{-1} above it)
 #pragma unroll
-  for (int i = 1; i < K; ++i) {
+  for (int i = 0; i < K; ++i) {
+    const double lii = a[pk(i, i)], inv = 1.0 / lii;
 #pragma unroll
     for (int j = 0; j < i; ++j) {
       double v = 0.0;
 #pragma unroll
       for (int l = j; l < i; ++l) v -= a[pk(i, l)] * a[pk(l, j)];
-      a[pk(i, j)] = v * a[pk(i, i)];
+      a[pk(i, j)] = div_by(v, lii, inv);
     }
+    a[pk(i, i)] = inv;
   }
   // L^{-T} L^{-1}, row i from rows i and below
 #pragma unroll
@@ -152,7 +165,7 @@ __device__ inline void pack_factor(int N, int n, double (&a)[K * (K + 1) / 2], d
         double v = a[pk(i, j)];
 #pragma unroll
         for (int l = 0; l < j; ++l) v -= a[pk(i, l)] * a[pk(j, l)];
-        a[pk(i, j)] = v * inv;
+        a[pk(i, j)] = div_by(v, ljj, inv);
       }
     }
   } else {
