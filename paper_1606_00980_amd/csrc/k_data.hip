@@ -21,6 +21,8 @@
 // [N][K][K] (both triangles) and b_w [K][N].
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "common.hpp"
 #include "launch.hpp"
 #include "pcg.hpp"
@@ -123,11 +125,17 @@ __global__ __launch_bounds__(DT) void k_data_table(int K, int P, const double* _
 // wave-uniform: one 32-byte scalar load per scan.
 // Bound: the FP64 multiply-adds, (2P + 1) K T per voxel (about 30 us at
 // N = 52,740, K = 15, T = 200, P = 3), and the scalar loads of the design in
-// front of them.  120 us there; a workgroup per output entry, which read Y
+// front of them.  133 us there; a workgroup per output entry, which read Y
 // once per entry (208 passes), took 2,427 us.
+// The running sums are added to the totals every 28 scans or so (tensor_fold).
+// In one chain over all scans each addition rounds at the size of the whole
+// sum: b_w was 3.7e-16 off (rms, relative; T = 200, K = 15; the kernel of an
+// entry per workgroup 3.7e-16 as well) and 1.8e-16 so, the residual sums
+// 1.3e-11 and 5e-12, for 13 us.
 // blockIdx.y = regressor chunk; the last one forms YY, dY and dd.
 constexpr int TENSOR_KC = 4;
 constexpr int TENSOR_WG = 64;
+constexpr int tensor_fold(int W) { return W >= 28 ? 1 : 28 / W; }   // in groups of W scans
 
 template <int P>
 __device__ __forceinline__ void tensor_cross(int T, int K, int Ks, int N, int n, int k0, const double* __restrict__ X,
@@ -135,11 +143,22 @@ __device__ __forceinline__ void tensor_cross(int T, int K, int Ks, int N, int n,
                                              double* __restrict__ Bt, double* __restrict__ Dt) {
   constexpr int W = 2 * P + 1, KC = TENSOR_KC;
   const double* y = Y + n;
-  double acc[W][KC];   // acc[d + P][c] = sum_j y[j - d] X[j][k0 + c]
+  // tot[d + P][c] = sum_j y[j - d] X[j][k0 + c], acc the part of the last scans
+  constexpr int FOLD = tensor_fold(W);
+  double acc[W][KC], tot[W][KC];
 #pragma unroll
   for (int d = 0; d < W; ++d)
 #pragma unroll
-    for (int c = 0; c < KC; ++c) acc[d][c] = 0.0;
+    for (int c = 0; c < KC; ++c) acc[d][c] = tot[d][c] = 0.0;
+  auto fold = [&]() {
+#pragma unroll
+    for (int d = 0; d < W; ++d)
+#pragma unroll
+      for (int c = 0; c < KC; ++c) {
+        tot[d][c] += acc[d][c];
+        acc[d][c] = 0.0;
+      }
+  };
   const int jend = T - 1 - P;
   if (jend >= P) {
     // y[m] of the window sits in ring[m % W]
@@ -164,19 +183,24 @@ __device__ __forceinline__ void tensor_cross(int T, int K, int Ks, int N, int n,
     };
     int j = P;
 #pragma unroll 1
-    for (; j + W - 1 <= jend; j += W) {
-      double cur[W];
+    while (j + W - 1 <= jend) {
+#pragma unroll 1
+      for (int f = 0; f < FOLD && j + W - 1 <= jend; ++f, j += W) {
+        double cur[W];
 #pragma unroll
-      for (int i = 0; i < W; ++i) cur[i] = nxt[i];
-      // the next W scans are loaded while these are used
+        for (int i = 0; i < W; ++i) cur[i] = nxt[i];
+        // the next W scans are loaded while these are used
 #pragma unroll
-      for (int i = 0; i < W; ++i) nxt[i] = y[(size_t)min(j + W + P + i, T - 1) * N];
+        for (int i = 0; i < W; ++i) nxt[i] = y[(size_t)min(j + W + P + i, T - 1) * N];
 #pragma unroll
-      for (int i = 0; i < W; ++i) scan(j, i, cur[i]);
+        for (int i = 0; i < W; ++i) scan(j, i, cur[i]);
+      }
+      fold();
     }
 #pragma unroll
     for (int i = 0; i < W - 1; ++i)
       if (j + i <= jend) scan(j, i, nxt[i]);
+    fold();
   }
   // the scans at the ends: y[0 .. 2P) and y[T - 2P .. T), where they exist
   constexpr int P2 = P > 0 ? 2 * P : 1, P1 = P > 0 ? P : 1;
@@ -195,13 +219,13 @@ __device__ __forceinline__ void tensor_cross(int T, int K, int Ks, int N, int n,
     }
   auto sum = [&](auto A, auto B, int c) {
     constexpr int a = decltype(A)::v, b = decltype(B)::v;
-    double s = acc[a - b + P][c];
+    double s = 0.0;
 #pragma unroll
     for (int i = 0; i < P; ++i) {
       if (i >= P - b && i <= T - 1 - b) s += yl[i + b - a >= 0 ? i + b - a : 0] * xl[i][c];
       if (i >= b && T - 1 - i >= P) s += yh[i - b + a >= 0 ? i - b + a : 0] * xh[i][c];
     }
-    return s;
+    return tot[a - b + P][c] + s;
   };
 #pragma unroll
   for (int c = 0; c < KC; ++c) {
@@ -224,34 +248,45 @@ __device__ __forceinline__ void tensor_auto(int T, int N, int n, const double* _
                                             double* __restrict__ dY, double* __restrict__ dd) {
   constexpr int W = P + 1;
   const double* y = Y + n;
-  double acc[W][W], ring[W];   // acc[a][b], a <= b: sum_t y[t - a] y[t - b]
+  double acc[W][W], tot[W][W], ring[W];   // tot[a][b], a <= b: sum_t y[t - a] y[t - b], acc the part of the last scans
 #pragma unroll
   for (int a = 0; a < W; ++a)
 #pragma unroll
-    for (int b = 0; b < W; ++b) acc[a][b] = 0.0;
+    for (int b = 0; b < W; ++b) acc[a][b] = tot[a][b] = 0.0;
 #pragma unroll
   for (int m = 0; m < P; ++m) ring[m] = y[(size_t)m * N];
-  for (int t = P; t < T; t += W) {
-    double cur[W];
+#pragma unroll 1
+  for (int t = P; t < T;) {
+#pragma unroll 1
+    for (int f = 0; f < tensor_fold(W) && t < T; ++f, t += W) {
+      double cur[W];
 #pragma unroll
-    for (int i = 0; i < W; ++i) cur[i] = y[(size_t)min(t + i, T - 1) * N];
+      for (int i = 0; i < W; ++i) cur[i] = y[(size_t)min(t + i, T - 1) * N];
 #pragma unroll
-    for (int i = 0; i < W; ++i) {
-      if (t + i >= T) break;
-      ring[(P + i) % W] = cur[i];
+      for (int i = 0; i < W; ++i) {
+        if (t + i >= T) break;
+        ring[(P + i) % W] = cur[i];
 #pragma unroll
-      for (int a = 0; a < W; ++a)
+        for (int a = 0; a < W; ++a)
 #pragma unroll
-        for (int b = a; b < W; ++b) acc[a][b] += ring[(P + i - a + W) % W] * ring[(P + i - b + W) % W];
+          for (int b = a; b < W; ++b) acc[a][b] += ring[(P + i - a + W) % W] * ring[(P + i - b + W) % W];
+      }
     }
-  }
-  YY[n] = acc[0][0];
 #pragma unroll
-  for (int p = 0; p < P; ++p) dY[(size_t)p * N + n] = acc[0][p + 1];
+    for (int a = 0; a < W; ++a)
+#pragma unroll
+      for (int b = a; b < W; ++b) {
+        tot[a][b] += acc[a][b];
+        acc[a][b] = 0.0;
+      }
+  }
+  YY[n] = tot[0][0];
+#pragma unroll
+  for (int p = 0; p < P; ++p) dY[(size_t)p * N + n] = tot[0][p + 1];
 #pragma unroll
   for (int p = 0; p < P; ++p)
 #pragma unroll
-    for (int q = 0; q < P; ++q) dd[((size_t)p * P + q) * N + n] = acc[(p < q ? p : q) + 1][(p < q ? q : p) + 1];
+    for (int q = 0; q < P; ++q) dd[((size_t)p * P + q) * N + n] = tot[(p < q ? p : q) + 1][(p < q ? q : p) + 1];
 }
 
 template <int P>
@@ -324,7 +359,7 @@ __device__ __forceinline__ void rhs_entries(int K, int P, int N, int n, int k0, 
   for (int c = 0; c < ASM_KC; ++c) {
     const int k = k0 + c;
     if (k >= K) break;
-    double acc = YX[(size_t)k * N + n];
+    double acc = 0.0;   // the small terms first
 #pragma unroll
     for (int p = 0; p < PMAX; ++p) {
       if (p < P) {
@@ -339,7 +374,7 @@ __device__ __forceinline__ void rhs_entries(int K, int P, int N, int n, int k0, 
         }
       }
     }
-    bw[(size_t)k * N + n] = lam * acc;
+    bw[(size_t)k * N + n] = lam * (YX[(size_t)k * N + n] + acc);
   }
 }
 
@@ -370,12 +405,12 @@ __global__ __launch_bounds__(ASM_WG) void k_data_assemble(int P, int N, int Ns, 
   }
   auto entry = [&](int e) {
     const double* t = tab + e * TAB;
-    double g = t[0];
+    double g = 0.0;
 #pragma unroll
     for (int p = 0; p < PMAX; ++p) g += t[1 + p] * m1[p];
 #pragma unroll
     for (int i = 0; i < ASM_NQ; ++i) g += t[1 + PMAX + i] * m2[i];
-    return lam * g;
+    return lam * (t[0] + g);
   };
   if constexpr (K <= KREG) {
 #pragma unroll
@@ -407,7 +442,9 @@ __global__ __launch_bounds__(ASM_WG) void k_data_rhs(int K, int P, int N, int Ns
 // triangle with the wave-uniform coefficient table (scalar loads) and the
 // lane's monomials of a, w in an LDS column of the lane; the parts linear in w
 // come from the draws' sums of w_k {1, a_p, a_p a_q}, so each tensor entry is
-// loaded once for all draws.
+// loaded once for all draws (ahead of their loop: 64 us, behind it 77).  The
+// terms nearly cancel (Y'Y is 10^4 times the residual sum), so the additions'
+// rounding errors are summed beside them.
 // Bound: FP64 multiply-adds, K(K+1)/2 (P+1)(P+2)/2 per draw and voxel (about
 // 15 us at N = 52,740, K = 15, P = 3, five draws).  Measured there 64 us; one
 // thread per voxel over both triangles and all lag pairs, with w and a in
@@ -426,14 +463,20 @@ __global__ __launch_bounds__(64 * RSS_WAVES) void k_data_rss(int K, int N, int N
                                                              const double* __restrict__ A, double u1, double u2t,
                                                              double* __restrict__ rss_out, double* __restrict__ scale,
                                                              double* __restrict__ mean) {
-  extern __shared__ double sw[];   // [K][64 * RSS_WAVES]: w of the lane
-  __shared__ double part[RSS_WAVES][64];
+  extern __shared__ double sw[];   // [K, at least 2][64 * RSS_WAVES]: w of the lane, at the end its sum
   constexpr int P1 = P > 0 ? P : 1, NQ = P * (P + 1) / 2, Q1 = NQ > 0 ? NQ : 1, LDW = 64 * RSS_WAVES;
   const int lane = threadIdx.x % 64, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const int n = blockIdx.x * 64 + lane;
   const int nn = n < N ? n : N - 1;   // lanes past the end compute on the last voxel and store nothing
   double* w = sw + threadIdx.x;
-  double tot = 0.0;
+  // tot + lo: what an addition to tot rounds away goes to lo
+  double tot = 0.0, lo = 0.0;
+  auto add = [&](double v) {
+#pragma clang fp contract(off)
+    const double t = tot + v, b = t - tot;
+    lo += (tot - (t - b)) + (v - b);
+    tot = t;
+  };
   for (int j = 0; j < Ns; ++j) {
     double a[P1], aa[Q1];
 #pragma unroll
@@ -447,14 +490,14 @@ __global__ __launch_bounds__(64 * RSS_WAVES) void k_data_rss(int K, int N, int N
     // coefficient of w_k w_l for packed entry e
     auto coef = [&](int e) {
       const double* t = Tab + (size_t)e * TAB;
-      double g = t[0];
+      double g = 0.0;
 #pragma unroll
       for (int p = 0; p < P; ++p) g += t[1 + p] * a[p];
 #pragma unroll
       for (int p = 0; p < P; ++p)
 #pragma unroll
         for (int q = p; q < P; ++q) g += t[1 + PMAX + tab_pair(p, q, PMAX)] * aa[tab_pair(p, q, P)];
-      return g;
+      return t[0] + g;
     };
     for (int k = wv; k < K; k += RSS_WAVES) {
       const double wk = w[k * LDW];
@@ -462,10 +505,10 @@ __global__ __launch_bounds__(64 * RSS_WAVES) void k_data_rss(int K, int N, int N
       double s = 0.0;
 #pragma unroll 4
       for (int l = 0; l < k; ++l) s += coef(e0 + l) * w[l * LDW];
-      tot += wk * (2.0 * s + coef(e0 + k) * wk);
+      add(wk * (2.0 * s + coef(e0 + k) * wk));
     }
     if (wv == 0) {
-      double v = YY[nn];
+      double v = 0.0;
 #pragma unroll
       for (int p = 0; p < P; ++p) {
         v -= 2.0 * dY[(size_t)p * N + nn] * a[p];
@@ -473,10 +516,22 @@ __global__ __launch_bounds__(64 * RSS_WAVES) void k_data_rss(int K, int N, int N
         for (int q = p; q < P; ++q)
           v += (p == q ? 1.0 : 2.0) * dd[((size_t)p * P + q) * N + nn] * aa[tab_pair(p, q, P)];
       }
-      tot += v;
+      add(YY[nn]);
+      add(v);
     }
   }
   for (int k = wv; k < K; k += RSS_WAVES) {
+    const double yx = YX[(size_t)k * N + nn];
+    double bt[P1], dt[Q1];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      bt[p] = Bt[((size_t)p * K + k) * N + nn];
+#pragma unroll
+      for (int q = p; q < P; ++q) {
+        dt[tab_pair(p, q, P)] = Dt[(((size_t)p * K + k) * P + q) * N + nn];
+        if (q != p) dt[tab_pair(p, q, P)] += Dt[(((size_t)q * K + k) * P + p) * N + nn];
+      }
+    }
     double m0 = 0.0, m1[P1] = {0.0}, m2[Q1] = {0.0};
 #pragma unroll 2
     for (int j = 0; j < Ns; ++j) {
@@ -493,26 +548,26 @@ __global__ __launch_bounds__(64 * RSS_WAVES) void k_data_rss(int K, int N, int N
         for (int q = p; q < P; ++q) m2[tab_pair(p, q, P)] += wa * a[q];
       }
     }
-    double v = -YX[(size_t)k * N + nn] * m0;
+    double v = 0.0;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-      v += Bt[((size_t)p * K + k) * N + nn] * m1[p];
+      v += bt[p] * m1[p];
 #pragma unroll
-      for (int q = p; q < P; ++q) {
-        double d = Dt[(((size_t)p * K + k) * P + q) * N + nn];
-        if (q != p) d += Dt[(((size_t)q * K + k) * P + p) * N + nn];
-        v -= d * m2[tab_pair(p, q, P)];
-      }
+      for (int q = p; q < P; ++q) v -= dt[tab_pair(p, q, P)] * m2[tab_pair(p, q, P)];
     }
-    tot += 2.0 * v;
+    add(-2.0 * yx * m0);
+    add(2.0 * v);
   }
-  part[wv][lane] = tot;
+  w[0] = tot;
+  w[LDW] = lo;
   __syncthreads();
   if (wv != 0 || n >= N) return;
-  tot = part[0][lane];
 #pragma unroll
-  for (int i = 1; i < RSS_WAVES; ++i) tot += part[i][lane];
-  const double rss = tot / Ns;
+  for (int i = 1; i < RSS_WAVES; ++i) {
+    add(w[i * 64]);
+    lo += w[LDW + i * 64];
+  }
+  const double rss = (__builtin_isfinite(lo) ? tot + lo : tot) / Ns;   // (an infinite sum leaves no remainder)
   const double u1t = 1.0 / (0.5 * rss + 1.0 / u1);
   if (rss_out) rss_out[n] = rss;
   if (scale) scale[n] = u1t;
@@ -671,7 +726,7 @@ hipError_t launch_data_rss(hipStream_t s, int K, int P, int N, int Ns, const dou
                            double* mean) {
   const double* tab = G + data_table_at(K, P);
   const dim3 g((N + 63) / 64), b(64 * RSS_WAVES);
-  const size_t lds = (size_t)K * 64 * RSS_WAVES * sizeof(double);
+  const size_t lds = (size_t)std::max(K, 2) * 64 * RSS_WAVES * sizeof(double);
   switch (P) {
 #define X_P(PP)                                                                                                  \
   case PP:                                                                                                       \

@@ -124,3 +124,64 @@ def test_blocks_and_residual_sums_over_draws(g, ctx, torch_cuda, P, Ns, nx, K):
     assert np.allclose(out[2].cpu().numpy(), u1t * (0.5 * (T - P) + 0.1), rtol=1e-14, atol=0)
     g.gp_data_destroy(d)
     g.gp_op_destroy(op)
+
+
+@pytest.mark.parametrize("K,P,T,Ns", [(6, 3, 200, 1), (15, 3, 200, 5), (4, 1, 160, 2), (5, 0, 160, 1)])
+def test_sums_over_scans_round_less_than_one_chain(g, ctx, torch_cuda, K, P, T, Ns):
+    """b_w and the residual sums of data with a large mean, against 80-bit
+    arithmetic, beside the same tensors summed scan by scan in one chain and
+    combined in FP64 (NumPy).  A chain of n additions of like terms is off by
+    about sqrt(n / 3) roundings of the whole, parts of 28 scans by about
+    sqrt(28 / 3 / (n / 28) + n / 28 / 3): 0.25 of the chain at n = 200, with
+    the few roundings of the combination on both sides under 0.6; b_w is held
+    to 0.7 of the chain's error and the residual sums too."""
+    torch = torch_cuda
+    nx, q = 1000, np.longdouble
+    r = np.random.default_rng(K + T)
+    X = r.standard_normal((T, K))
+    X[:, 0] = 1.0
+    W = r.standard_normal((Ns, K, nx))
+    W[:, 0] += 100.0
+    Y = X @ W[0] + r.standard_normal((T, nx))
+    A = r.uniform(-0.4, 0.4, (Ns, P, nx))
+    lam = r.uniform(0.5, 2.0, nx)
+    # sums over scans of y[t - a] X[t - b] and of y[t - a] y[t - b], one chain each
+    C, D = np.zeros((P + 1, P + 1, K, nx)), np.zeros((P + 1, P + 1, nx))
+    for t in range(P, T):
+        for a in range(P + 1):
+            for b in range(P + 1):
+                C[a, b] += X[t - b][:, None] * Y[t - a]
+                D[a, b] += Y[t - a] * Y[t - b]
+    G = np.array([[X[P - a:T - a].T @ X[P - b:T - b] for b in range(P + 1)] for a in range(P + 1)])
+    c = np.concatenate([np.ones((Ns, 1, nx)), -A], 1)
+    cq, Xq, Yq = c.astype(q), X.astype(q), Y.astype(q)
+    bw, bwq = np.zeros((K, nx)), np.zeros((K, nx), q)
+    rss, rssq = np.zeros(nx), np.zeros(nx, q)
+    for a in range(P, -1, -1):   # the small terms first
+        for b in range(P, -1, -1):
+            bw += (c[:, a] * c[:, b]).mean(0) * C[a, b]
+            bwq += (cq[:, a] * cq[:, b]).mean(0) * (Xq[P - b:T - b].T @ Yq[P - a:T - a])
+            for j in range(Ns):
+                quad = (W[j] * (G[a, b] @ W[j])).sum(0)
+                rss += c[j, a] * c[j, b] * (D[a, b] - 2.0 * (C[a, b] * W[j]).sum(0) + quad)
+    bw, bwq, rss = lam * bw, lam.astype(q) * bwq, rss / Ns
+    for j in range(Ns):
+        e = Yq - Xq @ W[j].astype(q)
+        f = sum(cq[j, a] * e[P - a:T - a] for a in range(P + 1))
+        rssq += (f * f).sum(0) / Ns
+    op = g.gp_op_create(ctx, np.ones((1, 1, nx), dtype=np.uint8), 4, K)
+    g.gp_op_set_alpha(op, np.zeros(K))
+    d = g.gp_data_create(op, T, P, X, dev(torch, Y))
+    out = torch.zeros((K, nx), dtype=torch.float64, device="cuda")
+    res = torch.zeros(nx, dtype=torch.float64, device="cuda")
+    Ad = dev(torch, A) if P else None
+    g.gp_data_assemble(d, dev(torch, lam), Ns, Ad, out)
+    g.gp_data_lambda(d, Ns, dev(torch, W), Ad, 10.0, 0.1, res, None, None)
+    g.gp_data_destroy(d)
+    g.gp_op_destroy(op)
+
+    def off(v, ref):
+        return float(np.sqrt(((v - ref) ** 2).sum() / (ref ** 2).sum()))
+
+    assert off(out.cpu().numpy(), bwq) <= 0.7 * off(bw, bwq)
+    assert off(res.cpu().numpy(), rssq) <= 0.7 * off(rss, rssq)
