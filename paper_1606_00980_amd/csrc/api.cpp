@@ -881,30 +881,42 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
   // right-hand side iterates is the outer step alone
   int round_len = chunk;
   uint64_t round_mask = f32 && o.chunk > 0 ? ~0ull : 1ull;
-  // the first round replays the shape of every operator's previous solve at
-  // these settings, the final refinement included (one round and one wait, and
-  // no idle iterations, where the solve behaves as the previous one): the
-  // whole brain's FP64 solve, 13 iterations in four rounds of up to six, 415 to
-  // 290 us; 16 default samples 1,169 to 1,028 us; a 36-iteration slice solve and
-  // sample 1,154 to 675 us
+  // the first rounds replay the shape of every operator's previous solves at
+  // these settings, the final refinement included (one wait, and no idle
+  // iterations, where the solve behaves as they did): the whole brain's FP64
+  // solve, 13 iterations in four rounds of up to six, 415 to 290 us; 16 default
+  // samples 1,169 to 1,028 us; a 36-iteration slice solve and sample 1,154 to
+  // 675 us.  (A first solve at its settings gains nothing.)  From a zero start
+  // value the shape is one round; from a caller's, which may be anywhere, the
+  // host looks every REPLAY_MOST iterations, which bounds the idle ones.
+  constexpr int REPLAY_MOST = 16;
   bool tail = false;
-  auto shape = [&](int j) -> SolveShape& {
-    return items[order[j]].op->shape[o.precond == GP_PRECOND_BLOCK_JACOBI][f32];
+  int rp_len = 0, rp_at = 0;
+  uint64_t rp_mask = 0;
+  auto shape = [&](int j) -> ShapeMemory& {
+    return items[order[j]].op->shape[o.precond == GP_PRECOND_BLOCK_JACOBI][f32][o.zero_guess != 0];
+  };
+  auto replay_piece = [&]() -> bool {
+    if (rp_at >= rp_len) return false;
+    round_len = o.zero_guess ? rp_len - rp_at : std::min(rp_len - rp_at, REPLAY_MOST);
+    tail = rp_at + round_len == rp_len;
+    round_mask = (rp_mask >> rp_at) & (((tail ? 2ull : 1ull) << round_len) - 1);
+    rp_at += round_len;
+    return true;
   };
   if (o.chunk <= 0) {
-    bool have = true;
-    uint64_t m = 0;
-    int len = 0;
+    bool have = nl > 0;
     for (int j = 0; j < nl; ++j) {
-      const SolveShape& sh = shape(j);
-      have = have && sh.mask && sh.len > 0 && sh.tol == o.tol && sh.inner_tol == o.inner_tol;
-      m |= sh.mask;
-      len = std::max(len, sh.len);
+      const ShapeMemory& m = shape(j);
+      const SolveShape& sh = m.replayed();
+      have = have && m.last.mask && sh.len > 0 && m.tol == o.tol && m.inner_tol == o.inner_tol;
+      rp_mask |= sh.mask;
+      rp_len = std::max(rp_len, sh.len);
     }
-    if (have) {
-      round_len = len;
-      round_mask = m;
-      tail = true;
+    if (!have) rp_len = 0;
+    if (rp_len > o.max_iter) {   // the last refinement follows iteration max_iter
+      rp_len = o.max_iter;
+      rp_mask |= 1ull << rp_len;
     }
   }
   auto launch_round = [&](bool outer_only) -> int {
@@ -963,24 +975,32 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
     if (nl == 0)
       if (int e = read_states()) return e;
   }
+  bool replaying = replay_piece();
   while (n_outer > 0 || n_inner > 0) {
     if (++rounds > max_rounds) return fail(GP_ERR_DEVICE, "solver driver made no progress");
-    st = launch_round(!f32 && n_inner == 0 && !tail);
+    st = launch_round(!f32 && n_inner == 0 && !replaying);
     if (st) return st;
     tail = false;
     st = read_states();
     if (st) return st;
-    plan();
+    replaying = replaying && n_inner > 0 && replay_piece();
+    if (!replaying) plan();
   }
   {
+    // one shape per operator, over all its items
+    std::map<ShapeMemory*, uint64_t> masks;
     size_t at = 0;
-    for (int j = 0; j < nl; ++j) {
-      uint64_t m = 0;
-      for (int r = 0; r < items[order[j]].R; ++r) m |= hs[at++].slots;
+    for (int j = 0; j < nl; ++j)
+      for (int r = 0; r < items[order[j]].R; ++r) masks[&shape(j)] |= hs[at++].slots;
+    for (const auto& kv : masks) {
+      ShapeMemory& m = *kv.first;
       int len = 0;
-      while (len < 63 && (m >> (len + 1)) != 0) ++len;
+      while (len < 63 && (kv.second >> (len + 1)) != 0) ++len;
+      m.prev = m.tol == o.tol && m.inner_tol == o.inner_tol ? m.last : SolveShape{};
       // a shape that reaches the last bit (63 or more iterations) is not replayed
-      shape(j) = SolveShape{len < 63 ? m : 0, len, o.tol, o.inner_tol};
+      m.last = SolveShape{len < 63 ? kv.second : 0, len};
+      m.tol = o.tol;
+      m.inner_tol = o.inner_tol;
     }
   }
   // results (hs holds the final states, in problem order)

@@ -97,15 +97,23 @@ struct RbData;
 }  // namespace rt
 }  // namespace gp
 
-// Shape of an operator's last solve at one preconditioner, precision and pair
-// of tolerances: the union over its right-hand sides of the iteration counts
-// after which they took an outer step (bit i: after i), and the largest such
-// count.  The first round of the next solve at the same settings replays it; a
-// solve that turns out longer goes on in planned rounds.
+// Shape of a solve: the union over an operator's right-hand sides of the
+// iteration counts after which they took an outer step (bit i: after i), and
+// the largest such count.
 struct SolveShape {
   uint64_t mask = 0;   // 0: none
   int len = 0;
+};
+
+// An operator's last two solves at one preconditioner, precision, kind of
+// start value and pair of tolerances.  The first rounds of the next such solve
+// replay the shorter one (a start value may be far or near from one solve to
+// the next, and idle iterations cost as much as waiting for a round); a solve
+// that turns out longer goes on in planned rounds.
+struct ShapeMemory {
+  SolveShape last, prev;
   double tol = 0.0, inner_tol = 0.0;
+  const SolveShape& replayed() const { return prev.mask && prev.len < last.len ? prev : last; }
 };
 
 struct gp_op {
@@ -130,7 +138,7 @@ struct gp_op {
   bool have_blocks = false, have_alpha = false;
   int pc_built = -1;
   int pc_want = GP_PRECOND_BLOCK_JACOBI;
-  SolveShape shape[2][2];   // [Jacobi, block Jacobi][FP64, FP32]
+  ShapeMemory shape[2][2][2];   // [Jacobi, block Jacobi][FP64, FP32][x given, zero start value]
   gp::rt::RbData* rb = nullptr;   // red-black split and its preconditioner, built on first use
   size_t bytes = 0;
 };
