@@ -462,8 +462,13 @@ void apply_plan(Prob& p, const Plan& pl) {
   p.mv_count = pl.mv_count;
 }
 
-void size_groups(std::vector<LaunchGroup>& gs, int cus) {
+void size_groups(std::vector<LaunchGroup>& gs, Prob* probs, int cus) {
   for (LaunchGroup& g : gs) {
+    double reads = 0.0;
+    for (int j = g.first; j < g.first + g.count; ++j)
+      reads += (double)probs[j].op.ntiles * probs[j].op.ntiles * probs[j].R;
+    g.need_fin = g.mv_mode || !update_finalizes(reads);
+    for (int j = g.first; j < g.first + g.count; ++j) probs[j].fin = !g.need_fin;
     const int wpc = g.wpc > 0 ? g.wpc : 8;
     const int cap = std::max(8, cus * wpc / 8 * 8);
     g.nblk = std::min(cap, (g.W + 7) / 8 * 8);
@@ -839,8 +844,6 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
     if (groups.empty() || groups.back().K != it.op->K)
       groups.push_back(LaunchGroup{it.op->K, j, 0, 0, 0, 0, 0, 0, plans[j].mv_mode, popts[j].wg_per_cu, 0, 0});
     LaunchGroup& g = groups.back();
-    p.fin = !plans[j].mv_mode && update_finalizes(it.op->ntiles, it.op->K);
-    g.need_fin = g.need_fin || !p.fin;
     p.work_begin = g.W;
     g.W += p.work_count;
     p.work_begin_o = g.Wo;
@@ -851,7 +854,7 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
     g.F += (it.R + fpb - 1) / fpb;
     g.count += 1;
   }
-  size_groups(groups, c->cus);
+  size_groups(groups, c->h_probs, c->cus);
   hipStream_t s = c->stream;
   HIPTRY(hipMemcpyAsync(c->d_probs, c->h_probs, np * sizeof(Prob), hipMemcpyHostToDevice, s));
   HIPTRY(hipMemsetAsync(ws + st_all, 0, totalR * sizeof(RhsState), s));

@@ -52,15 +52,22 @@ hipError_t launch_trace(hipStream_t s, const OpDev& op, int m, const int8_t* v, 
 // nblocks = sum over problems of ceil(R / finalize_rhs_per_block()).
 hipError_t launch_finalize(hipStream_t s, int kind, const Prob* probs, int nprob, int nblocks);
 int finalize_rhs_per_block();
-// Whether the update launch finalises a step itself (nt tiles, K regressors).
-// Each of its workgroups then sums the partials of its right-hand sides again,
-// 56 nt bytes each against the 28 K per voxel (FP32) that it moves anyway, and
-// a launch of 4 to 5 us is saved per step: the whole brain's FP64 solve (block
-// Jacobi, nt = 206, K = 6) 300 to 276 us, 16 default samples 1,047 to 1,018 us,
-// a Gibbs iteration 410 to 398 us, an FP64 trace 453 to 434 us.  The largest
-// operator (red-black, nt = 567, K = 10, 64 right-hand sides) would read 1.1 GB
-// of partials per step: 18.63 to 18.77 ms.
-inline bool update_finalizes(int nt, int K) { return nt <= 48 * K; }
+// Whether the update launch of a group finalises the step itself.  Each of its
+// workgroups then sums the partials of its right-hand sides again, 56 nt bytes
+// each (nt tiles), and the finalising launch of 4 to 5 us is saved.  reads: the
+// sum of nt * nt * R over the group's problems.
+// Microseconds gained per iteration over K = 2, 6, 10, nt = 30 to 480, 1 to 64
+// right-hand sides, both solvers (least, mean and most of each row):
+//   reads up to 2e5     0.2   1.7   3.0
+//         2e5 to 4e5    0.2   1.6   2.7
+//         4e5 to 8e5   -0.3   1.3   2.8
+//         8e5 to 2e6   -1.2   0.6   2.5
+//         2e6 to 4e6   -5.4  -2.3   0.5
+//         beyond      -39   -13    -2.8
+// A limit in nt alone lost 2 % at nt = 200 with 64 right-hand sides (K = 6,
+// block Jacobi, FP32: 4,449 to 4,536 us a solve).  Either way the bits are the
+// same.
+inline bool update_finalizes(double reads) { return reads <= 8e5; }
 
 // k_data.hip: time-summed AR(P) data tensors and the data term assembled from them
 // X: [T][data_design_stride(K)], the columns past K zero

@@ -322,6 +322,9 @@ std::vector<RbGroup> rb_groups(RbProb* h, int n, int rhs_tile, bool outer_chunks
       }
     long pairs = 0;
     for (int j = g.first; j < g.first + g.count; ++j) pairs += (long)h[j].rb.ntB * ((h[j].pr.R + 1) / 2);
+    double reads = 0.0;
+    for (int j = g.first; j < g.first + g.count; ++j) reads += (double)h[j].rb.ntB * h[j].rb.ntB * h[j].pr.R;
+    g.need_fin = !update_finalizes(reads);
     const int Ro = outer_pairs(g.K) && pairs >= 1024 ? 2 : 1;
     int F = 0;
     for (int j = g.first; j < g.first + g.count; ++j) {
@@ -333,8 +336,7 @@ std::vector<RbGroup> rb_groups(RbProb* h, int n, int rhs_tile, bool outer_chunks
       // for pairs holds that layout too)
       if (P.Rc < 2) P.uw = 1;
       g.uw = std::max(g.uw, P.uw);
-      P.pr.fin = update_finalizes(P.rb.ntB, P.rb.K);
-      g.need_fin = g.need_fin || !P.pr.fin;
+      P.pr.fin = !g.need_fin;
       P.wB = g.WB;
       g.WB += P.rb.ntB * P.nch;
       P.wR = g.WR;

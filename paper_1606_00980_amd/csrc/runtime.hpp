@@ -184,13 +184,14 @@ void apply_plan(Prob& p, const Plan& pl);
 struct LaunchGroup {
   int K, first, count, W, F, nblk, Wmv, nblk_mv, mv_mode, wpc;
   int Wo, nblk_o;   // refine / addsol work items and workgroups
-  bool need_fin = false;   // some problem's steps take a finalising launch
+  bool need_fin = false;   // the steps take a finalising launch
 };
 // Number of inner vectors (d, r, p, q) per right-hand side in the inner precision.
 constexpr int NVEC = 4;
 // Persistent workgroup counts of every group: wg_per_cu (default 8) per
 // compute unit, a multiple of the XCD count, no more than the work items.
-void size_groups(std::vector<LaunchGroup>& gs, int cus);
+// also decides where the groups' steps are finalised
+void size_groups(std::vector<LaunchGroup>& gs, Prob* probs, int cus);
 // Enqueue on stream q, for every group: [x += d, refine, finalise] (the
 // outer step of a solver round), or iters x [matvec, finalise, update].
 // With `profiled` and profiling on, each launch is timed with events.
@@ -319,7 +320,7 @@ struct RbMember {
 struct RbGroup {
   int K, first, count, WB, WR, WO, F;
   int uw;   // 2 when some member stores the red-stage vector in pairs, else 1
-  bool need_fin = false;   // some member's steps take a finalising launch
+  bool need_fin = false;   // the steps take a finalising launch
 };
 // Device bytes of a member's vectors and partials (states excluded).
 size_t rb_member_bytes(const gp_op* op, int R, bool f32);

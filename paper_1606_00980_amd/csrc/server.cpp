@@ -349,8 +349,6 @@ int rebuild_layout(gp_server* s) {
     if (s->groups.empty() || s->groups.back().K != q->op->K)
       s->groups.push_back(LaunchGroup{q->op->K, j, 0, 0, 0, 0, 0, 0, pl.mv_mode, o.wg_per_cu, 0, 0});
     auto& g = s->groups.back();
-    p.fin = !g.mv_mode && update_finalizes(q->op->ntiles, q->op->K);
-    g.need_fin = g.need_fin || !p.fin;
     p.work_begin = g.W;
     g.W += p.work_count;
     p.work_begin_o = g.Wo;
@@ -361,7 +359,7 @@ int rebuild_layout(gp_server* s) {
     g.F += (q->R + fpb - 1) / fpb;
     g.count += 1;
   }
-  size_groups(s->groups, s->ctx->cus);
+  size_groups(s->groups, s->h_probs, s->ctx->cus);
   HIPTRY(hipMemcpyAsync(s->d_probs, s->h_probs, (size_t)n * sizeof(Prob), hipMemcpyHostToDevice, s->stream));
   s->layout_dirty = false;
   return GP_OK;
