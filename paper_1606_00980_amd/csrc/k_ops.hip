@@ -197,54 +197,86 @@ __global__ __launch_bounds__(TILE) void k_precond(OpDev op, int pc, double* __re
 }
 
 // ----------------------------------------------------------------- apply
-// Items (rc right-hand sides, tile) run by blocks of tb tiles, every chunk of
-// right-hand sides over a block's tiles before the next block, and go to the
-// XCDs in contiguous ranges (as k_perturb's).  The vectors are read through
-// buffer descriptors: with a 64-bit address per gather the loads of few
-// neighbours were in flight at a time, and every right-hand side read the
-// blocks again: 25.1 us for 8 right-hand sides at K = 6, N = 52,740 (18.7 so:
-// 2.6 TB/s of its 49 MB), 98 for 16 at K = 10 (58).  A block is held across an
-// item's right-hand sides up to K = 9.
-template <int K>
+// RC = 0: one right-hand side per workgroup on a two-dimensional grid.
+// RC = 1: the same, the right-hand sides of a tile side by side and the items
+// dealt to the XCDs in contiguous ranges, so that the readers of a block and of
+// a vector's neighbours share an L2.  RC = 2: rc right-hand sides per workgroup,
+// their voxels' blocks held; items by blocks of tb tiles, every chunk of
+// right-hand sides over a block's tiles before the next block.
+// The vectors are read through buffer descriptors, the neighbours of all
+// regressors (four with RC = 2) together: with a 64-bit address per gather, or
+// left to the compiler's order, few loads were in flight at a time (K = 5: one).
+// Beyond K = KREG, and in launches that leave most wavefronts empty, the
+// compiler's order is the better one.
+// Measured (us; one right-hand side per workgroup with 64-bit addresses and no
+// mapping of items, then so):
+//   N = 52,740, K = 6, R = 8    25.1   17.9  (2.7 TB/s of its 49 MB)
+//   N = 85,936, K = 5, R = 8    22.0   19.4    K = 10, R = 8   77    41
+//               K = 15, R = 8    200     67    K = 15, R = 1   35    23
+//               K = 20, R = 4    194     74    K = 24, R = 4  546   120
+//   N = 12,704, K = 9, R = 2     8.2    6.2    N = 2,620, K = 5, R = 2   3.8   3.8
+template <int K, int RC>
 __global__ __launch_bounds__(TILE) void k_apply(OpDev op, const double* __restrict__ x, double* __restrict__ y, int R,
                                                 int rc, int tb) {
   constexpr int NB = Tri<K>::NB;
-  constexpr bool HOLD = K <= 9;
-  const int N = op.N, nch = (R + rc - 1) / rc;
-  const int item = xcd_remap(blockIdx.x, gridDim.x);
-  const int per = tb * nch;
-  const int blk = item / per, rem = item - blk * per;
-  const int len = min(tb, op.ntiles - blk * tb);
-  const int r0 = rem / len * rc, r1 = min(R, r0 + rc);
-  const int n = (blk * tb + rem % len) * TILE + threadIdx.x;
+  constexpr bool MANY = RC == 2, TOGETHER = RC > 0 && K <= KREG;
+  constexpr int G = !TOGETHER ? 1 : MANY && K > 4 ? 4 : K;
+  const int N = op.N;
+  int tile = blockIdx.x, r0 = blockIdx.y;
+  if constexpr (MANY) {
+    const int item = xcd_remap(blockIdx.x, gridDim.x);
+    const int per = tb * ((R + rc - 1) / rc), blk = item / per, rem = item - blk * per;
+    const int len = min(tb, op.ntiles - blk * tb);
+    r0 = rem / len * rc;
+    tile = blk * tb + rem % len;
+  } else if constexpr (RC == 1) {
+    const int item = xcd_remap(blockIdx.x, gridDim.x);
+    tile = item / R;
+    r0 = item - tile * R;
+  }
+  const int r1 = MANY ? min(R, r0 + rc) : r0 + 1;
+  const int n = tile * TILE + threadIdx.x;
   if (n >= N) return;
   const unsigned o = (unsigned)n * 8u;
   unsigned nb[6];
 #pragma unroll
   for (int d = 0; d < 6; ++d) nb[d] = (unsigned)op.nbr[(size_t)d * N + n] * 8u;
   const Slab<double> Bs(op.B64, NB, N);
-  double Bh[HOLD ? NB : 1];
-  if constexpr (HOLD) {
+  double B[NB];
+  auto load_block = [&]() {
 #pragma unroll
-    for (int e = 0; e < NB; ++e) Bh[e] = Bs.ld(e, o);
-  }
+    for (int e = 0; e < NB; ++e) B[e] = Bs.ld(e, o);
+  };
+  if constexpr (MANY) load_block();
 #pragma unroll 1
   for (int r = r0; r < r1; ++r) {
     const Slab<double> xs(x + (size_t)r * K * N, K, N), ys(y + (size_t)r * K * N, K, N);
     double xo[K], s6[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) xo[k] = xs.ld(k, o);
+    if constexpr (!MANY) load_block();
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      s6[k] = 0.0;
+    for (int k0 = 0; k0 < K; k0 += G) {
+      double t[G][6];
 #pragma unroll
-      for (int d = 0; d < 6; ++d) s6[k] += xo[k] - xs.ld(k, nb[d]);
+      for (int c = 0; c < G; ++c)
+#pragma unroll
+        for (int d = 0; d < 6; ++d)
+          if (k0 + c < K) t[c][d] = xs.ld(k0 + c, nb[d]);
+      if constexpr (TOGETHER) __builtin_amdgcn_sched_barrier(0);   // none waits for another
+#pragma unroll
+      for (int c = 0; c < G; ++c)
+        if (k0 + c < K) {
+          s6[k0 + c] = 0.0;
+#pragma unroll
+          for (int d = 0; d < 6; ++d) s6[k0 + c] += xo[k0 + c] - t[c][d];
+        }
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       double v = op.alpha64[k] * s6[k];
 #pragma unroll
-      for (int j = 0; j < K; ++j) v += (HOLD ? Bh[HOLD ? pk(k, j) : 0] : Bs.ld(pk(k, j), o)) * xo[j];
+      for (int j = 0; j < K; ++j) v += B[pk(k, j)] * xo[j];
       ys.st(k, o, v);
     }
   }
@@ -481,19 +513,37 @@ static int tiles_per_block(const OpDev& op) {
 
 hipError_t launch_apply(hipStream_t s, const OpDev& op, int R, const double* x, double* y) {
   if (op.ntiles == 0 || R == 0) return hipSuccess;
-  // right-hand sides per workgroup (their block read once): the largest of 4, 2,
-  // 1 that leaves two workgroups per compute unit (16 at K = 10, N = 52,740:
-  // 68, 62 and 58 us at 1, 2 and 4; 8 at K = 6: 18.7 at each)
-  int rc = 1;
-  for (int cand : {4, 2})
-    if ((long)op.ntiles * ((R + cand - 1) / cand) >= 512) {
-      rc = cand;
-      break;
-    }
-  const dim3 g((unsigned)((long)op.ntiles * ((R + rc - 1) / rc))), b(TILE);
+  // right-hand sides per workgroup (their block read once): the largest of 4, 2
+  // that leaves 640 workgroups (8 right-hand sides at N = 85,936, 672 of them:
+  // 23.2 us at K = 6 against 27.6 at one each, 12.1 against 12.6 at K = 3; 24 at
+  // N = 12,704, K = 4, 600 of them: 10.0 against 8.8), else one; more where a
+  // launch could not hold the workgroups (2^32 lanes).  Beyond K = KREG a block
+  // does not stay in registers (K = 20, N = 85,936, R = 4: 73 us at 1, 217 at
+  // 2).  0: one on a two-dimensional grid, where few workgroups make the
+  // mapping's divisions cost more than it gives (K = 10, N = 20,848, R = 4, 328
+  // of them: 12.6 us unmapped, 10.0 mapped; K = 7, N = 9,048, R = 3, 108: 4.7
+  // and 5.2).
+  int rc = (long)op.ntiles * R >= 320 ? 1 : 0;
+  if (op.K <= KREG)
+    for (int cand : {4, 2})
+      if ((long)op.ntiles * ((R + cand - 1) / cand) >= 640) {
+        rc = cand;
+        break;
+      }
+  const auto blocks = [&]() { return (long)op.ntiles * ((R + std::max(rc, 1) - 1) / std::max(rc, 1)); };
+  while (blocks() * TILE >= 1L << 32) rc *= 2;
+  const dim3 g = rc ? dim3((unsigned)blocks()) : dim3(op.ntiles, R), b(TILE);
   const int tb = tiles_per_block(op);
   switch (op.K) {
-#define X(KK) case KK: GP_LAUNCH(k_apply<KK>, g, b, 0, s, op, x, y, R, rc, tb); break;
+#define X(KK)                                                                          \
+  case KK:                                                                             \
+    if (rc > 1)                                                                        \
+      GP_LAUNCH((k_apply<KK, 2>), g, b, 0, s, op, x, y, R, rc, tb);                    \
+    else if (rc == 1)                                                                  \
+      GP_LAUNCH((k_apply<KK, 1>), g, b, 0, s, op, x, y, R, rc, tb);                    \
+    else                                                                               \
+      GP_LAUNCH((k_apply<KK, 0>), g, b, 0, s, op, x, y, R, rc, tb);                    \
+    break;
     GP_K_CASES(X)
 #undef X
     default: return hipErrorInvalidValue;
