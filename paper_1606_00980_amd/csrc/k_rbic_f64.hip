@@ -31,7 +31,7 @@ hipError_t launch_rb_split(hipStream_t s, const RbDev& rb, int R, const double* 
   // black pass (its time is in the gathers of t) takes one
   int rcr = 1;
   for (int cand : {4, 2})
-    if ((long)rb.ntR * ((R + cand - 1) / cand) >= 1024) {
+    if (!split_alone(rb.K) && (long)rb.ntR * ((R + cand - 1) / cand) >= 1024) {
       rcr = cand;
       break;
     }
@@ -41,10 +41,10 @@ hipError_t launch_rb_split(hipStream_t s, const RbDev& rb, int R, const double* 
     if (wr > 0) GP_LAUNCH(k_rb_split_red<KK>, dim3(wr), dim3(TILE), 0, s, rb, R, rcr, b, t, bbpart);         \
     if (wb > 0) {                                                                                            \
       if (first.f32)                                                                                         \
-        GP_LAUNCH((k_rb_split_black<KK, float>), dim3(wb), dim3(TILE), 0, s, rb, R, 1, b, x, zero_guess, t, c, xB, \
+        GP_LAUNCH((k_rb_split_black<KK, float>), dim3(wb), dim3(TILE), 0, s, rb, R, b, x, zero_guess, t, c, xB, \
                   bbpart, f32);                                                                              \
       else                                                                                                   \
-        GP_LAUNCH((k_rb_split_black<KK, double>), dim3(wb), dim3(TILE), 0, s, rb, R, 1, b, x, zero_guess, t, c, xB, \
+        GP_LAUNCH((k_rb_split_black<KK, double>), dim3(wb), dim3(TILE), 0, s, rb, R, b, x, zero_guess, t, c, xB, \
                   bbpart, f64);                                                                              \
     }                                                                                                        \
     break;

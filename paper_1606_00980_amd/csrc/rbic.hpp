@@ -442,8 +442,10 @@ __global__ __launch_bounds__(SETUP_WG) void k_rb_setup_black(RbDev rb, const dou
   // gathers of a chunk's six neighbours are in flight together (a missing
   // neighbour reads entry 0 and is dropped by a select).  Neighbour by
   // neighbour behind a branch, with one neighbour's gathers in flight: 176 us
-  // at K = 15, N = 52,740 (56 so), 17 at K = 6 (12), 203 at K = 10,
-  // N = 289,592 (100).
+  // at K = 15, N = 52,740 (56 so), 17 at K = 6 (10), 203 at K = 10,
+  // N = 289,592 (106).  The barrier keeps the chunks apart: without it the
+  // compiler waits for entry after entry at K = 7, 9 and 11 (N = 908: 67 us at
+  // K = 11, 27 neighbour by neighbour, 17 so).
   const Slab<double> Ps(rb.P64, NB, rb.NR);
   constexpr int SE = K <= 11 ? 8 : 4;
 #pragma unroll
@@ -466,7 +468,7 @@ __global__ __launch_bounds__(SETUP_WG) void k_rb_setup_black(RbDev rb, const dou
           a[pk(k, j0 + c)] -= ak * rb.alpha64[j0 + c] * s;
         }
       }
-      if constexpr (K > 11) __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
   const bool ok = spd_inverse_any<K>(a);
@@ -519,6 +521,12 @@ __device__ __forceinline__ void each_or_two(int r0, int r1, const F& f) {
 // tiles.  From K = 9 to 12 two right-hand sides share the reading of the
 // inverse, and the product is pinned before the branch that stores it: 878 ->
 // 595 us for 64 at K = 10, N = 289,592, 38 -> 30 for five at K = 15, N = 52,740.
+// From K = 16 on the inverse does not stay in registers and a workgroup takes
+// one right-hand side without a loop (see the black voxels; N = 2,620: 34 -> 24
+// us at K = 16, 61 -> 12 at K = 24; at K = 13 the loop is the faster one, 7.5
+// against 23).
+constexpr bool split_alone(int K) { return K >= 16; }
+
 template <int K>
 __global__ __launch_bounds__(TILE) void k_rb_split_red(RbDev rb, int R, int rc, const double* __restrict__ b,
                                                        double* __restrict__ t, double* __restrict__ bbpart) {
@@ -561,21 +569,30 @@ __global__ __launch_bounds__(TILE) void k_rb_split_red(RbDev rb, int R, int rc, 
       sums.add(rr[m] - w.r0, acc[m]);
     }
   };
-  each_or_two<outer_pairs(K)>(w.r0, w.r1, pass);
+  if constexpr (split_alone(K)) {
+    const int rr[1] = {w.r0};
+    pass(rr);
+  } else {
+    each_or_two<outer_pairs(K)>(w.r0, w.r1, pass);
+  }
   sums.flush(bbpart, 0, w.r0, w.r1 - w.r0, rb.ntS, w.tile);
 }
 
 // Black voxels: c = b_m + alpha .* sum_{n ~ m} t_n (c = b_B - E' D_R^{-1} b_R),
 // x_B = x_m (not from a zero start value: x_B is then first written by x_B = d
 // (+ a p)) and, from a zero start value, the first refinement; ||b||^2
-// partials bbpart[r][ntR + tile].
+// partials bbpart[r][ntR + tile].  One right-hand side per workgroup, no loop:
+// in one over right-hand sides, of which there was one, the compiler ordered
+// the loads one after the other (one right-hand side, N = 2,620: 23 us at
+// K = 15, 81 at K = 24; 9 and 15 so).
 template <int K, typename T>
-__global__ __launch_bounds__(TILE) void k_rb_split_black(RbDev rb, int R, int rc, const double* __restrict__ b,
+__global__ __launch_bounds__(TILE) void k_rb_split_black(RbDev rb, int R, const double* __restrict__ b,
                                                          const double* __restrict__ x, int zero_guess,
                                                          const double* __restrict__ t, double* __restrict__ c,
                                                          double* __restrict__ xB, double* __restrict__ bbpart,
                                                          RbFirst<T> first) {
-  const SplitItem w = split_item(rb.ntB, R, rc);
+  const SplitItem w = split_item(rb.ntB, R, 1);
+  const int r = w.r0;
   const int i = w.tile * TILE + threadIdx.x;
   const bool valid = i < rb.NB;
   const int ii = valid ? i : 0;   // lanes past the end compute on voxel 0 and store nothing
@@ -585,53 +602,50 @@ __global__ __launch_bounds__(TILE) void k_rb_split_black(RbDev rb, int R, int rc
   // the Schur inverse for the first refinement, held across the work item
   const Packed<T, K, HoldRb<T, K, 1>::v> S(RbT<T>::S(rb), rb.NB, oT);
   ItemSums<4> sums;
-#pragma unroll 1
-  for (int r = w.r0; r < w.r1; ++r) {
-    const Slab<double> bs(b + (size_t)r * K * rb.N, K, rb.N), ts(t + (size_t)r * K * rb.NR, K, rb.NR),
-        cs(c + (size_t)r * K * rb.NB, K, rb.NB);
-    double acc[4] = {0.0, 0.0, 0.0, 0.0}, s[K], cv[K], xv[K];
+  const Slab<double> bs(b + (size_t)r * K * rb.N, K, rb.N), ts(t + (size_t)r * K * rb.NR, K, rb.NR),
+      cs(c + (size_t)r * K * rb.NB, K, rb.NB);
+  double acc[4] = {0.0, 0.0, 0.0, 0.0}, s[K], cv[K], xv[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) cv[k] = bs.ld(k, om);
-    if (!zero_guess) {
-      const Slab<double> xu(x + (size_t)r * K * rb.N, K, rb.N);
+  for (int k = 0; k < K; ++k) cv[k] = bs.ld(k, om);
+  if (!zero_guess) {
+    const Slab<double> xu(x + (size_t)r * K * rb.N, K, rb.N);
 #pragma unroll
-      for (int k = 0; k < K; ++k) xv[k] = xu.ld(k, om);
-    }
-    neighbour_sum<double, K>(nb, ts, s);
+    for (int k = 0; k < K; ++k) xv[k] = xu.ld(k, om);
+  }
+  neighbour_sum<double, K>(nb, ts, s);
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    acc[3] += cv[k] * cv[k];
+    cv[k] += rb.alpha64[k] * s[k];
+  }
+  if (valid) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) cs.st(k, oi, cv[k]);
+    if (!zero_guess) RbVec<double, K>(xB + (size_t)r * K * rb.NB, rb.NB).store(ii, xv);
+  }
+  if (first.r) {
+    // the first refinement from x_B = 0: its residual is c itself
+    T rt[K], zt[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      acc[3] += cv[k] * cv[k];
-      cv[k] += rb.alpha64[k] * s[k];
+      acc[0] += cv[k] * cv[k];
+      rt[k] = (T)cv[k];
+      zt[k] = 0;
     }
+    sym_apply<K>(S, rt, zt);
+#pragma unroll
+    for (int k = 0; k < K; ++k) acc[2] += (double)rt[k] * (double)zt[k];
     if (valid) {
-#pragma unroll
-      for (int k = 0; k < K; ++k) cs.st(k, oi, cv[k]);
-      if (!zero_guess) RbVec<double, K>(xB + (size_t)r * K * rb.NB, rb.NB).store(ii, xv);
+      RbVec<T, K>(first.r + (size_t)r * K * rb.NB, rb.NB).store(ii, rt);
+      RbVec<T, K>(first.p + (size_t)r * K * rb.NB, rb.NB).store(ii, zt);
     }
-    if (first.r) {
-      // the first refinement from x_B = 0: its residual is c itself
-      T rt[K], zt[K];
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        acc[0] += cv[k] * cv[k];
-        rt[k] = (T)cv[k];
-        zt[k] = 0;
-      }
-      sym_apply<K>(S, rt, zt);
-#pragma unroll
-      for (int k = 0; k < K; ++k) acc[2] += (double)rt[k] * (double)zt[k];
-      if (valid) {
-        RbVec<T, K>(first.r + (size_t)r * K * rb.NB, rb.NB).store(ii, rt);
-        RbVec<T, K>(first.p + (size_t)r * K * rb.NB, rb.NB).store(ii, zt);
-      }
-    }
-    if (!valid) acc[0] = acc[2] = acc[3] = 0.0;
-    sums.add(r - w.r0, acc);
   }
-  sums.flush_to(w.r1 - w.r0, [&](int v, int rl) -> double* {
-    if (v == 3) return bbpart + (size_t)(w.r0 + rl) * rb.ntS + rb.ntR + w.tile;
+  if (!valid) acc[0] = acc[2] = acc[3] = 0.0;
+  sums.add(0, acc);
+  sums.flush_to(1, [&](int v, int) -> double* {
+    if (v == 3) return bbpart + (size_t)r * rb.ntS + rb.ntR + w.tile;
     if (!first.r) return nullptr;   // the refinement forms these from a start value
-    return first.part + (size_t)v * first.vstride + (size_t)(first.r0 + w.r0 + rl) * first.pstride + w.tile;
+    return first.part + (size_t)v * first.vstride + (size_t)(first.r0 + r) * first.pstride + w.tile;
   });
 }
 

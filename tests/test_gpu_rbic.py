@@ -554,3 +554,33 @@ def test_relative_residual_from_a_start_value(g, ctx, torch_cuda, precision, dim
             assert abs(st[r]["relres"] - rel) <= 1e-12 * qn * np.linalg.norm(xr) / nb, (r, st[r]["relres"], rel)
     finally:
         g.gp_op_destroy(op)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("K", [7, 9, 11, 13, 15, 16, 17, 24])
+def test_set_up_and_split_of_every_kind(g, ctx, torch_cuda, precision, K):
+    """The set-up's and the split's forms over K (blocks held or not, one
+    right-hand side to a workgroup or several) with an odd number of right-hand
+    sides, from zero and from a start value: the residual, recomputed by the
+    oracle, and each right-hand side's bits alone."""
+    w = synth.tiny((13, 11, 9), 6, K, seed=K)
+    op = make_op(g, ctx, torch_cuda, w)
+    try:
+        R, tol = 5, 1e-10
+        b = rhs(w, R, K)
+        Q = orc.precision(orc.grid(w.mask, w.conn), w.alpha, w.B)
+        prec = g.GP_PREC_FP64 if precision == "fp64" else g.GP_PREC_FP32_REFINE64
+        bd, x0 = dev(torch_cuda, b), dev(torch_cuda, np.random.default_rng(K).standard_normal(b.shape))
+        for zero in (0, 1):
+            o = g.gp_opts_default(tol=tol, precision=prec, precond=g.GP_PRECOND_RB_IC0, zero_guess=zero)
+            x = x0.clone()
+            _, st = g.gp_solve(op, R, bd, x, o)
+            assert all(s["status"] == g.GP_OK for s in st)
+            assert np.all(orc.relres(Q, x.cpu().numpy(), b)[:R - 1] <= 1.01 * tol)
+            for r in (0, 3):
+                one = x0[r:r + 1].clone()
+                g.gp_solve(op, 1, bd[r:r + 1], one, o)
+                assert torch_cuda.equal(one[0], x[r])
+    finally:
+        torch_cuda.cuda.synchronize()
+        g.gp_op_destroy(op)
