@@ -310,10 +310,12 @@ __global__ __launch_bounds__(TENSOR_WG) void k_data_tensors(int T, int K, int Ks
 // (both brackets are linear in them):
 //   B_kl = lambda (XX_kl - sum_p (R_klp + R_lkp) m1_p + sum_pq S_pklq m2_pq)
 //   b_k  = lambda (YX_k - sum_p Bt_pk m1_p + sum_pq Dt_pkq m2_pq).
-// blockIdx.y = 0: the block; with ASM_FUSED the others b_n, ASM_KC regressors
-// each.  From K = 11 on the block's registers leave one or two wavefronts a
-// SIMD, which b_n's loads then wait in: there it has a kernel of its own
-// (K = 15: 60 + 21 against 104 us fused; K = 6: 14 us fused against 13 + 12).
+// blockIdx.y = 0: the block; the others, if any, b_n, ASM_KC regressors each.
+// From K = 11 on the block's registers leave one or two wavefronts a SIMD, which
+// b_n's loads then wait in: there it has a kernel of its own (K = 15: 60 + 21
+// against 104 us fused; K = 6: 14 us fused against 13 + 12), unless the launch
+// leaves SIMDs empty anyway (at most ASM_FEW workgroups; K = 16, N = 908: 46 us
+// fused against 43 + 12).
 // Bound: the tensors read for b_n and the three packed arrays written, all
 // coalesced (at K = 15, P = 3, N = 52,740: 225 MB, 45 us at 5 TB/s).
 // Measured there 81 us; the rows of [N][K][K] blocks written by one kernel
@@ -322,6 +324,7 @@ __global__ __launch_bounds__(TENSOR_WG) void k_data_tensors(int T, int K, int Ks
 constexpr int ASM_WG = 64;
 constexpr int ASM_KC = 3;   // regressors of b_w per lane
 template <int K> constexpr bool ASM_FUSED = K <= 10;
+constexpr unsigned ASM_FEW = 1024;
 
 constexpr int ASM_NQ = PMAX * (PMAX + 1) / 2;
 
@@ -390,7 +393,7 @@ __global__ __launch_bounds__(ASM_WG) void k_data_assemble(int P, int N, int Ns, 
   // the coefficient table in LDS (every lane reads the same entry)
   constexpr int NB = K * (K + 1) / 2;
   __shared__ double tab[NB * TAB];
-  const bool rhs = ASM_FUSED<K> && blockIdx.y > 0;
+  const bool rhs = blockIdx.y > 0;
   if (!rhs)
     for (int i = threadIdx.x; i < NB * TAB; i += ASM_WG) tab[i] = Tab[i];
   __syncthreads();
@@ -757,12 +760,13 @@ hipError_t launch_data_assemble(hipStream_t s, int K, int P, int N, int Ns, cons
   const double* tab = G + data_table_at(K, P);
   const dim3 g((N + ASM_WG - 1) / ASM_WG), b(ASM_WG);
   const unsigned nrhs = bw ? (K + ASM_KC - 1) / ASM_KC : 0;
+  bool fused;
   switch (K) {
 #define X(KK)                                                                                                      \
   case KK:                                                                                                         \
-    if (!ASM_FUSED<KK> && bw)                                                                                      \
-      GP_LAUNCH(k_data_rhs, dim3(g.x, nrhs), b, 0, s, K, P, N, Ns, YX, Bt, Dt, lambda, A, bw);                     \
-    GP_LAUNCH(k_data_assemble<KK>, dim3(g.x, ASM_FUSED<KK> ? 1 + nrhs : 1), b, 0, s, P, N, Ns, tab, YX, Bt, Dt,     \
+    fused = ASM_FUSED<KK> || g.x * (1 + nrhs) <= ASM_FEW;                                                          \
+    if (!fused && bw) GP_LAUNCH(k_data_rhs, dim3(g.x, nrhs), b, 0, s, K, P, N, Ns, YX, Bt, Dt, lambda, A, bw);     \
+    GP_LAUNCH(k_data_assemble<KK>, dim3(g.x, fused ? 1 + nrhs : 1), b, 0, s, P, N, Ns, tab, YX, Bt, Dt,             \
               lambda, A, B64, B32, L64, bad, bw);                                                                  \
     break;
     X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16) X(17) X(18) X(19) X(20)

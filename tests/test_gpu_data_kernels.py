@@ -185,3 +185,27 @@ def test_sums_over_scans_round_less_than_one_chain(g, ctx, torch_cuda, K, P, T, 
 
     assert off(out.cpu().numpy(), bwq) <= 0.7 * off(bw, bwq)
     assert off(res.cpu().numpy(), rssq) <= 0.7 * off(rss, rssq)
+
+
+@pytest.mark.parametrize("K", [10, 11, 15, 24])
+def test_assembly_of_few_and_many_voxels(g, ctx, torch_cuda, K):
+    """b_w and the blocks of a voxel do not depend on whether b_w is formed by
+    the assembly's launch (few workgroups) or by its own (many, from K = 11)."""
+    torch = torch_cuda
+    nx, few, T, P = 13121, 500, 45, 2
+    X, Y, A, lam = problem(nx, K, T, P, 2, K)
+    got = []
+    for n in (nx, few):
+        op = g.gp_op_create(ctx, np.ones((1, 1, n), dtype=np.uint8), 4, K)
+        d = g.gp_data_create(op, T, P, X, dev(torch, Y[:, :n]))
+        bw = torch.full((K, n), float("nan"), dtype=torch.float64, device="cuda")
+        g.gp_data_assemble(d, dev(torch, lam[:n]), 2, dev(torch, A[:, :, :n]), bw)
+        g.gp_op_set_alpha(op, np.zeros(K))
+        x, y = torch.ones((1, K, n), dtype=torch.float64, device="cuda"), torch.zeros((1, K, n), dtype=torch.float64,
+                                                                                     device="cuda")
+        g.gp_apply(op, 1, x, y)
+        got.append((bw[:, :few].clone(), y[:, :, :few].clone()))
+        g.gp_data_destroy(d)
+        g.gp_op_destroy(op)
+    assert torch.isfinite(got[0][0]).all()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
