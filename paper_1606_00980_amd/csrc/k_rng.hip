@@ -21,6 +21,8 @@
 //                d = a - 1/3.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include <cstdint>
 
 #include "launch.hpp"
@@ -78,26 +80,31 @@ __global__ __launch_bounds__(256) void k_normal(uint64_t seed, uint64_t stream, 
 
 // A lane draws its block's words again for 16 of the block's 128 signs, so that
 // a wavefront writes 1 KB in a row (a lane writing its whole block byte by byte
-// took 21 us for 2 million signs; 3 so).
+// took 21 us for 2 million signs; 3 so).  The workgroups go over the signs in
+// strides of the grid, which holds all lanes up to 2^35 signs: a launch of one
+// lane per 16 signs would not go beyond 2^36 (2^32 lanes).
+constexpr unsigned SIGN_BLOCKS = 1u << 23;
+
 __global__ __launch_bounds__(256) void k_rademacher(uint64_t seed, uint64_t stream, size_t n,
-                                                    int8_t* __restrict__ out) {
-  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x, e0 = t * 16;
-  if (e0 >= n) return;
-  const U4 w = draw(t / 8, seed, stream);
-  const int sub = (int)(t % 8);
-  const uint32_t word = sub < 4 ? (sub < 2 ? w.x : w.y) : (sub < 6 ? w.z : w.w);
-  const uint32_t bits = (word >> (16 * (sub % 2))) & 0xFFFFu;
-  uint32_t v[4];
+                                                      int8_t* __restrict__ out) {
+  for (size_t t = (size_t)blockIdx.x * 256 + threadIdx.x; t * 16 < n; t += (size_t)gridDim.x * 256) {
+    const size_t e0 = t * 16;
+    const U4 w = draw(t / 8, seed, stream);
+    const int sub = (int)(t % 8);
+    const uint32_t word = sub < 4 ? (sub < 2 ? w.x : w.y) : (sub < 6 ? w.z : w.w);
+    const uint32_t bits = (word >> (16 * (sub % 2))) & 0xFFFFu;
+    uint32_t v[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    v[i] = 0xFFFFFFFFu;   // -1 in every byte; +1 where the bit is set
+    for (int i = 0; i < 4; ++i) {
+      v[i] = 0xFFFFFFFFu;   // -1 in every byte; +1 where the bit is set
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[i] ^= ((bits >> (4 * i + j)) & 1u) * (0xFEu << (8 * j));
-  }
-  if (n - e0 >= 16 && ((uintptr_t)(out + e0) & 15) == 0) {
-    *(uint4*)(out + e0) = make_uint4(v[0], v[1], v[2], v[3]);
-  } else {
-    for (int i = 0; i < 16 && e0 + i < n; ++i) out[e0 + i] = (int8_t)(v[i / 4] >> (8 * (i % 4)));
+      for (int j = 0; j < 4; ++j) v[i] ^= ((bits >> (4 * i + j)) & 1u) * (0xFEu << (8 * j));
+    }
+    if (n - e0 >= 16 && ((uintptr_t)(out + e0) & 15) == 0) {
+      *(uint4*)(out + e0) = make_uint4(v[0], v[1], v[2], v[3]);
+    } else {
+      for (int i = 0; i < 16 && e0 + i < n; ++i) out[e0 + i] = (int8_t)(v[i / 4] >> (8 * (i % 4)));
+    }
   }
 }
 
@@ -162,8 +169,8 @@ hipError_t launch_rng_gamma(hipStream_t s, uint64_t seed, uint64_t stream, size_
 
 hipError_t launch_rng_rademacher(hipStream_t s, uint64_t seed, uint64_t stream, size_t n, int8_t* out) {
   if (n == 0) return hipSuccess;
-  const size_t lanes = (n + 15) / 16;
-  GP_LAUNCH(k_rademacher, dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, s, seed, stream, n, out);
+  const size_t lanes = (n + 15) / 16, blocks = std::min<size_t>((lanes + 255) / 256, SIGN_BLOCKS);
+  GP_LAUNCH(k_rademacher, dim3((unsigned)blocks), dim3(256), 0, s, seed, stream, n, out);
   return hipGetLastError();
 }
 

@@ -58,3 +58,22 @@ def test_quadratic_forms(g, ctx, torch_cuda, K, dims, conn):
         g.gp_op_destroy(op)
     # a sum of at most 3 N squared differences in another order
     assert np.allclose(qf, orc.quadform(grid, W), rtol=1e-14 * (3 * N + 8), atol=0)
+
+
+def test_signs_beyond_one_launchs_lanes(g, ctx, torch_cuda):
+    """2^36 + 100 signs (64 GiB): more than lanes of 16 signs fit a launch."""
+    n = (1 << 36) + 100
+    free = torch_cuda.cuda.mem_get_info()[0]
+    if free < n + (8 << 30):
+        pytest.skip("needs 72 GiB of device memory")
+    out = torch_cuda.empty(n, dtype=torch_cuda.int8, device="cuda")
+    for at in (0, (1 << 35) - 128, 1 << 35, (1 << 36) - 128):
+        out[at:at + 228] = 0
+    g.gp_rng_rademacher(ctx, 9, 4, n, out)
+    for at in (0, (1 << 35) - 128, 1 << 35, (1 << 36) - 128):
+        e = np.arange(at, min(at + 228, n), dtype=np.uint64)
+        w = philox.philox4x32_10(np.arange(at // 128, int(e[-1]) // 128 + 1, dtype=np.uint64), 9, 4)
+        bits = (w[(e // 128 - at // 128).astype(int), (e % 128 // 32).astype(int)] >> (e % 32).astype(np.uint32)) & 1
+        assert np.array_equal(out[at:at + len(e)].cpu().numpy(), np.where(bits == 1, 1, -1))
+    del out
+    torch_cuda.cuda.empty_cache()
