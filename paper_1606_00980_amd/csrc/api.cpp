@@ -1045,6 +1045,16 @@ int run_group(gp_ctx* c, const std::vector<Item>& items, const gp_opts& o, gp_st
       HIPTRY(hipMemcpy(pf.data(), ws + lay[j].prof, NPROF * sizeof(long long), hipMemcpyDeviceToHost));
       const double N = it.op->N, K = it.op->K, ts = (double)tsz;
       const double NB = K * (K + 1) / 2, NP = o.precond == GP_PRECOND_JACOBI ? K : NB;
+      if (j >= nl) {
+        // one launch for the whole solve, timed as a matvec: per right-hand side
+        // the blocks once, b and x at the refinements, x at its updates; the
+        // other vectors stay in registers and LDS
+        const double add = std::max<double>(std::max(pf[PF_ADDSOL_D], pf[PF_ADDSOL_P]), pf[PF_ADDSOL_FRESH]);
+        prof_add(c, GP_KERNEL_MATVEC, pf[PF_MATVEC_RHS] * N,
+                 N * 8.0 * (pf[PF_MATVEC_ACT] * (NB + NP) +
+                            K * (2.0 * pf[PF_REFINE_RHS] - pf[PF_REFINE_X0] + 2.0 * add - pf[PF_ADDSOL_FRESH])));
+        continue;
+      }
       // algorithmic bytes: every vector entry, block and preconditioner entry
       // a launch needs, read or written once
       // x (unless the start value is zero) and b read, r and p written

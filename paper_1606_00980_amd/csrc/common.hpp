@@ -17,6 +17,7 @@ enum ProfSlot : int {
   PF_MATVEC_ACT, PF_UPDATE_RHS, PF_UPDATE_FRESH, PF_UPDATE_ACT,
   PF_REFINE_X0,      // refinements with a zero start value (x not read)
   PF_ADDSOL_FRESH,   // first x += d from a zero start value (x written, not read)
+  PF_UPDATE_SEEN,    // PF_MATVEC_ACT of the last step counted in PF_UPDATE_ACT (see count_update)
 };
 constexpr int RCMAX = 16;    // right-hand sides per workgroup, upper bound
 constexpr int UPAIR_KMAX = 10;   // FP32 red-stage vectors stored in right-hand-side pairs up to this K

@@ -454,6 +454,21 @@ __device__ inline void step_records(const Prob& pr, int nt, int r0, int r1, bool
   __syncthreads();
 }
 
+// Counts an update launch that finalises its steps (pr.fin) in PF_UPDATE_ACT
+// when the step of any right-hand side goes on.  The states change while the
+// launch runs, so each chunk's first tile looks at its own records; the first
+// of them to find one counts, which is seen by the number of the step, the
+// matvec launches with work so far (no update changes it).
+__device__ inline void count_update(const Prob& pr, const StepRec* rec, int n) {
+  if (!pr.prof || threadIdx.x != 0) return;
+  bool any = false;
+  for (int i = 0; i < n; ++i) any = any || rec[i].go;
+  if (!any) return;
+  const unsigned long long step = (unsigned long long)pr.prof[PF_MATVEC_ACT];
+  if (atomicMax((unsigned long long*)&pr.prof[PF_UPDATE_SEEN], step) < step)
+    atomicAdd((unsigned long long*)&pr.prof[PF_UPDATE_ACT], 1ull);
+}
+
 constexpr int FIN_WAVES = 4;   // right-hand sides finalised per workgroup
 
 // One wavefront per right-hand side of one problem: sum that right-hand side's
@@ -750,13 +765,14 @@ __global__ __launch_bounds__(TILE, (OccMV<T, K>::v)) void k_update(const Prob* _
     const Prob& pr = probs[w.p];
     const OpDev& op = pr.op;
     const int N = op.N;
-    if (w.tile == 0 && w.chunk == 0) prof_launch(pr, PF_UPDATE_ACT, PH_INNER);
+    if (w.tile == 0 && w.chunk == 0 && !pr.fin) prof_launch(pr, PF_UPDATE_ACT, PH_INNER);
     const int r0 = w.r0, r1 = w.r1;
     bool any = false;
     for (int r = r0; r < r1; ++r) any = any || step_active(pr, r);
     if (!any) continue;
     __syncthreads();   // the previous item's records have been read
     step_records(pr, op.ntiles, r0, r1, w.tile == 0, rec);
+    if (w.tile == 0 && pr.fin) count_update(pr, rec, r1 - r0);
     if (!w.valid) continue;
     const unsigned o = (unsigned)w.n * sizeof(T);
     const Slab<T> Ps(OpT<T>::P(op), NP, N);

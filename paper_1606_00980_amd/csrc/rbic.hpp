@@ -1054,13 +1054,14 @@ __global__ __launch_bounds__(TILE) void k_rb_update(const RbProb* __restrict__ p
   const RbWork w = rb_item<RBW_BLACK>(probs, nprob);
   const RbProb& P = probs[w.p];
   const RbDev& rb = P.rb;
-  count_launch(P, w, PH_INNER, PF_UPDATE_ACT);
+  if (!P.pr.fin) count_launch(P, w, PH_INNER, PF_UPDATE_ACT);
   const int i = w.tile * TILE + threadIdx.x;
   bool any = false;
   for (int r = w.r0; r < w.r1; ++r) any = any || step_active(P.pr, r);
   if (!any) return;
   __shared__ StepRec rec[RCMAX];
   step_records(P.pr, rb.ntB, w.r0, w.r1, w.tile == 0, rec);
+  if (w.tile == 0 && P.pr.fin) count_update(P.pr, rec, w.r1 - w.r0);
   if (i >= rb.NB) return;
   const unsigned oT = (unsigned)i * (unsigned)sizeof(T);
   const Packed<T, K, HOLD> S(RbT<T>::S(rb), rb.NB, oT);
