@@ -454,7 +454,9 @@ int gp_trace(gp_op* op, int m, const int8_t* probes, double* u, double* tr_total
  * operator under *base (host; NULL = defaults), keep the fastest in the
  * context for (K, log2 N, R rounded up to a power of two, precision,
  * preconditioner) and copy it into *best (host, may be NULL).  Later solves
- * whose rhs_tile / wg_per_cu / matvec are left automatic use it.  Blocking.
+ * whose rhs_tile / wg_per_cu / matvec are left automatic use it.  *best has
+ * them automatic where that is faster still (small operators in FP64, solved
+ * whole in one workgroup per right-hand side).  Blocking.
  * gp_tune_save / gp_tune_load: the context's table as a JSON file.          */
 int gp_autotune(gp_op* op, int R, const gp_opts* base, gp_opts* best);
 int gp_tune_save(gp_ctx* ctx, const char* path);

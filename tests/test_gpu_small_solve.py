@@ -154,3 +154,29 @@ def test_jacobi_around_the_largest_k(g, ctx, torch_cuda, K, N):
         g.gp_solve(op, R, bd, alone, g.gp_opts_default(**kw))
         assert torch.equal(alone, x)
         g.gp_op_destroy(op)
+
+
+def test_autotune_knows_the_one_workgroup_solve(g, ctx, torch_cuda, tmp_path):
+    """On an operator that automatic options solve in one workgroup, the tuner
+    returns them (they are several times faster than any grouped configuration)
+    and still keeps a grouped entry in its table; on a larger one it returns a
+    grouped configuration as ever."""
+    torch = torch_cuda
+    for nx, ny, small in ((61, 40, True), (120, 110, False)):
+        mask, B, alpha, b = operator(nx, ny, 2, nx)
+        op = g.gp_op_create(ctx, mask, 4, 2)
+        Bd, bd = torch.from_numpy(B).cuda(), torch.from_numpy(b).cuda()
+        g.gp_op_set_blocks(op, Bd)
+        g.gp_op_set_alpha(op, alpha)
+        o = g.gp_opts_default(tol=1e-10, precision=g.GP_PREC_FP64, zero_guess=1)
+        best = g.gp_autotune(op, 3, o)
+        assert (best.rhs_tile == 0) == small and (best.matvec == g.GP_MATVEC_AUTO) == small
+        x, y = torch.zeros_like(bd), torch.zeros_like(bd)
+        g.gp_solve(op, 3, bd, x, best)
+        g.gp_solve(op, 3, bd, y, o)
+        if small:
+            assert torch.equal(x, y)
+        path = str(tmp_path / f"tune{nx}.json")
+        g.gp_tune_save(ctx, path)
+        g.gp_tune_load(ctx, path)
+        g.gp_op_destroy(op)
