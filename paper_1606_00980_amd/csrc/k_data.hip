@@ -311,11 +311,12 @@ __global__ __launch_bounds__(TENSOR_WG) void k_data_tensors(int T, int K, int Ks
 //   B_kl = lambda (XX_kl - sum_p (R_klp + R_lkp) m1_p + sum_pq S_pklq m2_pq)
 //   b_k  = lambda (YX_k - sum_p Bt_pk m1_p + sum_pq Dt_pkq m2_pq).
 // blockIdx.y = 0: the block; the others, if any, b_n, ASM_KC regressors each.
-// From K = 11 on the block's registers leave one or two wavefronts a SIMD, which
-// b_n's loads then wait in: there it has a kernel of its own (K = 15: 60 + 21
-// against 104 us fused; K = 6: 14 us fused against 13 + 12), unless the launch
-// leaves SIMDs empty anyway (at most ASM_FEW workgroups; K = 16, N = 908: 46 us
-// fused against 43 + 12).
+// From K = 14 on the block's registers leave one wavefront a SIMD, which b_n's
+// loads then wait in: there it has a kernel of its own (N = 52,740; two kernels
+// against one, us: K = 6 13 + 12 and 14, K = 10 25 + 13 and 28, K = 11 26 + 14 and
+// 34, K = 13 36 + 16 and 45, K = 15 60 + 21 and 104, K = 16 67 + 19 and 108),
+// unless the launch leaves SIMDs empty anyway (at most ASM_FEW workgroups;
+// K = 16, N = 908: 43 + 12 and 46).
 // Bound: the tensors read for b_n and the three packed arrays written, all
 // coalesced (at K = 15, P = 3, N = 52,740: 225 MB, 45 us at 5 TB/s).
 // Measured there 81 us; the rows of [N][K][K] blocks written by one kernel
@@ -323,7 +324,7 @@ __global__ __launch_bounds__(TENSOR_WG) void k_data_tensors(int T, int K, int Ks
 // took 112 + 57 us (K = 6: 29 + 9 to 14 us).
 constexpr int ASM_WG = 64;
 constexpr int ASM_KC = 3;   // regressors of b_w per lane
-template <int K> constexpr bool ASM_FUSED = K <= 10;
+template <int K> constexpr bool ASM_FUSED = K <= 13;
 constexpr unsigned ASM_FEW = 1024;
 
 constexpr int ASM_NQ = PMAX * (PMAX + 1) / 2;

@@ -447,7 +447,7 @@ __global__ __launch_bounds__(SETUP_WG) void k_rb_setup_black(RbDev rb, const dou
   // compiler waits for entry after entry at K = 7, 9 and 11 (N = 908: 67 us at
   // K = 11, 27 neighbour by neighbour, 17 so).
   const Slab<double> Ps(rb.P64, NB, rb.NR);
-  constexpr int SE = K <= 11 ? 8 : 4;
+  constexpr int SE = 8;   // (4: 19.4 for 17.0 us at K = 11, N = 2,620; 54 for 52 at K = 16, N = 28,000)
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const double ak = rb.alpha64[k];
@@ -650,9 +650,10 @@ __global__ __launch_bounds__(TILE) void k_rb_split_black(RbDev rb, int R, const 
 }
 
 // f(rr) for the right-hand sides of [r0, r1) that are on(), two at a time; a
-// last one alone comes twice (its values are formed and stored twice).  The
-// FP64 stages of the outer step take two for K = 9..12: at one right-hand
-// side they read 660 bytes of voxel blocks beside 320 of vectors (K = 10), and
+// last one alone comes as both (the red stage then runs it alone, the refinement
+// forms and stores its values twice).  The FP64 stages of the outer step take
+// two for K = 9..12: at one right-hand side they read 660 bytes of voxel blocks
+// beside 320 of vectors (K = 10), and
 // the registers kept few loads in flight.  Two share the blocks, and the loads
 // go in groups whose size is set here (rows of gathers, block entries): the
 // compiler's own order held either too few or, moved past one another, all of

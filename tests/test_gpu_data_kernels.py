@@ -187,10 +187,10 @@ def test_sums_over_scans_round_less_than_one_chain(g, ctx, torch_cuda, K, P, T, 
     assert off(res.cpu().numpy(), rssq) <= 0.7 * off(rss, rssq)
 
 
-@pytest.mark.parametrize("K", [10, 11, 15, 24])
+@pytest.mark.parametrize("K", [10, 13, 14, 15, 24])
 def test_assembly_of_few_and_many_voxels(g, ctx, torch_cuda, K):
     """b_w and the blocks of a voxel do not depend on whether b_w is formed by
-    the assembly's launch (few workgroups) or by its own (many, from K = 11)."""
+    the assembly's launch (few workgroups) or by its own (many, from K = 14)."""
     torch = torch_cuda
     nx, few, T, P = 13121, 500, 45, 2
     X, Y, A, lam = problem(nx, K, T, P, 2, K)
