@@ -34,27 +34,26 @@ namespace {
 
 constexpr int DT = 256;   // threads per workgroup
 
-// Compile-time lags: for_lags<P>(f) calls f(Lag<0>), .., f(Lag<P - 1>).
-template <int V> struct Lag { static constexpr int v = V; };
-template <int P, int I = 0, typename F>
-__device__ __forceinline__ void for_lags(const F& f) {
-  if constexpr (I < P) {
-    f(Lag<I>{});
-    for_lags<P, I + 1>(f);
-  }
-}
-
 constexpr int PMAX = 4;   // largest AR order
+constexpr int GSCANS = 128;   // scans of the design staged at a time
 
-// One wavefront per global tensor entry, the scans dealt to the lanes.  A
-// thread per entry walked T dependent loads in turn (85 us at K = 15, T = 200;
-// 8 us with the wavefront).
+// Every sum over scans of this file (globals and tensors) is one chain of fused
+// multiply-adds over t = P .. T - 1, an entry of its own, as the definitions
+// above read: the same data give the same bits in whatever kernel forms them.
+// (Sums shared by the lag pairs, or added in parts, are as good or better
+// against exact values, but a last bit moved in the data moves the FP32 inner
+// solves to another path: draws 1e-11 and noise precisions up to 1e-9 away.)
+
+// One lane per global tensor entry, the design staged in LDS GSCANS scans at a
+// time (with the P before them).
+// A thread per entry reading it from memory walked T dependent loads in turn
+// (85 us at K = 15, T = 200; 12 us so).
 __global__ __launch_bounds__(DT) void k_data_globals(int T, int K, int Ks, int P, const double* __restrict__ X,
                                                      double* __restrict__ G) {
-  const int e = (blockIdx.x * DT + threadIdx.x) / 64, lane = threadIdx.x % 64;
+  __shared__ double sX[(PMAX + GSCANS) * KMAX];
+  const int e = blockIdx.x * DT + threadIdx.x;
   const int nXX = K * K, nR = K * K * P, nS = P * K * K * P;
-  if (e >= nXX + nR + nS) return;
-  int k, l, a = 0, b = 0;   // sum over scans of X[t - a][k] X[t - b][l]
+  int k = 0, l = 0, a = 0, b = 0;   // sum over scans of X[t - a][k] X[t - b][l]
   if (e < nXX) {
     k = e / K;
     l = e % K;
@@ -63,18 +62,24 @@ __global__ __launch_bounds__(DT) void k_data_globals(int T, int K, int Ks, int P
     k = i / (K * P);
     l = (i / P) % K;
     b = 1 + i % P;
-  } else {
+  } else if (e < nXX + nR + nS) {
     const int i = e - nXX - nR;
     a = 1 + i / (K * K * P);
     k = (i / (K * P)) % K;
     l = (i / P) % K;
     b = 1 + i % P;
   }
+  const double *xa = sX + (P - a) * K + k, *xb = sX + (P - b) * K + l;
   double s = 0.0;
-  for (int t = P + lane; t < T; t += 64) s += X[(t - a) * Ks + k] * X[(t - b) * Ks + l];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if (lane == 0) G[e] = s;
+  for (int t0 = P; t0 < T; t0 += GSCANS) {
+    const int nt = min(GSCANS, T - t0);
+    __syncthreads();
+    for (int i = threadIdx.x; i < (P + nt) * K; i += DT) sX[i] = X[(size_t)(t0 - P + i / K) * Ks + i % K];
+    __syncthreads();
+#pragma unroll 8
+    for (int t = 0; t < nt; ++t) s = __builtin_fma(xa[t * K], xb[t * K], s);
+  }
+  if (e < nXX + nR + nS) G[e] = s;
 }
 
 // Coefficient table of the voxel blocks, [K(K+1)/2][TAB]: packed entry (k, l) of
@@ -82,6 +87,9 @@ __global__ __launch_bounds__(DT) void k_data_globals(int T, int K, int Ks, int P
 // coefficients of a_p (PMAX slots), then those of a_p a_q, p <= q (packed by
 // tab_pair(p, q, PMAX)); slots past P are zero.
 constexpr int TAB = 16;
+// Table of the assembly behind it, [K(K+1)/2][BTAB]: XX_kl, R_klp + R_lkp (PMAX
+// slots), S_pklq (PMAX x PMAX slots); zero past P.
+constexpr int BTAB = 1 + PMAX + PMAX * PMAX;
 
 __host__ __device__ constexpr int tab_pair(int p, int q, int P) { return p * P - p * (p - 1) / 2 + q - p; }   // p <= q < P
 
@@ -110,136 +118,114 @@ __global__ __launch_bounds__(DT) void k_data_table(int K, int P, const double* _
         }
   }
   Tab[i] = v;
+  // and the entry's own parts for the assembly, in the order it adds them
+  if (c == 0) {
+    double* t = Tab + (size_t)K * (K + 1) / 2 * TAB + (size_t)e * BTAB;
+    t[0] = G[k * K + l];
+    for (int p = 0; p < PMAX; ++p) t[1 + p] = p < P ? R[(k * K + l) * P + p] + R[(l * K + k) * P + p] : 0.0;
+    for (int p = 0; p < PMAX; ++p)
+      for (int q = 0; q < PMAX; ++q)
+        t[1 + PMAX + p * PMAX + q] = p < P && q < P ? S[((p * K + k) * K + l) * P + q] : 0.0;
+  }
 }
 
-// Per voxel, the sums C(a, b)[k] = sum_{t=P}^{T-1} y[t - a] X[t - b][k], a, b = 0..P,
-// that YX = C(0, 0), Bt = C(0, p + 1) + C(p + 1, 0) and Dt = C(p + 1, q + 1)
-// are made of, and the products of y with itself (YY, dY, dd).
-//
-// With j = t - b, C(a, b) runs over j = P - b .. T - 1 - b of y[j - d] X[j][k],
-// d = a - b: the scans j = P .. T - 1 - P belong to every pair of a lag d, so
-// 2P + 1 running sums serve all (P + 1)^2 pairs and the at most P scans at
-// either end are added per pair.  A lane holds one voxel, a window of 2P + 1
-// values of y in a ring of registers (loaded once per scan, coalesced) and the
-// sums of KC regressors; the design's rows (padded to whole chunks) are
-// wave-uniform: one 32-byte scalar load per scan.
-// Bound: the FP64 multiply-adds, (2P + 1) K T per voxel (about 30 us at
-// N = 52,740, K = 15, T = 200, P = 3), and the scalar loads of the design in
-// front of them.  133 us there; a workgroup per output entry, which read Y
-// once per entry (208 passes), took 2,427 us.
-// The running sums are added to the totals every 28 scans or so (tensor_fold).
-// In one chain over all scans each addition rounds at the size of the whole
-// sum: b_w was 3.7e-16 off (rms, relative; T = 200, K = 15; the kernel of an
-// entry per workgroup 3.7e-16 as well) and 1.8e-16 so, the residual sums
-// 1.3e-11 and 5e-12, for 13 us.
+// Per voxel and regressor, YX, Bt and Dt, and per voxel YY, dY and dd, in one
+// pass over Y per chunk of KC regressors.  A lane holds one voxel, the last
+// P + 1 values of y in a ring of registers (loaded once per scan, coalesced) and
+// the (P + 1)^2 sums of KC regressors; the design's rows (padded to whole
+// chunks) are wave-uniform: one scalar load of KC doubles per scan.
+// Bound: the FP64 operations, (1 + 3 P + P^2) K T per voxel, and the scalar loads
+// of the design in front of them.  163 us at N = 52,740, K = 15, T = 200,
+// P = 3 (K = 6: 97); a workgroup per output entry, which read Y once per entry (208
+// passes), took 2,427.
 // blockIdx.y = regressor chunk; the last one forms YY, dY and dd.
+// KC = 4, or less where such a launch leaves SIMDs idle: a wavefront's chain over
+// the scans is then shorter (KC = 1, 2, 4 at P = 3, T = 200, us: N = 900, K = 6 29, 46
+// and 69; N = 5,000, K = 6 57, 51, 69; N = 10,000, K = 10 63, 60, 58; N = 20,000,
+// K = 6 77, 69, 77; N = 20,000, K = 15 109, 85, 76).
 constexpr int TENSOR_KC = 4;
 constexpr int TENSOR_WG = 64;
-constexpr int tensor_fold(int W) { return W >= 28 ? 1 : 28 / W; }   // in groups of W scans
 
-template <int P>
+template <int P, int KC>
 __device__ __forceinline__ void tensor_cross(int T, int K, int Ks, int N, int n, int k0, const double* __restrict__ X,
                                              const double* __restrict__ Y, double* __restrict__ YX,
                                              double* __restrict__ Bt, double* __restrict__ Dt) {
-  constexpr int W = 2 * P + 1, KC = TENSOR_KC;
+  // scans GS at a time, their data loaded while the last GS are used: the fewer
+  // the sums, the more scans it takes to cover a load from memory
+  constexpr int W = P + 1, P1 = P > 0 ? P : 1, GS = W * (KC == 1 ? 16 / W : KC == 2 ? 8 / W : 1);
   const double* y = Y + n;
-  // tot[d + P][c] = sum_j y[j - d] X[j][k0 + c], acc the part of the last scans
-  constexpr int FOLD = tensor_fold(W);
-  double acc[W][KC], tot[W][KC];
+  double yx[KC], bt[P1][KC], dt[P1][P1][KC], yr[W], xr[W][KC], nxt[GS];
 #pragma unroll
-  for (int d = 0; d < W; ++d)
+  for (int c = 0; c < KC; ++c) {
+    yx[c] = 0.0;
 #pragma unroll
-    for (int c = 0; c < KC; ++c) acc[d][c] = tot[d][c] = 0.0;
-  auto fold = [&]() {
+    for (int p = 0; p < P; ++p) {
+      bt[p][c] = 0.0;
 #pragma unroll
-    for (int d = 0; d < W; ++d)
+      for (int q = 0; q < P; ++q) dt[p][q][c] = 0.0;
+    }
+  }
+  // scan m sits in slot m % W of both rings
+#pragma unroll
+  for (int m = 0; m < P; ++m) {
+    yr[m] = y[(size_t)m * N];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) xr[m][c] = X[(size_t)m * Ks + k0 + c];
+  }
+#pragma unroll
+  for (int i = 0; i < GS; ++i) nxt[i] = y[(size_t)min(P + i, T - 1) * N];
+  // scan t + i of a group of GS, t = P (mod W)
+  auto scan = [&](int t, int i, double yn) {
+#pragma clang fp contract(off)
+    const int s0 = (P + i) % W;
+    yr[s0] = yn;
+    const double* x = X + (size_t)(t + i) * Ks + k0;
+#pragma unroll
+    for (int c = 0; c < KC; ++c) xr[s0][c] = x[c];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) yx[c] = __builtin_fma(yr[s0], xr[s0][c], yx[c]);
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      const int sp = (P + i - 1 - p) % W;
 #pragma unroll
       for (int c = 0; c < KC; ++c) {
-        tot[d][c] += acc[d][c];
-        acc[d][c] = 0.0;
+        const double m = yr[sp] * xr[s0][c];
+        bt[p][c] += __builtin_fma(yr[s0], xr[sp][c], m);
       }
-  };
-  const int jend = T - 1 - P;
-  if (jend >= P) {
-    // y[m] of the window sits in ring[m % W]
-    double ring[W], nxt[W];
 #pragma unroll
-    for (int m = 0; m < 2 * P; ++m) ring[m] = y[(size_t)m * N];
+      for (int q = 0; q < P; ++q) {
+        const int sq = (P + i - 1 - q) % W;
 #pragma unroll
-    for (int i = 0; i < W; ++i) nxt[i] = y[(size_t)min(2 * P + i, T - 1) * N];
-    // scan j + i of a block: y[j + i + P] enters the ring
-    auto scan = [&](int j, int i, double yn) {
-      ring[(2 * P + i) % W] = yn;
-      const double* xr = X + (size_t)(j + i) * Ks + k0;
-      double x[KC];
-#pragma unroll
-      for (int c = 0; c < KC; ++c) x[c] = xr[c];
-#pragma unroll
-      for (int d = -P; d <= P; ++d) {
-        const double yv = ring[(P + i - d + W) % W];
-#pragma unroll
-        for (int c = 0; c < KC; ++c) acc[d + P][c] += yv * x[c];
+        for (int c = 0; c < KC; ++c) dt[p][q][c] = __builtin_fma(yr[sp], xr[sq][c], dt[p][q][c]);
       }
-    };
-    int j = P;
-#pragma unroll 1
-    while (j + W - 1 <= jend) {
-#pragma unroll 1
-      for (int f = 0; f < FOLD && j + W - 1 <= jend; ++f, j += W) {
-        double cur[W];
-#pragma unroll
-        for (int i = 0; i < W; ++i) cur[i] = nxt[i];
-        // the next W scans are loaded while these are used
-#pragma unroll
-        for (int i = 0; i < W; ++i) nxt[i] = y[(size_t)min(j + W + P + i, T - 1) * N];
-#pragma unroll
-        for (int i = 0; i < W; ++i) scan(j, i, cur[i]);
-      }
-      fold();
     }
+  };
+  int t = P;
+#pragma unroll 1
+  for (; t + GS <= T; t += GS) {
+    double cur[GS];
 #pragma unroll
-    for (int i = 0; i < W - 1; ++i)
-      if (j + i <= jend) scan(j, i, nxt[i]);
-    fold();
-  }
-  // the scans at the ends: y[0 .. 2P) and y[T - 2P .. T), where they exist
-  constexpr int P2 = P > 0 ? 2 * P : 1, P1 = P > 0 ? P : 1;
-  double yl[P2], yh[P2], xl[P1][KC], xh[P1][KC];
+    for (int i = 0; i < GS; ++i) cur[i] = nxt[i];
+    // the next group's are loaded while these are used
 #pragma unroll
-  for (int m = 0; m < 2 * P; ++m) {
-    yl[m] = y[(size_t)min(m, T - 1) * N];
-    yh[m] = y[(size_t)max(T - 1 - m, 0) * N];
+    for (int i = 0; i < GS; ++i) nxt[i] = y[(size_t)min(t + GS + i, T - 1) * N];
+#pragma unroll
+    for (int i = 0; i < GS; ++i) scan(t, i, cur[i]);
   }
 #pragma unroll
-  for (int i = 0; i < P; ++i)
-#pragma unroll
-    for (int c = 0; c < KC; ++c) {
-      xl[i][c] = X[(size_t)min(i, T - 1) * Ks + k0 + c];
-      xh[i][c] = X[(size_t)max(T - 1 - i, 0) * Ks + k0 + c];
-    }
-  auto sum = [&](auto A, auto B, int c) {
-    constexpr int a = decltype(A)::v, b = decltype(B)::v;
-    double s = 0.0;
-#pragma unroll
-    for (int i = 0; i < P; ++i) {
-      if (i >= P - b && i <= T - 1 - b) s += yl[i + b - a >= 0 ? i + b - a : 0] * xl[i][c];
-      if (i >= b && T - 1 - i >= P) s += yh[i - b + a >= 0 ? i - b + a : 0] * xh[i][c];
-    }
-    return tot[a - b + P][c] + s;
-  };
+  for (int i = 0; i < GS - 1; ++i)
+    if (t + i < T) scan(t, i, nxt[i]);
 #pragma unroll
   for (int c = 0; c < KC; ++c) {
     const int k = k0 + c;
     if (k >= K) break;
-    YX[(size_t)k * N + n] = sum(Lag<0>{}, Lag<0>{}, c);
-    for_lags<P>([&](auto Pp) {
-      constexpr int p = decltype(Pp)::v;
-      Bt[((size_t)p * K + k) * N + n] = sum(Lag<0>{}, Lag<p + 1>{}, c) + sum(Lag<p + 1>{}, Lag<0>{}, c);
-      for_lags<P>([&](auto Q) {
-        constexpr int q = decltype(Q)::v;
-        Dt[(((size_t)p * K + k) * P + q) * N + n] = sum(Lag<p + 1>{}, Lag<q + 1>{}, c);
-      });
-    });
+    YX[(size_t)k * N + n] = yx[c];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      Bt[((size_t)p * K + k) * N + n] = bt[p][c];
+#pragma unroll
+      for (int q = 0; q < P; ++q) Dt[(((size_t)p * K + k) * P + q) * N + n] = dt[p][q][c];
+    }
   }
 }
 
@@ -248,48 +234,38 @@ __device__ __forceinline__ void tensor_auto(int T, int N, int n, const double* _
                                             double* __restrict__ dY, double* __restrict__ dd) {
   constexpr int W = P + 1;
   const double* y = Y + n;
-  double acc[W][W], tot[W][W], ring[W];   // tot[a][b], a <= b: sum_t y[t - a] y[t - b], acc the part of the last scans
+  double acc[W][W], ring[W];   // acc[a][b], a <= b: sum_t y[t - a] y[t - b]
 #pragma unroll
   for (int a = 0; a < W; ++a)
 #pragma unroll
-    for (int b = 0; b < W; ++b) acc[a][b] = tot[a][b] = 0.0;
+    for (int b = 0; b < W; ++b) acc[a][b] = 0.0;
 #pragma unroll
   for (int m = 0; m < P; ++m) ring[m] = y[(size_t)m * N];
-#pragma unroll 1
-  for (int t = P; t < T;) {
-#pragma unroll 1
-    for (int f = 0; f < tensor_fold(W) && t < T; ++f, t += W) {
-      double cur[W];
+  for (int t = P; t < T; t += W) {
+    double cur[W];
 #pragma unroll
-      for (int i = 0; i < W; ++i) cur[i] = y[(size_t)min(t + i, T - 1) * N];
+    for (int i = 0; i < W; ++i) cur[i] = y[(size_t)min(t + i, T - 1) * N];
 #pragma unroll
-      for (int i = 0; i < W; ++i) {
-        if (t + i >= T) break;
-        ring[(P + i) % W] = cur[i];
+    for (int i = 0; i < W; ++i) {
+      if (t + i >= T) break;
+      ring[(P + i) % W] = cur[i];
 #pragma unroll
-        for (int a = 0; a < W; ++a)
+      for (int a = 0; a < W; ++a)
 #pragma unroll
-          for (int b = a; b < W; ++b) acc[a][b] += ring[(P + i - a + W) % W] * ring[(P + i - b + W) % W];
-      }
+        for (int b = a; b < W; ++b)
+          acc[a][b] = __builtin_fma(ring[(P + i - a + W) % W], ring[(P + i - b + W) % W], acc[a][b]);
     }
-#pragma unroll
-    for (int a = 0; a < W; ++a)
-#pragma unroll
-      for (int b = a; b < W; ++b) {
-        tot[a][b] += acc[a][b];
-        acc[a][b] = 0.0;
-      }
   }
-  YY[n] = tot[0][0];
+  YY[n] = acc[0][0];
 #pragma unroll
-  for (int p = 0; p < P; ++p) dY[(size_t)p * N + n] = tot[0][p + 1];
+  for (int p = 0; p < P; ++p) dY[(size_t)p * N + n] = acc[0][p + 1];
 #pragma unroll
   for (int p = 0; p < P; ++p)
 #pragma unroll
-    for (int q = 0; q < P; ++q) dd[((size_t)p * P + q) * N + n] = tot[(p < q ? p : q) + 1][(p < q ? q : p) + 1];
+    for (int q = 0; q < P; ++q) dd[((size_t)p * P + q) * N + n] = acc[(p < q ? p : q) + 1][(p < q ? q : p) + 1];
 }
 
-template <int P>
+template <int P, int KC>
 __global__ __launch_bounds__(TENSOR_WG) void k_data_tensors(int T, int K, int Ks, int N, const double* __restrict__ X,
                                                             const double* __restrict__ Y, double* __restrict__ YX,
                                                             double* __restrict__ Bt, double* __restrict__ Dt,
@@ -297,9 +273,9 @@ __global__ __launch_bounds__(TENSOR_WG) void k_data_tensors(int T, int K, int Ks
                                                             double* __restrict__ dd) {
   const int n = blockIdx.x * TENSOR_WG + threadIdx.x;
   if (n >= N) return;
-  const int k0 = blockIdx.y * TENSOR_KC;
+  const int k0 = blockIdx.y * KC;
   if (k0 < K)
-    tensor_cross<P>(T, K, Ks, N, n, k0, X, Y, YX, Bt, Dt);
+    tensor_cross<P, KC>(T, K, Ks, N, n, k0, X, Y, YX, Bt, Dt);
   else
     tensor_auto<P>(T, N, n, Y, YY, dY, dd);
 }
@@ -313,15 +289,15 @@ __global__ __launch_bounds__(TENSOR_WG) void k_data_tensors(int T, int K, int Ks
 // blockIdx.y = 0: the block; the others, if any, b_n, ASM_KC regressors each.
 // From K = 14 on the block's registers leave one wavefront a SIMD, which b_n's
 // loads then wait in: there it has a kernel of its own (N = 52,740; two kernels
-// against one, us: K = 6 13 + 12 and 14, K = 10 25 + 13 and 28, K = 11 26 + 14 and
-// 34, K = 13 36 + 16 and 45, K = 15 60 + 21 and 104, K = 16 67 + 19 and 108),
-// unless the launch leaves SIMDs empty anyway (at most ASM_FEW workgroups;
-// K = 16, N = 908: 43 + 12 and 46).
+// against one, us: K = 6 12 + 11 and 15, K = 10 27 + 13 and 32, K = 11 29 + 14 and
+// 35, K = 13 38 + 16 and 43, K = 15 53 + 18 and 78, K = 16 63 + 19 and 86), unless
+// the launch leaves SIMDs empty anyway (at most ASM_FEW workgroups; K = 16,
+// N = 908: 35 + 5 and 37).
 // Bound: the tensors read for b_n and the three packed arrays written, all
 // coalesced (at K = 15, P = 3, N = 52,740: 225 MB, 45 us at 5 TB/s).
 // Measured there 81 us; the rows of [N][K][K] blocks written by one kernel
 // and gathered again by the packing kernel, a lane's rows K*K*8 bytes apart,
-// took 112 + 57 us (K = 6: 29 + 9 to 14 us).
+// took 112 + 57 us (K = 6: 29 + 9 to 16 us).
 constexpr int ASM_WG = 64;
 constexpr int ASM_KC = 3;   // regressors of b_w per lane
 template <int K> constexpr bool ASM_FUSED = K <= 13;
@@ -363,22 +339,19 @@ __device__ __forceinline__ void rhs_entries(int K, int P, int N, int n, int k0, 
   for (int c = 0; c < ASM_KC; ++c) {
     const int k = k0 + c;
     if (k >= K) break;
-    double acc = 0.0;   // the small terms first
+    double acc = 0.0;
 #pragma unroll
     for (int p = 0; p < PMAX; ++p) {
       if (p < P) {
-        acc -= Bt[((size_t)p * K + k) * N + n] * m1[p];
+        acc = __builtin_fma(Bt[((size_t)p * K + k) * N + n], m1[p], acc);
 #pragma unroll
-        for (int q = p; q < PMAX; ++q) {
-          if (q < P) {
-            double d = Dt[(((size_t)p * K + k) * P + q) * N + n];
-            if (q != p) d += Dt[(((size_t)q * K + k) * P + p) * N + n];
-            acc += d * m2[tab_pair(p, q, PMAX)];
-          }
-        }
+        for (int q = 0; q < PMAX; ++q)
+          if (q < P)
+            acc = __builtin_fma(-Dt[(((size_t)p * K + k) * P + q) * N + n],
+                                m2[p <= q ? tab_pair(p, q, PMAX) : tab_pair(q, p, PMAX)], acc);
       }
     }
-    bw[(size_t)k * N + n] = lam * (YX[(size_t)k * N + n] + acc);
+    bw[(size_t)k * N + n] = lam * (YX[(size_t)k * N + n] - acc);
   }
 }
 
@@ -393,10 +366,10 @@ __global__ __launch_bounds__(ASM_WG) void k_data_assemble(int P, int N, int Ns, 
                                                           int* __restrict__ bad, double* __restrict__ bw) {
   // the coefficient table in LDS (every lane reads the same entry)
   constexpr int NB = K * (K + 1) / 2;
-  __shared__ double tab[NB * TAB];
+  __shared__ double tab[NB * BTAB];
   const bool rhs = blockIdx.y > 0;
   if (!rhs)
-    for (int i = threadIdx.x; i < NB * TAB; i += ASM_WG) tab[i] = Tab[i];
+    for (int i = threadIdx.x; i < NB * BTAB; i += ASM_WG) tab[i] = Tab[i];
   __syncthreads();
   const int n = blockIdx.x * ASM_WG + threadIdx.x;
   if (n >= N) return;
@@ -407,18 +380,32 @@ __global__ __launch_bounds__(ASM_WG) void k_data_assemble(int P, int N, int Ns, 
     rhs_entries(K, P, N, n, ((int)blockIdx.y - 1) * ASM_KC, lam, m1, m2, YX, Bt, Dt, bw);
     return;
   }
+  // B_kl and B_lk, each in the order of its own terms (S_plkq = S_qklp), averaged;
+  // terms past P add zero
   auto entry = [&](int e) {
-    const double* t = tab + e * TAB;
-    double g = 0.0;
+#pragma clang fp contract(off)
+    const double* t = tab + e * BTAB;
+    double u = 0.0, v = 0.0;
 #pragma unroll
-    for (int p = 0; p < PMAX; ++p) g += t[1 + p] * m1[p];
+    for (int p = 0; p < PMAX; ++p) {
+      u = __builtin_fma(t[1 + p], m1[p], u);
+      v = __builtin_fma(t[1 + p], m1[p], v);
 #pragma unroll
-    for (int i = 0; i < ASM_NQ; ++i) g += t[1 + PMAX + i] * m2[i];
-    return lam * (t[0] + g);
+      for (int q = 0; q < PMAX; ++q) {
+        const double m = m2[p <= q ? tab_pair(p, q, PMAX) : tab_pair(q, p, PMAX)];
+        u = __builtin_fma(-t[1 + PMAX + p * PMAX + q], m, u);
+        v = __builtin_fma(-t[1 + PMAX + q * PMAX + p], m, v);
+      }
+    }
+    return 0.5 * (lam * (t[0] - u) + lam * (t[0] - v));
   };
   if constexpr (K <= KREG) {
 #pragma unroll
-    for (int e = 0; e < NB; ++e) a[e] = entry(e);
+    for (int e = 0; e < NB; ++e) {
+      a[e] = entry(e);
+      // (or the compiler loads the table of many entries at once and spills)
+      if (e % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+    }
   } else {
 #pragma unroll 1
     for (int e = 0; e < NB; ++e) a[e] = entry(e);
@@ -701,24 +688,30 @@ size_t data_table_at(int K, int P) {
   return (n + TAB - 1) / TAB * TAB;
 }
 
-size_t data_globals_size(int K, int P) { return data_table_at(K, P) + (size_t)(K * (K + 1) / 2) * TAB; }
+size_t data_globals_size(int K, int P) { return data_table_at(K, P) + (size_t)(K * (K + 1) / 2) * (TAB + BTAB); }
 
 int data_design_stride(int K) { return (K + TENSOR_KC - 1) / TENSOR_KC * TENSOR_KC; }
 
 hipError_t launch_data_tensors(hipStream_t s, int T, int K, int P, int N, const double* X, const double* Y,
                                double* G, double* YX, double* Bt, double* Dt, double* YY, double* dY, double* dd) {
   const int nG = K * K + K * K * P + P * K * K * P, Ks = data_design_stride(K);
-  GP_LAUNCH(k_data_globals, dim3((nG + DT / 64 - 1) / (DT / 64)), dim3(DT), 0, s, T, K, Ks, P, X, G);
+  GP_LAUNCH(k_data_globals, dim3((nG + DT - 1) / DT), dim3(DT), 0, s, T, K, Ks, P, X, G);
   if (hipError_t e = hipGetLastError()) return e;
   const int nT = K * (K + 1) / 2 * TAB;
   GP_LAUNCH(k_data_table, dim3((nT + DT - 1) / DT), dim3(DT), 0, s, K, P, G, G + data_table_at(K, P));
   if (hipError_t e = hipGetLastError()) return e;
-  const dim3 g((N + TENSOR_WG - 1) / TENSOR_WG, (K + TENSOR_KC - 1) / TENSOR_KC + 1), b(TENSOR_WG);
-  switch (P) {
-#define X_P(PP) \
-  case PP: GP_LAUNCH(k_data_tensors<PP>, g, b, 0, s, T, K, Ks, N, X, Y, YX, Bt, Dt, YY, dY, dd); break;
+  const unsigned nb = (N + TENSOR_WG - 1) / TENSOR_WG;
+  const int kc = nb * K <= 400 ? 1 : nb * ((K + TENSOR_KC - 1) / TENSOR_KC) <= 800 ? 2 : TENSOR_KC;
+  const dim3 g(nb, (K + kc - 1) / kc + 1), b(TENSOR_WG);
+  switch (P * 8 + kc) {
+#define X_PC(PP, CC)                                                                                     \
+  case PP * 8 + CC:                                                                                      \
+    GP_LAUNCH((k_data_tensors<PP, CC>), g, b, 0, s, T, K, Ks, N, X, Y, YX, Bt, Dt, YY, dY, dd);           \
+    break;
+#define X_P(PP) X_PC(PP, 1) X_PC(PP, 2) X_PC(PP, TENSOR_KC)
     X_P(0) X_P(1) X_P(2) X_P(3) X_P(4)
 #undef X_P
+#undef X_PC
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -758,7 +751,7 @@ hipError_t launch_data_assemble(hipStream_t s, int K, int P, int N, int Ns, cons
                                 const double* Bt, const double* Dt, const double* lambda, const double* A,
                                 double* B64, float* B32, double* L64, int* bad, double* bw) {
   if (P > PMAX) return hipErrorInvalidValue;
-  const double* tab = G + data_table_at(K, P);
+  const double* tab = G + data_table_at(K, P) + (size_t)(K * (K + 1) / 2) * TAB;
   const dim3 g((N + ASM_WG - 1) / ASM_WG), b(ASM_WG);
   const unsigned nrhs = bw ? (K + ASM_KC - 1) / ASM_KC : 0;
   bool fused;

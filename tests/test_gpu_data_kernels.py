@@ -2,6 +2,8 @@
 the explicit whitening of every scan (Appendix A.2) in NumPy: few scans (the
 lag windows of the two ends overlap), voxel counts around a wavefront, every
 AR order, K on both sides of the regressor chunk."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -126,65 +128,58 @@ def test_blocks_and_residual_sums_over_draws(g, ctx, torch_cuda, P, Ns, nx, K):
     g.gp_op_destroy(op)
 
 
-@pytest.mark.parametrize("K,P,T,Ns", [(6, 3, 200, 1), (15, 3, 200, 5), (4, 1, 160, 2), (5, 0, 160, 1)])
-def test_sums_over_scans_round_less_than_one_chain(g, ctx, torch_cuda, K, P, T, Ns):
-    """b_w and the residual sums of data with a large mean, against 80-bit
-    arithmetic, beside the same tensors summed scan by scan in one chain and
-    combined in FP64 (NumPy).  A chain of n additions of like terms is off by
-    about sqrt(n / 3) roundings of the whole, parts of 28 scans by about
-    sqrt(28 / 3 / (n / 28) + n / 28 / 3): 0.25 of the chain at n = 200, with
-    the few roundings of the combination on both sides under 0.6; b_w is held
-    to 0.7 of the chain's error and the residual sums too."""
+@pytest.mark.parametrize("K,P,T", [(6, 3, 45), (15, 3, 31), (3, 4, 40), (5, 1, 140), (4, 2, 19), (2, 0, 23)])
+def test_sums_over_scans_are_one_chain_each(g, ctx, torch_cuda, K, P, T):
+    """Every sum over scans is one chain of fused multiply-adds, and B_n and b_w
+    add their terms in the order of their definition: the bits of the same
+    operations done here with libm's fma, at voxel counts of each split of the
+    regressors (few, more and many wavefronts)."""
     torch = torch_cuda
-    nx, q = 1000, np.longdouble
-    r = np.random.default_rng(K + T)
-    X = r.standard_normal((T, K))
-    X[:, 0] = 1.0
-    W = r.standard_normal((Ns, K, nx))
-    W[:, 0] += 100.0
-    Y = X @ W[0] + r.standard_normal((T, nx))
-    A = r.uniform(-0.4, 0.4, (Ns, P, nx))
-    lam = r.uniform(0.5, 2.0, nx)
-    # sums over scans of y[t - a] X[t - b] and of y[t - a] y[t - b], one chain each
-    C, D = np.zeros((P + 1, P + 1, K, nx)), np.zeros((P + 1, P + 1, nx))
+    libm = ctypes.CDLL("libm.so.6")
+    libm.fma.restype, libm.fma.argtypes = ctypes.c_double, [ctypes.c_double] * 3
+    ufma = np.frompyfunc(libm.fma, 3, 1)
+
+    def fma(x, y, z):
+        return ufma(x, y, z).astype(np.float64)
+
+    few, sizes = 20, (20, 64 * (400 // K) + 65, 64 * 801 + 7)
+    X, Y, A, lam = problem(sizes[-1], K, T, P, 1, K + P)
+    y, a, lm = Y[:, :few], A[0, :, :few], lam[:few]
+    XX, YX = np.zeros((K, K)), np.zeros((K, few))
+    R, S = np.zeros((K, K, P)), np.zeros((P, K, K, P))
+    Bt, Dt = np.zeros((P, K, few)), np.zeros((P, K, P, few))
     for t in range(P, T):
-        for a in range(P + 1):
-            for b in range(P + 1):
-                C[a, b] += X[t - b][:, None] * Y[t - a]
-                D[a, b] += Y[t - a] * Y[t - b]
-    G = np.array([[X[P - a:T - a].T @ X[P - b:T - b] for b in range(P + 1)] for a in range(P + 1)])
-    c = np.concatenate([np.ones((Ns, 1, nx)), -A], 1)
-    cq, Xq, Yq = c.astype(q), X.astype(q), Y.astype(q)
-    bw, bwq = np.zeros((K, nx)), np.zeros((K, nx), q)
-    rss, rssq = np.zeros(nx), np.zeros(nx, q)
-    for a in range(P, -1, -1):   # the small terms first
-        for b in range(P, -1, -1):
-            bw += (c[:, a] * c[:, b]).mean(0) * C[a, b]
-            bwq += (cq[:, a] * cq[:, b]).mean(0) * (Xq[P - b:T - b].T @ Yq[P - a:T - a])
-            for j in range(Ns):
-                quad = (W[j] * (G[a, b] @ W[j])).sum(0)
-                rss += c[j, a] * c[j, b] * (D[a, b] - 2.0 * (C[a, b] * W[j]).sum(0) + quad)
-    bw, bwq, rss = lam * bw, lam.astype(q) * bwq, rss / Ns
-    for j in range(Ns):
-        e = Yq - Xq @ W[j].astype(q)
-        f = sum(cq[j, a] * e[P - a:T - a] for a in range(P + 1))
-        rssq += (f * f).sum(0) / Ns
-    op = g.gp_op_create(ctx, np.ones((1, 1, nx), dtype=np.uint8), 4, K)
-    g.gp_op_set_alpha(op, np.zeros(K))
-    d = g.gp_data_create(op, T, P, X, dev(torch, Y))
-    out = torch.zeros((K, nx), dtype=torch.float64, device="cuda")
-    res = torch.zeros(nx, dtype=torch.float64, device="cuda")
-    Ad = dev(torch, A) if P else None
-    g.gp_data_assemble(d, dev(torch, lam), Ns, Ad, out)
-    g.gp_data_lambda(d, Ns, dev(torch, W), Ad, 10.0, 0.1, res, None, None)
-    g.gp_data_destroy(d)
-    g.gp_op_destroy(op)
-
-    def off(v, ref):
-        return float(np.sqrt(((v - ref) ** 2).sum() / (ref ** 2).sum()))
-
-    assert off(out.cpu().numpy(), bwq) <= 0.7 * off(bw, bwq)
-    assert off(res.cpu().numpy(), rssq) <= 0.7 * off(rss, rssq)
+        x, lx, ly = X[t], X[t - P:t][::-1], y[t - P:t][::-1]   # row p: t - 1 - p
+        XX = fma(x[:, None], x, XX)
+        YX = fma(y[t], x[:, None], YX)
+        if P:
+            R = fma(x[:, None, None], lx.T, R)
+            S = fma(lx[:, :, None, None], lx.T, S)
+            Bt = Bt + fma(y[t], lx[:, :, None], ly[:, None] * x[:, None])
+            Dt = fma(ly[:, None, None], lx.T[:, :, None], Dt)
+    B, b = np.zeros((few, K, K)), np.zeros((K, few))
+    for p in range(P):
+        b = fma(Bt[p], a[p], b)
+        B = fma((R[..., p] + R[..., p].T), a[p][:, None, None], B)
+        for q in range(P):
+            b = fma(-Dt[p, :, q], a[p] * a[q], b)
+            B = fma(-S[p, ..., q], (a[p] * a[q])[:, None, None], B)
+    b = lm * (YX - b)
+    B = lm[:, None, None] * (XX - B)
+    B = 0.5 * (B + B.transpose(0, 2, 1))
+    for nx in sizes:
+        op = g.gp_op_create(ctx, np.ones((1, 1, nx), dtype=np.uint8), 4, K)
+        g.gp_op_set_alpha(op, np.zeros(K))
+        d = g.gp_data_create(op, T, P, X, dev(torch, Y[:, :nx]))
+        bw = torch.zeros((K, nx), dtype=torch.float64, device="cuda")
+        g.gp_data_assemble(d, dev(torch, lam[:nx]), 1, dev(torch, A[:, :, :nx]) if P else None, bw)
+        unit = torch.eye(K, dtype=torch.float64, device="cuda")[:, :, None].expand(K, K, nx).contiguous()
+        cols = torch.empty_like(unit)
+        g.gp_apply(op, K, unit, cols)
+        g.gp_data_destroy(d)
+        g.gp_op_destroy(op)
+        assert np.array_equal(bw[:, :few].cpu().numpy(), b), nx
+        assert np.array_equal(cols[:, :, :few].cpu().numpy(), B.transpose(1, 2, 0)), nx
 
 
 @pytest.mark.parametrize("K", [10, 13, 14, 15, 24])
